@@ -112,10 +112,10 @@ void exclusive_scan_u64(const uint64_t* in, uint64_t* out, int64_t n, uint64_t* 
 void exclusive_scan_u32_to_u64(const uint32_t* in, uint64_t* out, int64_t n, uint64_t* total_dev,
                                hipStream_t s);
 
-// Stable LSD radix sort of 64-bit keys over bits [0, end_bit), with an
+// Stable LSD radix sort of 64-bit keys over bits [begin_bit, end_bit), with an
 // optional 32-bit payload.  Result is left in keys/vals (buffers swapped
 // internally through the provided temporaries of the same size).
-void radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int end_bit, uint64_t* tmp_keys,
+void radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int begin_bit, int end_bit, uint64_t* tmp_keys,
                     uint32_t* tmp_vals, hipStream_t s);
 
 }  // namespace lds

@@ -264,16 +264,16 @@ __global__ __launch_bounds__(NT) void k_sort_rows_block(const int64_t* rp, int64
     for (int i = threadIdx.x; i < len; i += NT) col[s0 + i] = v[i];
 }
 
-// keys (row << 32 | column) of the slots of rows [0, r1) and back
-__global__ void k_row_keys(const int64_t* rp, int64_t r1, const int32_t* col, uint64_t* keys) {
+// keys (row << vb | column) of the slots of rows [0, r1) and back
+__global__ void k_row_keys(const int64_t* rp, int64_t r1, int vb, const int32_t* col, uint64_t* keys) {
     for (int64_t r = blockIdx.x; r < r1; r += gridDim.x)
         for (int64_t q = rp[r] + threadIdx.x; q < rp[r + 1]; q += kT)
-            keys[q - rp[0]] = ((uint64_t)r << 32) | (uint32_t)col[q];
+            keys[q - rp[0]] = ((uint64_t)r << vb) | (uint32_t)col[q];
 }
 
-__global__ void k_row_unkeys(const uint64_t* keys, int64_t n, int32_t* col) {
+__global__ void k_row_unkeys(const uint64_t* keys, int64_t n, int vb, int32_t* col) {
     const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (i < n) col[i] = (int32_t)(uint32_t)keys[i];
+    if (i < n) col[i] = (int32_t)(keys[i] & ((1ull << vb) - 1));
 }
 
 // ------------------------------------------------------ heavy 2D part
@@ -717,7 +717,7 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         LDS_HIP(hipGetLastError());
         dsrc.release();
         ddst.release();
-        radix_sort_u64(keys.p, nullptr, nk, 2 * vb, tmp.p, nullptr, s);
+        radix_sort_u64(keys.p, nullptr, nk, 0, 2 * vb, tmp.p, nullptr, s);
         DBuf<uint32_t> flag;
         flag.alloc(nk, s);
         k_unique_flags<<<grid_for(nk, kT), kT, 0, s>>>(keys.p, nk, sentinel, strict, flag.p, err.p);
@@ -777,7 +777,8 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         rt.alloc(n, s);
         k_relabel_keys<<<grid_for(n, kT), kT, 0, s>>>(deg_orig.p, n, vb, g.max_deg, rk.p);
         LDS_HIP(hipGetLastError());
-        radix_sort_u64(rk.p, nullptr, n, vb + bits_for((uint64_t)g.max_deg), rt.p, nullptr, s);
+        // keys in id order: the stable sort needs the degree bits only
+        radix_sort_u64(rk.p, nullptr, n, vb, vb + bits_for((uint64_t)g.max_deg), rt.p, nullptr, s);
         k_relabel_apply<<<grid_for(n, kT), kT, 0, s>>>(rk.p, n, vb, deg_orig.p, g.orig_of.p, g.int_of.p,
                                                       g.deg.p);
         LDS_HIP(hipGetLastError());
@@ -838,10 +839,10 @@ void sort_rows(Graph& g, hipStream_t s) {
             DBuf<uint64_t> keys, tmp;
             keys.alloc(nk, s);
             tmp.alloc(nk, s);
-            k_row_keys<<<(unsigned)std::min<int64_t>(rb, 65535), kT, 0, s>>>(g.rowptr.p, rb, g.col.p, keys.p);
+            k_row_keys<<<(unsigned)std::min<int64_t>(rb, 65535), kT, 0, s>>>(g.rowptr.p, rb, g.vbits, g.col.p, keys.p);
             LDS_HIP(hipGetLastError());
-            radix_sort_u64(keys.p, nullptr, nk, 32 + bits_for((uint64_t)rb), tmp.p, nullptr, s);
-            k_row_unkeys<<<grid_for(nk, kT), kT, 0, s>>>(keys.p, nk, g.col.p);
+            radix_sort_u64(keys.p, nullptr, nk, 0, g.vbits + bits_for((uint64_t)rb), tmp.p, nullptr, s);
+            k_row_unkeys<<<grid_for(nk, kT), kT, 0, s>>>(keys.p, nk, g.vbits, g.col.p);
             LDS_HIP(hipGetLastError());
         }
         if (r512 > rb) k_sort_rows_block<256, 4096><<<(unsigned)(r512 - rb), 256, 0, s>>>(g.rowptr.p, rb, g.col.p);

@@ -173,16 +173,16 @@ void exclusive_scan_u32_to_u64(const uint32_t* in, uint64_t* out, int64_t n, uin
     scan_impl<uint32_t>(in, out, n, total_dev, s);
 }
 
-void radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int end_bit, uint64_t* tmp_keys,
+void radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int begin_bit, int end_bit, uint64_t* tmp_keys,
                     uint32_t* tmp_vals, hipStream_t s) {
-    if (n <= 1 || end_bit <= 0) return;
+    if (n <= 1 || end_bit <= begin_bit) return;
     const int64_t nblocks = (n + kTile - 1) / kTile;
     DBuf<uint64_t> hist;
     hist.alloc((size_t)256 * nblocks, s);
     uint64_t *ka = keys, *kb = tmp_keys;
     uint32_t *va = vals, *vb = tmp_vals;
     int passes = 0;
-    for (int shift = 0; shift < end_bit; shift += 8, ++passes) {
+    for (int shift = begin_bit; shift < end_bit; shift += 8, ++passes) {
         k_radix_hist<<<grid_for(nblocks, 1), kThreads, 0, s>>>(ka, n, shift, hist.p, nblocks);
         LDS_HIP(hipGetLastError());
         exclusive_scan_u64(hist.p, hist.p, 256 * nblocks, nullptr, s);

@@ -9,12 +9,15 @@
 // internal ids a > b > c is found exactly once, from the oriented edge
 // (a -> b), as the element c of N+(a) ∩ N+(b).
 //
-// Per oriented edge, one thread probes the shorter out-list against the
-// longer one by binary search.  A count pass, an exclusive scan and a write
-// pass give a deterministic order (oriented edges in CSR order, c ascending).
+// A wave takes up to 64 oriented edges of one vertex and looks up the shorter
+// out-list of each edge's ends in the other (k_tri_units).  A count pass, an
+// exclusive scan and a write pass give a deterministic order (oriented edges
+// in CSR order, c ascending).
 // The incidence CSR for the Frank-Wolfe pull sweep then holds, for every
 // vertex with t_u > 0 (rows ordered by t_u descending), the other two
 // vertices of each of its triangles, in triangle order.
+#include <algorithm>
+
 #include "graph.hpp"
 
 namespace lds {
@@ -38,55 +41,197 @@ __global__ void k_outdeg(const int64_t* rp, const int32_t* col, int64_t n, int32
     outdeg[u] = (int32_t)(lower_bound_i32(col, rp[u], rp[u + 1], (int32_t)u) - rp[u]);
 }
 
-// slot s of row u is an oriented edge u -> v iff v < u; emit / count the
-// common out-neighbours of u and v (all are < v since N+(v) < v)
-template <bool WRITE>
-__global__ void k_tri_edges(const int64_t* rp, const int32_t* col, const int32_t* outdeg, int64_t n, int64_t ns,
-                            uint32_t* cnt, const uint64_t* off, int32_t* tri) {
-    const int64_t s = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (s >= ns) return;
-    // row of slot s
-    int64_t lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (rp[mid] <= s) lo = mid; else hi = mid - 1;
-    }
-    const int32_t u = (int32_t)lo;
-    const int32_t v = col[s];
-    uint32_t c = 0;
-    if (v < u) {
-        const int64_t ua = rp[u], ub = rp[u] + outdeg[u];
-        const int64_t va = rp[v], vb = rp[v] + outdeg[v];
-        // probe the shorter list against the longer
-        const bool ushort = (ub - ua) <= (vb - va);
-        const int64_t pa = ushort ? ua : va, pb = ushort ? ub : vb;
-        const int64_t qa = ushort ? va : ua, qb = ushort ? vb : ub;
-        uint64_t o = WRITE ? off[s] : 0;
-        int64_t q = qa;
-        for (int64_t i = pa; i < pb; ++i) {
-            const int32_t w = col[i];
-            if (w >= v) break;  // lists ascending; common elements are < v
-            q = lower_bound_i32(col, q, qb, w);
-            if (q < qb && col[q] == w) {
-                if (WRITE) {
-                    tri[3 * o + 0] = u;
-                    tri[3 * o + 1] = v;
-                    tri[3 * o + 2] = w;
-                    ++o;
-                }
-                ++c;
-            }
-        }
-    }
-    if (!WRITE) cnt[s] = c;
+// The listing works in units: up to kUnitEdges consecutive oriented edges
+// u -> v_i (v_i = N+(u)[i], i in [i0, i0 + kUnitEdges)) of one vertex, one
+// wave each.  Edge i has candidates w: either all of N+(v_i) ("walk", looked up
+// in N+(u)[0, i), staged in LDS) or all of N+(u)[0, i) ("probe", looked up in
+// N+(v_i) in memory), both ascending, whichever is shorter up to the factor
+// kProbeBias that a lookup in memory costs over one in LDS.  The candidates of
+// a unit's edges are numbered consecutively and dealt to the lanes, so a wave
+// is full whatever the list lengths, neighbouring lanes read neighbouring
+// column entries, and ballots give the triangles in (edge, w) order.
+// Bound: latency of the lookups.  One thread per slot of the CSR (both
+// orientations, the row found by binary search, one list probed serially in
+// the other) took 4.4 ms to count and 5.0 ms to write on 1M vertices, 2e7
+// edges, 1.3e7 triangles; by units 1.2 and 1.5 ms.
+constexpr int kUnitEdges = 64;
+constexpr int kUnitList = 1024;  // entries of N+(u) staged per wave; longer lists are read from memory
+constexpr int kProbeBias = 4;
+
+__device__ inline int64_t unit_count(int32_t outdeg) {
+    return outdeg < 2 ? 0 : (outdeg + kUnitEdges - 1) / kUnitEdges;
 }
 
-__global__ void k_tcount(const int32_t* tri, int64_t T, int32_t* tc) {
-    const int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (t >= T) return;
-    atomicAdd(&tc[tri[3 * t]], 1);
-    atomicAdd(&tc[tri[3 * t + 1]], 1);
-    atomicAdd(&tc[tri[3 * t + 2]], 1);
+__global__ void k_unit_counts(const int32_t* outdeg, int64_t n, uint32_t* cnt) {
+    const int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (u < n) cnt[u] = (uint32_t)unit_count(outdeg[u]);
+}
+
+__global__ void k_unit_fill(const int32_t* outdeg, const uint64_t* first, int64_t n, int32_t* unit_u,
+                            int32_t* unit_i0) {
+    const int64_t u = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (u >= n) return;
+    const int64_t c = unit_count(outdeg[u]), o = (int64_t)first[u];
+    for (int64_t k = 0; k < c; ++k) {
+        unit_u[o + k] = (int32_t)u;
+        unit_i0[o + k] = (int32_t)(k * kUnitEdges);
+    }
+}
+
+__device__ inline uint32_t wave_incl_scan_u32(uint32_t x) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)x, d, 64);
+        if (lane >= d) x += y;
+    }
+    return x;
+}
+
+// count (WRITE = false: cnt per unit) or write (tri from off[unit], and the
+// counts of the first two members: one atomic per unit for u, one per edge
+// for v; the third members are counted by k_member_count)
+template <bool WRITE>
+__global__ __launch_bounds__(kT) void k_tri_units(const int64_t* rp, const int32_t* col, const int32_t* outdeg,
+                                                  const int32_t* unit_u, const int32_t* unit_i0, int64_t units,
+                                                  uint32_t* cnt, const uint64_t* off, int32_t* tri, int32_t* tc) {
+    constexpr int NW = kT / 64;
+    __shared__ int32_t list[NW][kUnitList];
+    __shared__ uint32_t pre[NW][kUnitEdges];    // inclusive candidate counts of the unit's edges
+    __shared__ uint32_t ecnt[NW][kUnitEdges];   // WRITE: triangles of each edge
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t k = (int64_t)blockIdx.x * NW + w;
+    if (k >= units) return;  // whole waves; no workgroup barrier below
+    const int32_t u = unit_u[k];
+    const int i0 = unit_i0[k];
+    const int du = outdeg[u];
+    const int64_t ua = rp[u];
+    const int need = min(du, i0 + kUnitEdges);
+    const bool staged = need <= kUnitList;
+    const int i = i0 + lane;
+    int32_t v = 0;
+    int dv = 0;
+    int64_t va = 0;
+    if (i < du) {
+        v = col[ua + i];
+        dv = outdeg[v];
+        va = rp[v];
+    }
+    if (staged)
+        for (int q = lane; q < need; q += 64) list[w][q] = col[ua + q];
+    const bool walk = (int64_t)dv <= (int64_t)kProbeBias * i;
+    const uint32_t items = i < du && dv > 0 ? (uint32_t)(walk ? dv : i) : 0u;
+    const uint32_t inc = wave_incl_scan_u32(items);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    pre[w][lane] = inc;
+    if (WRITE) ecnt[w][lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    uint32_t found = 0;
+    uint64_t o = WRITE ? off[k] : 0;
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    for (uint32_t base = 0; base < total; base += 64) {
+        const uint32_t c = base + (uint32_t)lane;
+        const bool in = c < total;
+        // the edge of candidate c: first e with pre[e] > c
+        int e = 0;
+#pragma unroll
+        for (int st = 32; st > 0; st >>= 1)
+            if (pre[w][e + st - 1] <= c) e += st;
+        if (!in) e = 63;
+        const int32_t ev = __shfl(v, e, 64);
+        const int edv = __shfl(dv, e, 64);
+        const int64_t eva = ((int64_t)__shfl((int)(va >> 32), e, 64) << 32) | (uint32_t)__shfl((int)(uint32_t)va, e, 64);
+        const int ei = i0 + e;
+        const uint32_t q = c - (e > 0 ? pre[w][e - 1] : 0u);
+        bool hit = false;
+        int32_t x = 0;
+        if (in) {
+            if ((int64_t)edv <= (int64_t)kProbeBias * ei) {  // walk N+(v), look up in N+(u)[0, ei)
+                x = col[eva + q];
+                if (staged) {
+                    int lo = 0, hi = ei;
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        if (list[w][mid] < x) lo = mid + 1; else hi = mid;
+                    }
+                    hit = lo < ei && list[w][lo] == x;
+                } else {
+                    const int64_t p = lower_bound_i32(col, ua, ua + ei, x);
+                    hit = p < ua + ei && col[p] == x;
+                }
+            } else {  // probe N+(u)[0, ei) in N+(v)
+                x = staged ? list[w][q] : col[ua + q];
+                const int64_t p = lower_bound_i32(col, eva, eva + edv, x);
+                hit = p < eva + edv && col[p] == x;
+            }
+        }
+        const uint64_t H = __ballot(hit);
+        if (WRITE) {
+            if (hit) {
+                const uint64_t t = o + (uint64_t)__popcll(H & lt);
+                tri[3 * t + 0] = u;
+                tri[3 * t + 1] = ev;
+                tri[3 * t + 2] = x;
+                atomicAdd(&ecnt[w][e], 1u);
+            }
+            o += (uint64_t)__popcll(H);
+        }
+        found += (uint32_t)__popcll(H);
+    }
+    if (!WRITE) {
+        if (lane == 0) cnt[k] = found;
+        return;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (ecnt[w][lane]) atomicAdd(&tc[v], (int32_t)ecnt[w][lane]);
+    if (lane == 0 && found) atomicAdd(&tc[u], (int32_t)found);
+}
+
+// Counts of a list of member ids (every stride-th entry of ids, from the
+// first): patterns crowd on the vertices of smallest internal id, so the
+// counts of the first nh ids are kept in an LDS histogram per workgroup
+// (nearly the whole LDS of a CU) and added once at the end; the rest are
+// atomics in memory.  Bound: atomic rate.  One atomic per member on the list
+// in memory took 4.6 ms for 3.7e7 triangle members, and a histogram of 8192
+// ids left 14 ms on 1.8e8 members of 4-cliques, whose blocks' vertices lie
+// past it; this one takes 0.2 (for the 1.3e7 third members) and 0.8 ms.
+constexpr int kCountIds = 36864;
+constexpr int kCountT = 1024;
+constexpr int64_t kCountPerWG = 16384;  // entries that are worth a workgroup's histogram
+__global__ __launch_bounds__(kCountT) void k_member_count(const int32_t* ids, int64_t count, int stride, int nh,
+                                                          int32_t* cnt) {
+    extern __shared__ int32_t hist[];
+    for (int i = threadIdx.x; i < nh; i += kCountT) hist[i] = 0;
+    __syncthreads();
+    const int64_t step = (int64_t)gridDim.x * kCountT;
+    for (int64_t t0 = (int64_t)blockIdx.x * kCountT + threadIdx.x; t0 < count; t0 += 4 * step) {
+        int32_t x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = t0 + q * step < count ? ids[(t0 + q * step) * stride] : -1;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (x[q] < 0) continue;
+            if (x[q] < nh)
+                atomicAdd(&hist[x[q]], 1);
+            else
+                atomicAdd(&cnt[x[q]], 1);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < nh; i += kCountT)
+        if (hist[i]) atomicAdd(&cnt[i], hist[i]);
+}
+
+void count_members(const int32_t* ids, int64_t count, int stride, int64_t n, int32_t* cnt, hipStream_t s) {
+    if (count <= 0) return;
+    const int nh = (int)std::min<int64_t>(n, kCountIds);
+    LDS_HIP(hipFuncSetAttribute((const void*)k_member_count, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kCountIds * (int)sizeof(int32_t)));
+    const unsigned grid = std::min(grid_for(count, (int)kCountPerWG), kReduceWG);
+    k_member_count<<<grid, kCountT, (size_t)nh * sizeof(int32_t), s>>>(ids, count, stride, nh, cnt);
+    LDS_HIP(hipGetLastError());
 }
 
 __global__ void k_tmax(const int32_t* tc, int64_t n, int* out, unsigned long long* nz) {
@@ -200,28 +345,6 @@ __global__ void k_clique_tris(const int64_t* rp, const int32_t* col, const int32
     if (!WRITE) cnt[t] = k;
 }
 
-// per-vertex 4-clique counts.  Internal ids are ordered by degree, so the
-// vertices in most cliques have the smallest ids: their counts are kept in
-// an LDS histogram per workgroup (one global atomic per workgroup and hub at
-// the end) instead of millions of atomics on a few addresses.
-constexpr int kHubIds = 8192;
-__global__ __launch_bounds__(kT) void k_qcount(const int32_t* q4, int64_t Q, int32_t* qc) {
-    __shared__ int32_t hist[kHubIds];
-    for (int i = threadIdx.x; i < kHubIds; i += kT) hist[i] = 0;
-    __syncthreads();
-    for (int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x; t < Q; t += (int64_t)gridDim.x * kT)
-        for (int j = 0; j < 4; ++j) {
-            const int32_t v = q4[4 * t + j];
-            if (v < kHubIds)
-                atomicAdd(&hist[v], 1);
-            else
-                atomicAdd(&qc[v], 1);
-        }
-    __syncthreads();
-    for (int i = threadIdx.x; i < kHubIds; i += kT)
-        if (hist[i]) atomicAdd(&qc[i], hist[i]);
-}
-
 template <class T>
 T d2h(const T* p, hipStream_t s) {
     T v;
@@ -269,7 +392,8 @@ void build_incidence_plan(Graph& g, const int32_t* pat, int64_t np, const int32_
         rt.alloc(n, s);
         k_row_keys<<<grid_for(n, kT), kT, 0, s>>>(count, n, vb, (int32_t)cmax, rk.p);
         LDS_HIP(hipGetLastError());
-        radix_sort_u64(rk.p, nullptr, n, vb + bits_for((uint64_t)cmax), rt.p, nullptr, s);
+        // keys in id order: the stable sort needs the count bits only
+        radix_sort_u64(rk.p, nullptr, n, vb, vb + bits_for((uint64_t)cmax), rt.p, nullptr, s);
         k_row_apply<<<grid_for(nrows, kT), kT, 0, s>>>(rk.p, nrows, vb, count, p.own_rid.p, row_of.p, rcount.p);
         LDS_HIP(hipGetLastError());
     }
@@ -287,7 +411,9 @@ void build_incidence_plan(Graph& g, const int32_t* pat, int64_t np, const int32_
         it.alloc(H * np, s);
         k_inc_keys<H><<<grid_for(np, kT), kT, 0, s>>>(pat, np, row_of.p, tb, ik.p);
         LDS_HIP(hipGetLastError());
-        radix_sort_u64(ik.p, nullptr, H * np, tb + rb, it.p, nullptr, s);
+        // the keys are made in pattern order and the sort is stable, so the
+        // row bits alone order them
+        radix_sort_u64(ik.p, nullptr, H * np, tb, tb + rb, it.p, nullptr, s);
         p.own_tos.alloc(H * np, s);
         k_inc_pay<H><<<grid_for(H * np, kT), kT, 0, s>>>(ik.p, H * np, tb, pat, p.own_rid.p, p.own_py.p,
                                                        p.own_tos.p);
@@ -353,24 +479,37 @@ void list_triangles(Graph& g, hipStream_t s) {
         outdeg.alloc(n, s);
         k_outdeg<<<grid_for(n, kT), kT, 0, s>>>(g.rowptr.p, g.col.p, n, outdeg.p);
         LDS_HIP(hipGetLastError());
+        // units of work: kUnitEdges oriented edges of one vertex each
         DBuf<uint32_t> cnt;
         DBuf<uint64_t> off, tot;
-        cnt.alloc(ns, s);
-        off.alloc(ns, s);
+        cnt.alloc(n, s);
+        off.alloc(n, s);
         tot.alloc(1, s);
-        k_tri_edges<false><<<grid_for(ns, kT), kT, 0, s>>>(g.rowptr.p, g.col.p, outdeg.p, n, ns, cnt.p, nullptr,
-                                                         nullptr);
+        k_unit_counts<<<grid_for(n, kT), kT, 0, s>>>(outdeg.p, n, cnt.p);
         LDS_HIP(hipGetLastError());
-        exclusive_scan_u32_to_u64(cnt.p, off.p, ns, tot.p, s);
-        T = (int64_t)d2h(tot.p, s);
-        cnt.release();
-        g.tri.alloc(3 * T, s);
-        if (T > 0) {
-            k_tri_edges<true><<<grid_for(ns, kT), kT, 0, s>>>(g.rowptr.p, g.col.p, outdeg.p, n, ns, nullptr, off.p,
-                                                            g.tri.p);
+        exclusive_scan_u32_to_u64(cnt.p, off.p, n, tot.p, s);
+        const int64_t units = (int64_t)d2h(tot.p, s);
+        if (units > 0) {
+            DBuf<int32_t> unit_u, unit_i0;
+            unit_u.alloc(units, s);
+            unit_i0.alloc(units, s);
+            k_unit_fill<<<grid_for(n, kT), kT, 0, s>>>(outdeg.p, off.p, n, unit_u.p, unit_i0.p);
             LDS_HIP(hipGetLastError());
-            k_tcount<<<grid_for(T, kT), kT, 0, s>>>(g.tri.p, T, g.tcount.p);
+            cnt.alloc(units, s);
+            off.alloc(units, s);
+            const unsigned grid = grid_for(units, kT / 64);
+            k_tri_units<false><<<grid, kT, 0, s>>>(g.rowptr.p, g.col.p, outdeg.p, unit_u.p, unit_i0.p, units, cnt.p,
+                                                   nullptr, nullptr, nullptr);
             LDS_HIP(hipGetLastError());
+            exclusive_scan_u32_to_u64(cnt.p, off.p, units, tot.p, s);
+            T = (int64_t)d2h(tot.p, s);
+            g.tri.alloc(3 * T, s);
+            if (T > 0) {
+                k_tri_units<true><<<grid, kT, 0, s>>>(g.rowptr.p, g.col.p, outdeg.p, unit_u.p, unit_i0.p, units,
+                                                      nullptr, off.p, g.tri.p, g.tcount.p);
+                LDS_HIP(hipGetLastError());
+                count_members(g.tri.p + 2, T, 3, n, g.tcount.p, s);
+            }
         }
     }
     g.T = T;
@@ -398,8 +537,7 @@ void list_cliques4(Graph& g, hipStream_t s) {
         if (Q > 0) {
             k_clique_tris<true><<<grid_for(T, kT), kT, 0, s>>>(g.rowptr.p, g.col.p, g.tri.p, T, nullptr, off.p, g.q4.p);
             LDS_HIP(hipGetLastError());
-            k_qcount<<<std::min<unsigned>(grid_for(Q, kT), 2048u), kT, 0, s>>>(g.q4.p, Q, g.qcount.p);
-            LDS_HIP(hipGetLastError());
+            count_members(g.q4.p, 4 * Q, 1, n, g.qcount.p, s);
         }
     }
     g.Q4 = Q;
