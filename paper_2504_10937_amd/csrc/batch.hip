@@ -22,6 +22,7 @@
 #include <numeric>
 
 #include "batch.hpp"
+#include "wave.hpp"
 
 namespace lds {
 
@@ -33,10 +34,9 @@ struct BItem {
     const int32_t* rid;  // compact row -> vertex (nullptr: identity)
     const int64_t* rp;
     const int32_t* py;
-    const int64_t* hwo;
-    const int64_t* chunk_row;
-    const int64_t* cwo;
+    const uint64_t* wdesc;  // per decision word: its slots and first row (word_desc)
     const uint64_t* head;
+    const int64_t* bitbase;
     const int32_t* cnt;     // deg (edges) or triangle count per vertex
     const int32_t* orig_of;
     uint64_t* K0;           // the graph's key buffers
@@ -44,22 +44,9 @@ struct BItem {
     uint64_t* bits;         // iters * total_words decision words
     uint64_t* sums;         // iters * 4 exact gap sums, or nullptr
     float* r_out;           // n loads by caller id, or nullptr
-    int64_t n_hub, n_chunks, chunk_words, total_words, nrows;
+    int32_t chunk_words, total_words, nrows, n_hub;
     int32_t n, h, mult, B, iters, lds_keys;
 };
-
-__device__ inline u128 wave_sum128(u128 x) {
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) {
-        const uint64_t lo = (uint64_t)x, hi = (uint64_t)(x >> 64);
-        const uint64_t lo2 = ((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(lo >> 32), m, 64) << 32) |
-                             (uint32_t)__shfl_xor((int)(uint32_t)lo, m, 64);
-        const uint64_t hi2 = ((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(hi >> 32), m, 64) << 32) |
-                             (uint32_t)__shfl_xor((int)(uint32_t)hi, m, 64);
-        x += ((u128)hi2 << 64) | lo2;
-    }
-    return x;
-}
 
 __device__ inline uint64_t readlane64(uint64_t v, int lane) {
     const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, lane);
@@ -71,164 +58,223 @@ __device__ inline uint64_t fw_inc(int h, int i) {  // D_i - D_{i-1}
     return (uint64_t)(h == 3 ? 6 : 2) * (uint64_t)(i + 1);
 }
 
-// does the vertex with key ku beat the other vertices of the pattern at slot s?
-template <int H>
-__device__ inline bool wins(uint64_t ku, const uint64_t* K, const int32_t* __restrict__ py, int64_t s) {
-    if (H == 2) return ku < K[py[s]];
-    const int2 v = reinterpret_cast<const int2*>(py)[s];
-    return ku < K[v.x] && ku < K[v.y];
-}
+constexpr int kG = 8;      // 64-slot words in flight per wave
+constexpr int kRows = 4;   // rows per thread whose bounds stay in registers over the iterations
 
-template <int H, int NT>
-__device__ void run_graph(const BItem& it, uint64_t* Ka, uint64_t* Kb, uint64_t (*words)[32], uint64_t (*red)[4],
-                          uint32_t* hcnt) {
+// LDS of a workgroup: two key buffers of kmax vertices, then the decision
+// words of an iteration (wmax of them; plans with more words read them back
+// from memory)
+struct Lds {
+    uint64_t* keys;
+    int32_t kmax;
+    uint64_t* words;
+    int32_t wmax;
+    uint64_t (*red)[4];
+};
+
+// One graph, all iterations, by one workgroup; the keys ping-pong between Ka
+// and Kb (LDS when KLDS, else the graph's own buffers).  An iteration has two
+// phases.  Decision words: every wave takes an equal run of them, kG at a time
+// with their payload reads in flight together and every key an LDS read; a
+// word's slots and first row are scalars (word_desc), whatever rows or chunks
+// it belongs to.  Rows: a thread per row (a wave per row of more than kChunk
+// slots) counts the row's wins in the words and writes its key.  Bound: LDS
+// reads (two or three 8-byte keys per slot) and issue.  One word at a time by
+// chunks, with keys through generic pointers and a barrier pair per hub row,
+// 768 graphs (half edge, half triangle density, n <= 5000) took 21 ms; now
+// 8.0 ms.
+template <int H, int NT, bool KLDS>
+__device__ void run_graph(const BItem& it, uint64_t* Ka, uint64_t* Kb, const Lds& l) {
     constexpr int NW = NT / 64;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int B = it.B;
     const uint64_t idm = (1ull << B) - 1ull;
+    const uint64_t le = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
+    const int words = it.total_words;
+    const bool wlds = words <= l.wmax;
+    // a wave's run of words, in whole batches
+    const int per = ((words + NW - 1) / NW + kG - 1) / kG * kG;
+    const int wb = min(words, w * per), we = min(words, wb + per);
     // initial keys in both buffers: vertices without slots never change
     for (int u = threadIdx.x; u < it.n; u += NT) {
         const uint64_t k = (((uint64_t)it.cnt[u] * (uint64_t)it.mult) << B) | (idm - (uint64_t)it.orig_of[u]);
         Ka[u] = k;
         Kb[u] = k;
     }
+    struct Row {
+        int32_t bit, len, u;
+    };
+    auto load_row = [&](int r) {
+        Row x{0, 0, 0};
+        if (r < it.nrows) {
+            x.bit = (int32_t)it.bitbase[r];
+            x.len = (int32_t)(it.rp[r + 1] - it.rp[r]);
+            x.u = it.rid ? it.rid[r] : r;
+        }
+        return x;
+    };
+    Row mine[kRows];
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) mine[k] = load_row(it.n_hub + (int)threadIdx.x + k * NT);
+    // the run's first 64 word descriptors and row-start flags
+    const uint64_t wd0 = wb + lane < we ? it.wdesc[wb + lane] : 0ull;
+    const uint64_t hd0 = wb + lane < min(we, it.chunk_words) ? it.head[wb + lane] : 0ull;
     __syncthreads();
-    uint64_t* Kin = Ka;
-    uint64_t* Kout = Kb;
+    int cur = 0;
     for (int i = 1; i <= it.iters; ++i) {
+        const uint64_t* Kin = cur ? Kb : Ka;
+        uint64_t* Kout = cur ? Ka : Kb;
         const uint64_t inc = fw_inc(H, i);
         uint64_t* bits = it.bits + (int64_t)(i - 1) * it.total_words;
-        u128 sq = 0, mn = 0;
-        // hub rows: the whole workgroup, one row at a time
-        for (int64_t r = 0; r < it.n_hub; ++r) {
-            const int32_t u = it.rid ? it.rid[r] : (int32_t)r;
-            const int64_t s0 = it.rp[r], s1 = it.rp[r + 1];
-            const uint64_t Ku = Kin[u];
-            uint64_t* bw = bits + it.chunk_words + it.hwo[r];
-            uint32_t cnt = 0;
-            for (int64_t base = s0; base < s1; base += NT) {
-                const int64_t s = base + threadIdx.x;
-                const bool win = s < s1 && wins<H>(Ku, Kin, it.py, s);
-                const uint64_t W = __ballot(win);
-                const int64_t wb = base + 64 * w;
-                if (lane == 0 && wb < s1) bw[(wb - s0) / 64] = W;
-                cnt += (uint32_t)__popcll(W);
+        // ---- decision words
+        for (int b0 = wb; b0 < we; b0 += 64) {
+            const int x = b0 + lane;
+            uint64_t wd = wd0, hd = hd0;
+            if (b0 > wb) {
+                wd = x < we ? it.wdesc[x] : 0ull;
+                hd = x < min(we, it.chunk_words) ? it.head[x] : 0ull;
             }
-            if (lane == 0) hcnt[w] = cnt;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                uint64_t tot = 0;
-                for (int q = 0; q < NW; ++q) tot += hcnt[q];
-                Kout[u] = Ku + ((tot * inc) << B);
-                if (it.sums) {
-                    const uint64_t A = Ku >> B;
-                    sq += (u128)A * A;
-                    mn += (u128)A * tot;
-                }
-            }
-            __syncthreads();
-        }
-        // chunks: one wave each; decision words, then one lane per row
-        for (int64_t c = w; c < it.n_chunks; c += NW) {
-            const int64_t r0 = it.chunk_row[c], r1 = it.chunk_row[c + 1];
-            if (r0 >= r1) continue;
-            const int64_t s0 = it.rp[r0], s1 = it.rp[r1];
-            const int64_t w0 = it.cwo[c];
-            const int nw = (int)(it.cwo[c + 1] - w0);  // <= 32
-            const int nsl = (int)(s1 - s0);
-            const uint64_t hreg = (lane < nw) ? it.head[w0 + lane] : 0ull;
-            const uint64_t le = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
-            int32_t rb = -1;  // chunk-relative row of the slot before the current word
             uint64_t mybits = 0;
-            for (int t = 0; t < nw; ++t) {
-                const uint64_t Hw = readlane64(hreg, t);
-                const int off = t * 64 + lane;
-                const int32_t row = rb + (int32_t)__popcll(Hw & le);
-                rb += (int32_t)__popcll(Hw);
-                bool win = false;
-                if (off < nsl) {
-                    const int32_t u = it.rid ? it.rid[r0 + row] : (int32_t)(r0 + row);
-                    win = wins<H>(Kin[u], Kin, it.py, s0 + off);
-                }
-                const uint64_t W = __ballot(win);
-                if (lane == t) mybits = W;
-            }
-            if (lane < nw) {
-                bits[w0 + lane] = mybits;
-                words[w][lane] = mybits;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            for (int64_t rbase = r0; rbase < r1; rbase += 64) {
-                const int64_t r = rbase + lane;
-                if (r < r1) {
-                    const int sa = (int)(it.rp[r] - s0), sb = (int)(it.rp[r + 1] - s0);
-                    uint32_t cnt = 0;
-                    for (int wd = sa >> 6; wd <= ((sb - 1) >> 6); ++wd) {
-                        const int lo = max(sa - wd * 64, 0), hi = min(sb - wd * 64, 64);
-                        const uint64_t mk = ((hi >= 64) ? ~0ull : ((1ull << hi) - 1ull)) & (~0ull << lo);
-                        cnt += (uint32_t)__popcll(words[w][wd] & mk);
-                    }
-                    const int32_t u = it.rid ? it.rid[r] : (int32_t)r;
-                    const uint64_t Ku = Kin[u];
-                    Kout[u] = Ku + (((uint64_t)cnt * inc) << B);
-                    if (it.sums) {
-                        const uint64_t A = Ku >> B;
-                        sq += (u128)A * A;
-                        mn += (u128)A * cnt;
+            const int nb = min(64, we - b0);
+            for (int t0 = 0; t0 < nb; t0 += kG) {
+                int32_t v[kG][H - 1], uu[kG];
+                bool win[kG];
+#pragma unroll
+                for (int j = 0; j < kG; ++j) {
+                    // past the run's end: word 0 of nothing (no lane is in)
+                    const uint64_t dsc = readlane64(wd, t0 + j), hw = readlane64(hd, t0 + j);
+                    const int nin = t0 + j < nb ? word_slots(dsc) : 0;
+                    win[j] = lane < nin;
+                    uu[j] = word_row(dsc) + (int32_t)__popcll(hw & le);
+                    const int32_t* py = it.py + (int64_t)word_slot(dsc) * (H - 1);
+                    if (H == 2) {
+                        v[j][0] = win[j] ? py[lane] : 0;
+                    } else {
+                        const int2 y = win[j] ? reinterpret_cast<const int2*>(py)[lane] : make_int2(0, 0);
+                        v[j][0] = y.x;
+                        v[j][H - 2] = y.y;
                     }
                 }
+                if (it.rid) {
+#pragma unroll
+                    for (int j = 0; j < kG; ++j) uu[j] = win[j] ? it.rid[uu[j]] : 0;
+                } else {
+#pragma unroll
+                    for (int j = 0; j < kG; ++j) uu[j] = win[j] ? uu[j] : 0;
+                }
+                uint64_t k0[kG], kv[kG][H - 1];
+#pragma unroll
+                for (int j = 0; j < kG; ++j) {
+                    k0[j] = Kin[uu[j]];
+#pragma unroll
+                    for (int q = 0; q < H - 1; ++q) kv[j][q] = Kin[v[j][q]];
+                }
+#pragma unroll
+                for (int j = 0; j < kG; ++j) {
+#pragma unroll
+                    for (int q = 0; q < H - 1; ++q) win[j] = win[j] && k0[j] < kv[j][q];
+                    const uint64_t W = __ballot(win[j]);
+                    if (lane == t0 + j) mybits = W;
+                }
             }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();  // words[w] is rewritten by the next chunk
+            if (x < we) {
+                bits[x] = mybits;
+                if (wlds) l.words[x] = mybits;
+            }
         }
+        __syncthreads();
+        // ---- rows
+        u128 sq = 0, mn = 0;
+        auto word = [&](int x) { return wlds ? l.words[x] : bits[x]; };
+        auto update = [&](int32_t u, uint64_t wins) {
+            const uint64_t Ku = Kin[u];
+            Kout[u] = Ku + ((wins * inc) << B);
+            if (it.sums) {
+                const uint64_t A = Ku >> B;
+                sq += (u128)A * A;
+                mn += (u128)A * wins;
+            }
+        };
+        for (int r = w; r < it.n_hub; r += NW) {  // word-aligned
+            const Row y = load_row(r);
+            uint32_t c = 0;
+            for (int q = lane; q < (y.len + 63) / 64; q += 64) c += (uint32_t)__popcll(word((y.bit >> 6) + q));
+#pragma unroll
+            for (int m = 32; m > 0; m >>= 1) c += (uint32_t)__shfl_xor((int)c, m, 64);
+            if (lane == 0) update(y.u, c);
+        }
+        auto row = [&](const Row& y) {
+            uint32_t c = 0;
+            const int last = y.bit + y.len - 1;
+            for (int wi = y.bit >> 6; wi <= last >> 6; ++wi) {
+                const int lo = max(y.bit - wi * 64, 0), hi = min(last + 1 - wi * 64, 64);
+                const uint64_t mk = ((hi >= 64) ? ~0ull : ((1ull << hi) - 1ull)) & (~0ull << lo);
+                c += (uint32_t)__popcll(word(wi) & mk);
+            }
+            update(y.u, c);
+        };
+#pragma unroll
+        for (int k = 0; k < kRows; ++k)
+            if (mine[k].len > 0) row(mine[k]);
+        for (int r = it.n_hub + (int)threadIdx.x + kRows * NT; r < it.nrows; r += NT) row(load_row(r));
         if (it.sums) {
-            sq = wave_sum128(sq);
-            mn = wave_sum128(mn);
-            if (lane == 0) {
-                red[w][0] = (uint64_t)sq;
-                red[w][1] = (uint64_t)(sq >> 64);
-                red[w][2] = (uint64_t)mn;
-                red[w][3] = (uint64_t)(mn >> 64);
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                u128 S = 0, M = 0;
-                for (int q = 0; q < NW; ++q) {
-                    S += ((u128)red[q][1] << 64) | red[q][0];
-                    M += ((u128)red[q][3] << 64) | red[q][2];
-                }
-                uint64_t* o = it.sums + 4 * (int64_t)(i - 1);
-                o[0] = (uint64_t)S;
-                o[1] = (uint64_t)(S >> 64);
-                o[2] = (uint64_t)M;
-                o[3] = (uint64_t)(M >> 64);
+            sq = wave::sum128_lane63(sq);
+            mn = wave::sum128_lane63(mn);
+            if (lane == 63) {
+                l.red[w][0] = (uint64_t)sq;
+                l.red[w][1] = (uint64_t)(sq >> 64);
+                l.red[w][2] = (uint64_t)mn;
+                l.red[w][3] = (uint64_t)(mn >> 64);
             }
         }
-        __syncthreads();  // all keys of iteration i written before iteration i+1 reads them
-        uint64_t* t = Kin;
-        Kin = Kout;
-        Kout = t;
+        __syncthreads();  // keys of iteration i written, its words read
+        cur ^= 1;
+        // the waves' sums are read before the next barrier, rewritten after it
+        if (it.sums && threadIdx.x == NT - 1) {
+            u128 S = 0, M = 0;
+            for (int q = 0; q < NW; ++q) {
+                S += ((u128)l.red[q][1] << 64) | l.red[q][0];
+                M += ((u128)l.red[q][3] << 64) | l.red[q][2];
+            }
+            uint64_t* o = it.sums + 4 * (int64_t)(i - 1);
+            o[0] = (uint64_t)S;
+            o[1] = (uint64_t)(S >> 64);
+            o[2] = (uint64_t)M;
+            o[3] = (uint64_t)(M >> 64);
+        }
     }
     // final keys into the graph's buffer number (iters & 1), loads by caller id
+    const uint64_t* Kend = cur ? Kb : Ka;
     uint64_t* Kfin = (it.iters & 1) ? it.K1 : it.K0;
     const double D = (double)((uint64_t)(H == 3 ? 3 : 1) * (uint64_t)(it.iters + 1) * (uint64_t)(it.iters + 2));
     for (int u = threadIdx.x; u < it.n; u += NT) {
-        const uint64_t k = Kin[u];
-        if (it.lds_keys) Kfin[u] = k;
+        const uint64_t k = Kend[u];
+        if (KLDS) Kfin[u] = k;
         if (it.r_out) it.r_out[it.orig_of[u]] = (float)((double)(k >> B) / D);
     }
     __syncthreads();  // LDS keys are reused by the next graph
 }
 
 template <int NT>
+__device__ inline void run_item(const BItem& it, const Lds& l) {
+    if (it.lds_keys) {
+        if (it.h == 2)
+            run_graph<2, NT, true>(it, l.keys, l.keys + l.kmax, l);
+        else
+            run_graph<3, NT, true>(it, l.keys, l.keys + l.kmax, l);
+    } else {
+        if (it.h == 2)
+            run_graph<2, NT, false>(it, it.K0, it.K1, l);
+        else
+            run_graph<3, NT, false>(it, it.K0, it.K1, l);
+    }
+}
+
+template <int NT>
 __global__ __launch_bounds__(NT) void k_fw_batch(const BItem* __restrict__ items, int32_t count, int32_t* queue,
-                                                int32_t kmax) {
-    extern __shared__ uint64_t skeys[];  // 2 * kmax
-    constexpr int NW = NT / 64;
-    __shared__ uint64_t words[NW][32];
-    __shared__ uint64_t red[NW][4];
-    __shared__ uint32_t hcnt[NW];
+                                                int32_t kmax, int32_t wmax) {
+    extern __shared__ uint64_t dyn[];  // 2 * kmax keys, wmax words
+    __shared__ uint64_t red[NT / 64][4];
     __shared__ int32_t next;
     for (;;) {
         if (threadIdx.x == 0) next = atomicAdd(queue, 1);
@@ -237,13 +283,20 @@ __global__ __launch_bounds__(NT) void k_fw_batch(const BItem* __restrict__ items
         __syncthreads();  // every thread has read `next`
         if (idx >= count) break;
         const BItem it = items[idx];
-        uint64_t* Ka = it.lds_keys ? skeys : it.K0;
-        uint64_t* Kb = it.lds_keys ? skeys + kmax : it.K1;
-        if (it.h == 2)
-            run_graph<2, NT>(it, Ka, Kb, words, red, hcnt);
-        else
-            run_graph<3, NT>(it, Ka, Kb, words, red, hcnt);
+        run_item<NT>(it, Lds{dyn, kmax, dyn + 2 * (size_t)kmax, wmax, red});
     }
+}
+
+// One small graph by one workgroup (fw_run_one): keys and words in LDS
+template <int NT>
+__global__ __launch_bounds__(NT) void k_fw_one(BItem it) {
+    extern __shared__ uint64_t dyn[];
+    __shared__ uint64_t red[NT / 64][4];
+    const Lds l{dyn, it.n, dyn + 2 * (size_t)it.n, it.total_words, red};
+    if (it.h == 2)
+        run_graph<2, NT, true>(it, l.keys, l.keys + l.kmax, l);
+    else
+        run_graph<3, NT, true>(it, l.keys, l.keys + l.kmax, l);
 }
 
 __global__ void k_zero_i32(int32_t* p) { *p = 0; }
@@ -255,8 +308,8 @@ void set_lds_limit(size_t bytes) {
 
 template <int NT>
 void launch_batch(unsigned grid, size_t lds, hipStream_t s, const BItem* items, int32_t count, int32_t* queue,
-                  int32_t kmax) {
-    k_fw_batch<NT><<<grid, NT, lds, s>>>(items, count, queue, kmax);
+                  int32_t kmax, int32_t wmax) {
+    k_fw_batch<NT><<<grid, NT, lds, s>>>(items, count, queue, kmax, wmax);
 }
 
 int device_cus() {
@@ -270,7 +323,71 @@ int device_cus() {
     return cus;
 }
 
+// the kernel's view of a graph whose FW buffers are sized for iters
+BItem make_item(Graph& g, int mode, int iters, int lds_vertices) {
+    const SweepPlan& p = (mode == 2) ? g.edge_plan : g.tri_plan;
+    FwState& f = g.fw[mode == 2 ? 0 : 1];
+    BItem x;
+    std::memset(&x, 0, sizeof(x));
+    x.rid = p.rid;
+    x.rp = p.rp;
+    x.py = p.py;
+    x.wdesc = p.wdesc.p;
+    x.head = p.head.p;
+    x.bitbase = p.bitbase.p;
+    x.cnt = (mode == 2) ? g.deg.p : g.tcount.p;
+    x.orig_of = g.orig_of.p;
+    x.K0 = f.K[0].p;
+    x.K1 = f.K[1].p;
+    x.bits = f.bits.p;
+    x.chunk_words = (int32_t)p.chunk_words;
+    x.total_words = (int32_t)p.total_words;
+    x.nrows = (int32_t)p.nrows;
+    x.n_hub = (int32_t)p.n_hub;
+    x.n = (int32_t)g.n;
+    x.h = mode;
+    x.mult = (mode == 2) ? 1 : 2;
+    x.B = g.idbits;
+    x.iters = (p.nrows > 0) ? iters : 0;
+    x.lds_keys = (g.n <= lds_vertices) ? 1 : 0;
+    return x;
+}
+
 }  // namespace
+
+// Whether fw_run gives the graph to one workgroup for all iterations: its
+// keys fit LDS and a sweep launch would take longer than the workgroup's pass
+// over the slots.  An iteration takes one workgroup 2.0 us at 446 slots, 2.8 at 2.6k,
+// 4.7 at 10k and 9 at 24k; a sweep launch takes 6.7, 7.2, 7.4 and 7.5 us.
+namespace {
+constexpr size_t kMaxLds = 160 * 1024 - 2048;  // dynamic LDS of a workgroup, beside the reductions
+size_t one_lds(const Graph& g, const SweepPlan& p) {
+    return ((size_t)2 * (size_t)g.n + (size_t)p.total_words) * sizeof(uint64_t);
+}
+}  // namespace
+
+bool fw_fits_one(const Graph& g, int mode) {
+    if (mode != 2 && mode != 3) return false;
+    const SweepPlan& p = plan_of(g, mode);
+    return g.n > 0 && g.n <= kOneVertices && p.nrows > 0 && p.nslots <= kOneSlots && p.wdesc.p &&
+           one_lds(g, p) <= kMaxLds;
+}
+
+void fw_run_one(Graph& g, int mode, int iters, uint64_t* sums, hipStream_t s) {
+    BItem x = make_item(g, mode, iters, kOneVertices);
+    x.sums = sums;
+    const size_t lds = one_lds(g, plan_of(g, mode));
+    if (x.total_words <= 4 * kG) {  // a batch of words per wave: fewer waves, cheaper barriers
+        LDS_HIP(hipFuncSetAttribute((const void*)k_fw_one<256>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)kMaxLds));
+        k_fw_one<256><<<1, 256, lds, s>>>(x);
+    } else {
+        LDS_HIP(hipFuncSetAttribute((const void*)k_fw_one<1024>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)kMaxLds));
+        k_fw_one<1024><<<1, 1024, lds, s>>>(x);
+    }
+    LDS_HIP(hipGetLastError());
+}
 
 int64_t batch_cost(const Graph& g, int mode, int iters) {
     const SweepPlan& p = (mode == 2) ? g.edge_plan : g.tri_plan;
@@ -297,9 +414,10 @@ void batch_build(Batch& b, hipStream_t s) {
     b.kernel_items.clear();
     b.plain_items.clear();
     for (int i = 0; i < count; ++i) {
-        // graphs with a 2D part (large edge plans) take their own launches
+        // graphs whose plans have no word descriptors (large ones) take their
+        // own launches
         if (batch_cost(*b.gs[i], b.modes[i], b.iters[i]) <= t.max_kernel_cost &&
-            plan_of(*b.gs[i], b.modes[i]).heavy.n_parts == 0)
+            plan_of(*b.gs[i], b.modes[i]).wdesc_built)
             b.kernel_items.push_back(i);
         else
             b.plain_items.push_back(i);
@@ -309,9 +427,15 @@ void batch_build(Batch& b, hipStream_t s) {
             return batch_cost(*b.gs[x], b.modes[x], b.iters[x]) > batch_cost(*b.gs[y], b.modes[y], b.iters[y]);
         });
     int32_t kmax = 0;
-    for (int i : b.kernel_items)
+    int64_t wmax = 0;
+    for (int i : b.kernel_items) {
         if (b.gs[i]->n <= t.lds_vertices) kmax = std::max<int32_t>(kmax, (int32_t)b.gs[i]->n);
+        wmax = std::max(wmax, plan_of(*b.gs[i], b.modes[i]).total_words);
+    }
     b.kmax = kmax;
+    // the words of an iteration in what LDS the keys leave to each workgroup of a CU
+    const int64_t room = ((int64_t)kMaxLds / t.wg_per_cu - (t.wg_per_cu > 1 ? 2048 : 0)) / 8 - 2 * (int64_t)kmax;
+    b.wmax = (int32_t)std::max<int64_t>(0, std::min(wmax, room));
     const size_t nk = b.kernel_items.size();
     b.sums.release();
     if (b.want_gap) {
@@ -326,37 +450,11 @@ void batch_build(Batch& b, hipStream_t s) {
         const int i = b.kernel_items[j];
         Graph& g = *b.gs[i];
         const int mode = b.modes[i];
-        const SweepPlan& p = (mode == 2) ? g.edge_plan : g.tri_plan;
-        FwState& f = g.fw[mode == 2 ? 0 : 1];
-        BItem& x = h[j];
-        std::memset(&x, 0, sizeof(x));
-        x.rid = p.rid;
-        x.rp = p.rp;
-        x.py = p.py;
-        x.hwo = p.hwo.p;
-        x.chunk_row = p.chunk_row.p;
-        x.cwo = p.cwo.p;
-        x.head = p.head.p;
-        x.cnt = (mode == 2) ? g.deg.p : g.tcount.p;
-        x.orig_of = g.orig_of.p;
-        x.K0 = f.K[0].p;
-        x.K1 = f.K[1].p;
-        x.bits = f.bits.p;
-        x.sums = b.want_gap ? b.sums.p + soff : nullptr;
+        h[j] = make_item(g, mode, b.iters[i], t.lds_vertices);
+        h[j].sums = b.want_gap ? b.sums.p + soff : nullptr;
         b.sum_off[j] = soff;
         if (b.want_gap) soff += 4 * (int64_t)b.iters[i];
-        x.r_out = b.r_out.empty() ? nullptr : b.r_out[i];
-        x.n_hub = p.n_hub;
-        x.n_chunks = p.n_chunks;
-        x.chunk_words = p.chunk_words;
-        x.total_words = p.total_words;
-        x.nrows = p.nrows;
-        x.n = (int32_t)g.n;
-        x.h = mode;
-        x.mult = (mode == 2) ? 1 : 2;
-        x.B = g.idbits;
-        x.iters = (p.nrows > 0) ? b.iters[i] : 0;
-        x.lds_keys = (g.n <= t.lds_vertices) ? 1 : 0;
+        h[j].r_out = b.r_out.empty() ? nullptr : b.r_out[i];
         // a graph without patterns keeps its initial keys; its state still
         // records the requested iteration count
     }
@@ -380,7 +478,7 @@ void batch_build(Batch& b, hipStream_t s) {
         LDS_HIP(hipEventCreate(&b.ev[1]));
     }
     if (nk == 0) return;
-    const size_t lds = (size_t)2 * (size_t)kmax * sizeof(uint64_t);
+    const size_t lds = ((size_t)2 * (size_t)kmax + (size_t)b.wmax) * sizeof(uint64_t);
     const unsigned grid =
         (unsigned)std::min<int64_t>((int64_t)device_cus() * t.wg_per_cu, (int64_t)nk);
     switch (t.threads) {
@@ -394,9 +492,9 @@ void batch_build(Batch& b, hipStream_t s) {
     LDS_HIP(hipStreamBeginCapture(b.cap, hipStreamCaptureModeThreadLocal));
     k_zero_i32<<<1, 1, 0, b.cap>>>(b.queue.p);
     switch (t.threads) {
-        case 256: launch_batch<256>(grid, lds, b.cap, items, (int32_t)nk, b.queue.p, kmax); break;
-        case 512: launch_batch<512>(grid, lds, b.cap, items, (int32_t)nk, b.queue.p, kmax); break;
-        default: launch_batch<1024>(grid, lds, b.cap, items, (int32_t)nk, b.queue.p, kmax); break;
+        case 256: launch_batch<256>(grid, lds, b.cap, items, (int32_t)nk, b.queue.p, kmax, b.wmax); break;
+        case 512: launch_batch<512>(grid, lds, b.cap, items, (int32_t)nk, b.queue.p, kmax, b.wmax); break;
+        default: launch_batch<1024>(grid, lds, b.cap, items, (int32_t)nk, b.queue.p, kmax, b.wmax); break;
     }
     const hipError_t le = hipGetLastError();
     hipGraph_t gr = nullptr;
@@ -414,9 +512,9 @@ void launch_direct(Batch& b, hipStream_t s) {
     const BItem* items = reinterpret_cast<const BItem*>(b.items.p);
     k_zero_i32<<<1, 1, 0, s>>>(b.queue.p);
     switch (b.tune.threads) {
-        case 256: launch_batch<256>(b.grid, b.lds_bytes, s, items, nk, b.queue.p, b.kmax); break;
-        case 512: launch_batch<512>(b.grid, b.lds_bytes, s, items, nk, b.queue.p, b.kmax); break;
-        default: launch_batch<1024>(b.grid, b.lds_bytes, s, items, nk, b.queue.p, b.kmax); break;
+        case 256: launch_batch<256>(b.grid, b.lds_bytes, s, items, nk, b.queue.p, b.kmax, b.wmax); break;
+        case 512: launch_batch<512>(b.grid, b.lds_bytes, s, items, nk, b.queue.p, b.kmax, b.wmax); break;
+        default: launch_batch<1024>(b.grid, b.lds_bytes, s, items, nk, b.queue.p, b.kmax, b.wmax); break;
     }
     LDS_HIP(hipGetLastError());
 }

@@ -30,7 +30,7 @@ struct Batch {
     DBuf<uint8_t> items;             // device item table
     DBuf<int32_t> queue;             // work-queue counter
     DBuf<uint64_t> sums;             // exact gap sums of the kernel items
-    int32_t kmax = 0;
+    int32_t kmax = 0, wmax = 0;      // LDS per workgroup: vertices with keys (twice), decision words
     unsigned grid = 0;
     size_t lds_bytes = 0;
     hipStream_t cap = nullptr;       // private stream used for capture
@@ -42,6 +42,14 @@ struct Batch {
 };
 
 int64_t batch_cost(const Graph& g, int mode, int iters);
+// Frank-Wolfe on one small graph by one workgroup in one launch (batch.hip):
+// whether fw_run does so, and the launch; the FW buffers must be sized, sums
+// (device, 4 * iters words, or nullptr) receives the exact gap sums, and the
+// result is in K[iters & 1]
+constexpr int32_t kOneVertices = 8192;   // two key buffers of 64 KB in LDS
+constexpr int64_t kOneSlots = 16384;
+bool fw_fits_one(const Graph& g, int mode);
+void fw_run_one(Graph& g, int mode, int iters, uint64_t* sums, hipStream_t s);
 void batch_build(Batch& b, hipStream_t s);  // sizes buffers, builds the item table, captures the hipGraph
 void batch_run(Batch& b, hipStream_t s);    // per-graph runs of large graphs, then the captured launch
 

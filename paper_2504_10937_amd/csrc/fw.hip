@@ -26,8 +26,10 @@
 // The duality-gap terms sum_u A_u^2 and sum_u A_u b_u (= sum over patterns of
 // the winning numerator, i.e. the minimum) are accumulated exactly in 128-bit
 // integers per workgroup and reduced once after the last iteration.
+#include "batch.hpp"
 #include "graph.hpp"
 #include "push.hpp"
+#include "wave.hpp"
 
 #include <mutex>
 
@@ -52,12 +54,12 @@ struct SweepArgs {
     int64_t n_hub;
     const int64_t* hwo;
     int64_t n_pieces;
+    int piece;           // most slots of a piece
     const int32_t* hp_row;
     const int32_t* hp_off;
     unsigned long long* hub_ctr;  // per hub row: (pieces done << 40) | wins so far
     int64_t n_chunks;
-    const int64_t* chunk_row;
-    const int64_t* cwo;
+    const ChunkDesc* desc;
     const uint64_t* head;
     int64_t chunk_words;
     const uint64_t* Kin;
@@ -101,21 +103,6 @@ __device__ inline uint64_t readlane64(uint64_t v, int lane) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-__device__ inline uint64_t shfl_xor64(uint64_t v, int m) {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, m, 64);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), m, 64);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ inline u128 wave_sum128(u128 x) {
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) {
-        const uint64_t lo = shfl_xor64((uint64_t)x, m), hi = shfl_xor64((uint64_t)(x >> 64), m);
-        x += ((u128)hi << 64) | lo;
-    }
-    return x;
-}
-
 // 16-bit monotone code of a load numerator: a pseudo-float with the 6-bit
 // position of the leading one and the next 10 bits (0 for A = 0).  A < A'
 // implies qcode(A) <= qcode(A'), so different codes decide a comparison of
@@ -127,13 +114,6 @@ __device__ inline uint16_t qcode(uint64_t A) {
     const int e = 63 - __clzll(A);
     const uint64_t mant = (e >= 10) ? (A >> (e - 10)) : (A << (10 - e));
     return (uint16_t)(((uint32_t)e << 10) | (uint32_t)(mant & 0x3FFu));
-}
-
-// does the row vertex (key ku, code qu) beat the vertex with code qv, whose
-// 64-bit key is gathered only when the codes tie?
-__device__ inline bool beats(uint64_t ku, uint16_t qu, uint16_t qv, const uint64_t* __restrict__ K, int32_t v) {
-    if (qu != qv) return qu < qv;
-    return ku < K[v];
 }
 
 // the h-1 other vertices of the pattern stored at a slot; the slot arrays
@@ -196,6 +176,60 @@ __device__ inline uint16_t qload(const uint16_t* __restrict__ qc, int nc, const 
     else
         q = Q[v];
     return q;
+}
+
+// Decisions of G slots per lane: does the row vertex (code qu[j], key ku(j))
+// beat the other members of the pattern at slot sl[j]?  The members' codes are
+// gathered one member at a time, the last one first (members are stored by
+// internal id, descending, so the last has the smallest id, the most slots and
+// most often a code in LDS): a slot that has lost needs no further gathers.
+// Equal codes are settled by the 64-bit keys after every code has been
+// compared, all reads of a few slots in flight together: ties are 0.1-2% of
+// the slots, but most batches hold one, and a read and wait per tied word was
+// the longest part of a batch's chain of dependent reads.
+template <int H, int G, class KU>
+__device__ inline void decide(const uint16_t* __restrict__ qc, int nc, const uint16_t* __restrict__ Q,
+                              const uint64_t* __restrict__ K, const Slot<H> (&sl)[G], const bool (&in)[G],
+                              const uint16_t (&qu)[G], KU ku, bool (&win)[G]) {
+    uint32_t tied[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        win[j] = in[j];
+        tied[j] = 0;
+    }
+#pragma unroll
+    for (int q = H - 2; q >= 0; --q) {
+        uint16_t qv[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) qv[j] = win[j] ? qload(qc, nc, Q, (uint32_t)sl[j].v[q]) : (uint16_t)0;
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (qu[j] == qv[j]) tied[j] |= 1u << q;
+            win[j] = win[j] && qu[j] <= qv[j];
+        }
+    }
+    constexpr int S = H == 2 ? G : (G >= 4 ? 4 : G);  // slots whose keys are in flight together
+#pragma unroll
+    for (int j0 = 0; j0 < G; j0 += S) {
+        uint64_t k0[S], kv[S][H - 1];
+#pragma unroll
+        for (int j = 0; j < S; ++j) {
+            const int x = j0 + j;
+            k0[j] = 0;
+#pragma unroll
+            for (int q = 0; q < H - 1; ++q) kv[j][q] = ~0ull;
+            if (win[x] && tied[x]) {
+                k0[j] = ku(x);
+#pragma unroll
+                for (int q = 0; q < H - 1; ++q)
+                    if (H == 2 || ((tied[x] >> q) & 1u)) kv[j][q] = K[(uint32_t)sl[x].v[q]];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < S; ++j)
+#pragma unroll
+            for (int q = 0; q < H - 1; ++q) win[j0 + j] = win[j0 + j] && k0[j] < kv[j][q];
+    }
 }
 
 // LDS bytes of the 2D part: block codes (u16) and win counts (u32), two slabs
@@ -339,14 +373,22 @@ __device__ inline void heavy_parts(const SweepArgs& a, uint8_t* dyn, int64_t* sg
 // each), both strided over the grid.
 template <int H, bool IDENT, bool GAP>
 __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
-    extern __shared__ uint16_t qc[];
+    extern __shared__ __align__(16) uint16_t qc[];
     __shared__ uint64_t red[kWaves][4];
     __shared__ uint64_t words[kWaves][32];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nc = a.ncache;
     // the 2D part first (its LDS layout), then the hot codes for the rest
     heavy_parts<H == 2 && IDENT>(a, reinterpret_cast<uint8_t*>(qc), reinterpret_cast<int64_t*>(&words[0][0]));
-    for (int i = threadIdx.x; i < nc; i += kPT) qc[i] = a.Qin[i];
+    // the hot codes, 16 bytes per load and all of a thread's loads in flight
+    // (2-byte loads took 10 of the 28 us of a 3M-slot sweep)
+    {
+        const uint4* __restrict__ src = reinterpret_cast<const uint4*>(a.Qin);
+        const int n16 = nc >> 3;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < n16; i += kPT) reinterpret_cast<uint4*>(qc)[i] = src[i];
+        for (int i = (n16 << 3) + threadIdx.x; i < nc; i += kPT) qc[i] = a.Qin[i];
+    }
     // hub push: the hub rows' win counters of this workgroup, after the codes
     const int Hp = (H == 2 && IDENT) ? (int)a.n_push : 0;
     uint32_t* hcnt = reinterpret_cast<uint32_t*>(qc + ((nc + 1) & ~1));
@@ -361,46 +403,46 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
     //      counter for the next sweep.  With the hub push a piece covers only
     //      the row's hub prefix and adds its wins alone: k_push_finish adds
     //      the pushed wins and writes the key.
-    for (int64_t pc = (int64_t)blockIdx.x * kWaves + w; pc < a.n_pieces; pc += (int64_t)gridDim.x * kWaves) {
+    const bool few = a.n_pieces + a.n_chunks <= (int64_t)gridDim.x * kWaves;
+    for (int64_t pc = few ? (int64_t)w * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * kWaves + w; pc < a.n_pieces;
+         pc += (int64_t)gridDim.x * kWaves) {
         const int64_t r = a.hp_row[pc];
         const uint32_t u = IDENT ? (uint32_t)r : (uint32_t)a.rid[r];
         const int64_t rs = a.rp[r], re = a.rp[r + 1];
         const int64_t s0 = rs + a.hp_off[pc];
-        const int64_t s1 = min(Hp > 0 ? rs + a.hub_pre[r] : re, s0 + (int64_t)kPiece);
+        // offsets within the piece in 32 bits
+        const int len = (int)min((Hp > 0 ? rs + a.hub_pre[r] : re) - s0, (int64_t)a.piece);
+        const int32_t* __restrict__ pyc = a.py + s0 * (H - 1);
         const uint64_t Ku = a.Kin[u];
         const uint16_t Qu = qcode(Ku >> a.B);
         uint64_t* bw = a.bits + a.chunk_words + a.hwo[r] + (s0 - rs) / 64;
         uint32_t cnt = 0;
-        for (int64_t base = s0; base < s1; base += 64 * kG) {
+        for (int base = 0; base < len; base += 64 * kG) {
             Slot<H> sl[kG];
             bool in[kG];
 #pragma unroll
             for (int j = 0; j < kG; ++j) {
-                const int64_t s = base + 64 * j + lane;
-                in[j] = s < s1;
-                if (in[j]) sl[j] = load_slot<H>(a.py, s);
+                const int off = base + 64 * j + lane;
+                in[j] = off < len;
+                if (in[j]) sl[j] = load_slot<H>(pyc, off);
             }
-            uint16_t qv[kG][H - 1];
+            uint16_t qu[kG];
+            bool win[kG];
 #pragma unroll
-            for (int j = 0; j < kG; ++j)
-#pragma unroll
-                for (int q = 0; q < H - 1; ++q)
-                    qv[j][q] = in[j] ? qload(qc, nc, a.Qin, (uint32_t)sl[j].v[q]) : (uint16_t)0;
+            for (int j = 0; j < kG; ++j) qu[j] = Qu;
+            decide<H, kG>(qc, nc, a.Qin, a.Kin, sl, in, qu, [&](int) { return Ku; }, win);
 #pragma unroll
             for (int j = 0; j < kG; ++j) {
-                bool win = in[j];
-#pragma unroll
-                for (int q = 0; q < H - 1; ++q) win = win && beats(Ku, Qu, qv[j][q], a.Kin, sl[j].v[q]);
-                const uint64_t W = __ballot(win);
-                const int64_t wb = base + 64 * j;  // first slot of this word
-                if (lane == 0 && wb < s1) __builtin_nontemporal_store(W, bw + (wb - s0) / 64);
+                const uint64_t W = __ballot(win[j]);
+                const int wb = base + 64 * j;  // first slot of this word
+                if (lane == 0 && wb < len) __builtin_nontemporal_store(W, bw + wb / 64);
                 cnt += (uint32_t)__popcll(W);
             }
         }
         if (lane == 0 && Hp > 0) {
             atomicAdd(a.hub_ctr + r, (unsigned long long)cnt);
         } else if (lane == 0) {
-            const unsigned long long npc = (unsigned long long)((re - rs + kPiece - 1) / kPiece);
+            const unsigned long long npc = (unsigned long long)((re - rs + a.piece - 1) / a.piece);
             const unsigned long long old = atomicAdd(a.hub_ctr + r, (1ull << 40) | (unsigned long long)cnt);
             if ((old >> 40) == npc - 1) {
                 const uint64_t tot = (old & ((1ull << 40) - 1)) + cnt;
@@ -421,16 +463,38 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
     //      flight; each word's ballot is kept by lane t
     //   B. one lane per row: popcount of the row's slot range in the chunk's
     //      decision words (staged in LDS), key and code update
-    for (int64_t c = (int64_t)blockIdx.x * kWaves + w; c < a.n_chunks; c += (int64_t)gridDim.x * kWaves) {
-        const int64_t r0 = a.chunk_row[c], r1 = a.chunk_row[c + 1];
-        if (r0 >= r1) continue;
-        const int64_t s0 = a.rp[r0], s1 = a.rp[r1];
-        const int64_t w0 = a.cwo[c];
-        const int nw = (int)(a.cwo[c + 1] - w0);  // <= 32: a chunk spans < 2048 slots
-        const int nsl = (int)(s1 - s0);
+    // A wave's time is a chain of dependent reads, so what does not depend on
+    // the decisions is read ahead: the next chunk's descriptor during this
+    // chunk, and the bounds and keys of the first 64 rows before the first
+    // batch (their codes also serve the slots of chunks of at most 64 rows).
+    // Pieces and chunks are dealt to the waves in turn (the chunks from the wave
+    // after the last piece's on), so no wave has two more than another.
+    // Neighbouring chunks (rows with cached codes in common) go to the waves of
+    // one workgroup, except in a plan that leaves waves without work, which is
+    // dealt over the compute units first.
+    const int64_t cstep = (int64_t)gridDim.x * kWaves;
+    int64_t c0 = few ? (int64_t)w * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * kWaves + w;
+    c0 -= a.n_pieces % cstep;
+    if (c0 < 0) c0 += cstep;
+    ChunkDesc dn{};
+    if (c0 < a.n_chunks) dn = a.desc[c0];
+    for (int64_t c = c0; c < a.n_chunks; c += cstep) {
+        const ChunkDesc d = dn;
+        if (c + cstep < a.n_chunks) dn = a.desc[c + cstep];
+        const int nrows = d.nrows;
+        if (nrows <= 0) continue;
+        const int64_t r0 = d.r0, s0 = d.s0, w0 = d.w0;
+        const int nsl = d.nsl, nw = (nsl + 63) >> 6;  // <= 32: a chunk spans < 2048 slots
         const int32_t* __restrict__ pyc = a.py + s0 * (H - 1);
         const uint64_t hreg = (lane < nw) ? __builtin_nontemporal_load(a.head + w0 + lane) : 0ull;
         const uint64_t le = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
+        // the first 64 rows: bounds, vertex, key, code
+        const int64_t rl = r0 + min(lane, nrows - 1);
+        int pa = (int)(a.rp[rl] - s0), pb = (int)(a.rp[rl + 1] - s0);
+        uint32_t pu = IDENT ? (uint32_t)rl : (uint32_t)a.rid[rl];
+        uint64_t pk = a.Kin[pu];
+        const int pq = (int)qcode(pk >> a.B);
+        const bool small = nrows <= 64;
         int32_t rowrel = -1;  // chunk-relative row of the slot before the current word
         uint64_t mybits = 0;
         for (int t0 = 0; t0 < nw; t0 += kG) {
@@ -438,49 +502,41 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
 #pragma unroll
             for (int j = 0; j < kG; ++j) Hw[j] = readlane64(hreg, t0 + j);  // t0 + j < 40
             Slot<H> sl[kG];
-            uint32_t uu[kG];
+            int32_t row[kG];
             bool val[kG];
             int32_t rb = rowrel;
 #pragma unroll
             for (int j = 0; j < kG; ++j) {
                 const int off = (t0 + j) * 64 + lane;
                 val[j] = off < nsl;
-                const int32_t row = rb + (int32_t)__popcll(Hw[j] & le);
+                row[j] = rb + (int32_t)__popcll(Hw[j] & le);
                 rb += (int32_t)__popcll(Hw[j]);
-                uu[j] = 0;
-                if (val[j]) {
-                    sl[j] = load_slot<H>(pyc, off);
-                    uu[j] = IDENT ? (uint32_t)(r0 + row) : (uint32_t)a.rid[r0 + row];
-                }
+                if (val[j]) sl[j] = load_slot<H>(pyc, off);
             }
             rowrel = rb;
-            uint16_t qu[kG], qv[kG][H - 1];
+            uint16_t qu[kG];
+            if (small) {
 #pragma unroll
-            for (int j = 0; j < kG; ++j) {
-                qu[j] = val[j] ? qload(qc, nc, a.Qin, uu[j]) : (uint16_t)0;
+                for (int j = 0; j < kG; ++j) qu[j] = (uint16_t)__shfl(pq, row[j], 64);
+            } else {
 #pragma unroll
-                for (int q = 0; q < H - 1; ++q)
-                    qv[j][q] = val[j] ? qload(qc, nc, a.Qin, (uint32_t)sl[j].v[q]) : (uint16_t)0;
+                for (int j = 0; j < kG; ++j)
+                    qu[j] = val[j] ? qload(qc, nc, a.Qin,
+                                           IDENT ? (uint32_t)(r0 + row[j]) : (uint32_t)a.rid[r0 + row[j]])
+                                   : (uint16_t)0;
             }
+            bool win[kG];
+            decide<H, kG>(qc, nc, a.Qin, a.Kin, sl, val, qu,
+                          [&](int j) { return a.Kin[IDENT ? (uint32_t)(r0 + row[j]) : (uint32_t)a.rid[r0 + row[j]]]; },
+                          win);
 #pragma unroll
             for (int j = 0; j < kG; ++j) {
-                if (t0 + j < nw) {
-                    bool win = val[j];
-#pragma unroll
-                    for (int q = 0; q < H - 1; ++q) {
-                        if (qu[j] != qv[j][q]) {
-                            win = win && (qu[j] < qv[j][q]);
-                        } else if (win) {
-                            win = a.Kin[uu[j]] < a.Kin[(uint32_t)sl[j].v[q]];
-                        }
-                    }
-                    if (H == 2 && Hp > 0 && val[j] && !win) {  // a hub's win, pushed to its counter
-                        const uint32_t v = (uint32_t)sl[j].v[0];
-                        if (v < (uint32_t)Hp) atomicAdd(&hcnt[v >> 1], 1u << ((v & 1u) * 16));
-                    }
-                    const uint64_t W = __ballot(win);
-                    if (lane == t0 + j) mybits = W;
+                if (H == 2 && Hp > 0 && val[j] && !win[j]) {  // a hub's win, pushed to its counter
+                    const uint32_t v = (uint32_t)sl[j].v[0];
+                    if (v < (uint32_t)Hp) atomicAdd(&hcnt[v >> 1], 1u << ((v & 1u) * 16));
                 }
+                const uint64_t W = __ballot(win[j]);
+                if (lane == t0 + j) mybits = W;
             }
         }
         if (lane < nw) {
@@ -489,18 +545,24 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        for (int64_t rbase = r0; rbase < r1; rbase += 64) {
-            const int64_t r = rbase + lane;
-            if (r < r1) {
-                const int sa = (int)(a.rp[r] - s0), sb = (int)(a.rp[r + 1] - s0);  // sb > sa
+        for (int rbase = 0; rbase < nrows; rbase += 64) {
+            const int sa = pa, sb = pb;  // sb > sa
+            const uint32_t u = pu;
+            const uint64_t Ku = pk;
+            if (rbase + 64 < nrows) {  // the next 64 rows
+                const int64_t rn = r0 + min(rbase + 64 + lane, nrows - 1);
+                pa = (int)(a.rp[rn] - s0);
+                pb = (int)(a.rp[rn + 1] - s0);
+                pu = IDENT ? (uint32_t)rn : (uint32_t)a.rid[rn];
+                pk = a.Kin[pu];
+            }
+            if (rbase + lane < nrows) {
                 uint32_t cnt = 0;
                 for (int wd = sa >> 6; wd <= ((sb - 1) >> 6); ++wd) {
                     const int lo = max(sa - wd * 64, 0), hi = min(sb - wd * 64, 64);
                     const uint64_t mk = ((hi >= 64) ? ~0ull : ((1ull << hi) - 1ull)) & (~0ull << lo);
                     cnt += (uint32_t)__popcll(words[w][wd] & mk);
                 }
-                const uint32_t u = IDENT ? (uint32_t)r : (uint32_t)a.rid[r];
-                const uint64_t Ku = a.Kin[u];
                 const uint64_t Kn = Ku + (((uint64_t)cnt * a.inc) << a.B);
                 a.Kout[u] = Kn;
                 a.Qout[u] = qcode(Kn >> a.B);
@@ -520,9 +582,9 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
         for (int i = threadIdx.x; i < (Hp + 1) / 2; i += kPT) o[i] = hcnt[i];
     }
     if (GAP) {
-        sq = wave_sum128(sq);
-        mn = wave_sum128(mn);
-        if (lane == 0) {
+        sq = wave::sum128_lane63(sq);
+        mn = wave::sum128_lane63(mn);
+        if (lane == 63) {
             red[w][0] = (uint64_t)sq;
             red[w][1] = (uint64_t)(sq >> 64);
             red[w][2] = (uint64_t)mn;
@@ -554,9 +616,9 @@ __global__ __launch_bounds__(256) void k_gap_reduce(const uint64_t* partial, int
         S += ((u128)p[4 * b + 1] << 64) | p[4 * b];
         M += ((u128)p[4 * b + 3] << 64) | p[4 * b + 2];
     }
-    S = wave_sum128(S);
-    M = wave_sum128(M);
-    if (lane == 0) {
+    S = wave::sum128_lane63(S);
+    M = wave::sum128_lane63(M);
+    if (lane == 63) {
         red[w][0] = (uint64_t)S;
         red[w][1] = (uint64_t)(S >> 64);
         red[w][2] = (uint64_t)M;
@@ -617,9 +679,9 @@ __global__ __launch_bounds__(256) void k_push_finish(unsigned long long* hub_ctr
         }
     }
     if (GAP) {  // wave 0 alone: all 64 lanes active
-        sq = wave_sum128(sq);
-        mn = wave_sum128(mn);
-        if (lane == 0) {
+        sq = wave::sum128_lane63(sq);
+        mn = wave::sum128_lane63(mn);
+        if (lane == 63) {
             uint64_t* o = partial + (int64_t)blockIdx.x * 4;
             o[0] = (uint64_t)sq;
             o[1] = (uint64_t)(sq >> 64);
@@ -664,9 +726,9 @@ __global__ __launch_bounds__(256) void k_heavy_finish(const uint32_t* part_cnt, 
         }
     }
     if (GAP) {
-        sq = wave_sum128(sq);
-        mn = wave_sum128(mn);
-        if (lane == 0) {
+        sq = wave::sum128_lane63(sq);
+        mn = wave::sum128_lane63(mn);
+        if (lane == 63) {
             red[w][0] = (uint64_t)sq;
             red[w][1] = (uint64_t)(sq >> 64);
             red[w][2] = (uint64_t)mn;
@@ -805,6 +867,12 @@ unsigned sweep_grid() {
     return (unsigned)(cus * kWgPerCU);
 }
 
+// workgroups that have a chunk, piece or part to sweep (at least one)
+unsigned sweep_blocks(const SweepPlan& p) {
+    const int64_t work = p.n_chunks + (p.n_push > 0 ? p.n_ppieces : p.n_pieces) + p.heavy.n_parts;
+    return (unsigned)std::min<int64_t>(sweep_grid(), std::max<int64_t>(1, work));
+}
+
 // workgroups of the heavy rows' finishing kernel (0 without a 2D part); its
 // gap partial sums follow the sweep's in each iteration's slice
 unsigned finish_grid(const SweepPlan& p) { return p.heavy.n_parts > 0 ? sweep_grid() : 0u; }
@@ -837,12 +905,12 @@ void fill_sweep_args(const Graph& g, const SweepPlan& p, SweepArgs& a) {
     a.n_hub = p.n_hub;
     a.hwo = p.hwo.p;
     a.n_pieces = p.n_pieces;
+    a.piece = p.piece;
     a.hp_row = p.hp_row.p;
     a.hp_off = p.hp_off.p;
     a.hub_ctr = p.hub_ctr.p;
     a.n_chunks = p.n_chunks;
-    a.chunk_row = p.chunk_row.p;
-    a.cwo = p.cwo.p;
+    a.desc = p.desc.p;
     a.head = p.head.p;
     a.chunk_words = p.chunk_words;
     a.B = g.idbits;
@@ -967,7 +1035,8 @@ void fw_run(Graph& g, int mode, int iters, bool want_gap, hipStream_t s) {
     FwState& f = g.fw[mode_slot(mode)];
     const int B = g.idbits;
     const int64_t n = g.n;
-    if (n > 0) {
+    const bool one = iters > 0 && fw_fits_one(g, mode);  // one launch for all iterations
+    if (n > 0 && !one) {
         const int32_t* cnt = (mode == 2) ? g.deg.p : (mode == 3 ? g.tcount.p : g.qcount.p);
         k_init_keys<<<grid_for(n, 256), 256, 0, s>>>(cnt, mode == 3 ? 2 : 1, g.orig_of.p, n, B, f.K[0].p, f.K[1].p,
                                                     f.Q[0].p, f.Q[1].p);
@@ -975,20 +1044,25 @@ void fw_run(Graph& g, int mode, int iters, bool want_gap, hipStream_t s) {
     }
     f.cur = 0;
     g.sg[mode_slot(mode)].valid = false;
-    const unsigned blocks = sweep_grid();
+    const unsigned blocks = sweep_blocks(p);
     const unsigned gblocks = blocks + finish_grid(p) + push_grid(p);  // gap partial sums per iteration
-    const size_t npart = want_gap ? (size_t)iters * gblocks * 4 : 0;
+    const size_t npart = want_gap ? (size_t)iters * (one ? 1 : gblocks) * 4 : 0;
     if (f.partial.n < npart) f.partial.alloc(npart, s);
     SweepArgs a;
     fill_sweep_args(g, p, a);
-    if (p.n_push > 0) use_push(p, f, blocks, a, s);
+    if (p.n_push > 0 && !one) use_push(p, f, blocks, a, s);
     if (!f.ev[0]) {
         LDS_HIP(hipEventCreate(&f.ev[0]));
         LDS_HIP(hipEventCreate(&f.ev[1]));
     }
     LDS_HIP(hipEventRecord(f.ev[0], s));
     f.launches = 0;
-    for (int i = 1; i <= iters && blocks > 0 && p.nrows > 0; ++i) {
+    if (one) {
+        fw_run_one(g, mode, iters, want_gap ? f.partial.p : nullptr, s);
+        f.cur = iters & 1;
+        f.launches = iters;
+    }
+    for (int i = 1; i <= iters && blocks > 0 && p.nrows > 0 && !one; ++i) {
         sweep_iteration(f, p, a, mode, i, blocks, want_gap ? f.partial.p + (size_t)(i - 1) * gblocks * 4 : nullptr,
                         s);
         ++f.launches;
@@ -1002,7 +1076,10 @@ void fw_run(Graph& g, int mode, int iters, bool want_gap, hipStream_t s) {
     f.fval.clear();
     if (want_gap && iters > 0) {
         std::vector<uint64_t> sums((size_t)iters * 4, 0);
-        if (blocks > 0 && p.nrows > 0) {
+        if (one) {
+            LDS_HIP(hipMemcpyAsync(sums.data(), f.partial.p, sums.size() * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+            LDS_HIP(hipStreamSynchronize(s));
+        } else if (blocks > 0 && p.nrows > 0) {
             DBuf<uint64_t> out;
             out.alloc((size_t)iters * 4, s);
             k_gap_reduce<<<iters, 256, 0, s>>>(f.partial.p, gblocks, out.p);

@@ -14,10 +14,11 @@
 // slot, ordered by slot count (descending), mapped to internal ids by rowid.
 //
 // Sweep plan.  Rows with more than kChunk slots are hubs, one workgroup
-// each.  The remaining rows are cut into chunks: chunk c holds the rows whose
-// first slot lies in [c*kChunk, (c+1)*kChunk) (relative to the first
-// non-hub slot), so a chunk spans fewer than 2*kChunk slots and always
-// starts at a row start.  Each chunk is one wave64.  The decision bits of one
+// each.  The remaining rows are cut into chunks of a target size C <= kChunk
+// (SweepPlan::chunk): chunk c holds the rows whose first slot lies in
+// [c*C, (c+1)*C) (relative to the first non-hub slot), so a chunk spans
+// fewer than 2*kChunk slots and always starts at a row start.  Each chunk is
+// one wave64.  The decision bits of one
 // iteration are stored per chunk from a 64-bit-word-aligned offset (cwo),
 // followed by the hub rows (hwo); a per-chunk "head" bitmap marks row starts.
 #pragma once
@@ -27,8 +28,8 @@
 
 namespace lds {
 
-constexpr int kChunk = 1024;  // target slots per wave; spans < 2*kChunk = 32 words
-constexpr int kPiece = 2048;  // slots of a hub-row piece (a multiple of 64)
+constexpr int kChunk = 1024;  // largest target slots per wave; spans < 2*kChunk = 32 words
+constexpr int kPiece = 2048;  // most slots of a hub-row piece (a multiple of 64)
 // LDS bytes of the persistent edge sweep for the staged codes and, with the
 // hub push, the per-workgroup win counters of the hub rows
 constexpr int64_t kSweepLds = 155648;
@@ -92,6 +93,24 @@ struct HeavyPlan {
     }
 };
 
+// A chunk as the sweep reads it, in one load: rows [r0, r0 + nrows), first
+// slot s0, first decision word w0 and the number of slots.
+struct alignas(32) ChunkDesc {
+    int64_t s0, w0;
+    int32_t r0, nrows, nsl, pad;
+};
+
+// A decision word as the batched kernel reads it (word_desc): first slot in the
+// low 32 bits, then the number of slots less one (6 bits) and the row of the
+// slot before the word's first plus one (26 bits).
+constexpr int64_t kWordDescSlots = (int64_t)1 << 24;  // largest plans that get word descriptors
+__host__ __device__ inline uint64_t word_desc(int64_t slot, int64_t row_before, int slots) {
+    return (uint64_t)(uint32_t)slot | ((uint64_t)(slots - 1) << 32) | ((uint64_t)(row_before + 1) << 38);
+}
+__host__ __device__ inline uint32_t word_slot(uint64_t d) { return (uint32_t)d; }
+__host__ __device__ inline int word_slots(uint64_t d) { return (int)((d >> 32) & 63) + 1; }
+__host__ __device__ inline int32_t word_row(uint64_t d) { return (int32_t)(d >> 38) - 1; }
+
 struct SweepPlan {
     int h = 2;                  // pattern arity: 2 edges, 3 triangles
     int64_t nrows = 0;          // compact rows
@@ -107,7 +126,8 @@ struct SweepPlan {
     int64_t n_big = 0;             // rows [0, n_big) have >= 64 slots (rows are ordered by slot count)
     int64_t n_hub = 0;          // rows [0, n_hub) are hubs
     DBuf<int64_t> hwo;          // n_hub + 1 word offsets (relative to hub region)
-    int64_t n_pieces = 0;       // hub rows cut into word-aligned pieces of <= kPiece slots, one wave each
+    int piece = kPiece;         // most slots of a hub-row piece
+    int64_t n_pieces = 0;       // hub rows cut into word-aligned pieces of <= piece slots, one wave each
     DBuf<int32_t> hp_row;       // per piece: hub row
     DBuf<int32_t> hp_off;       // per piece: first slot, relative to the row start (a multiple of 64)
     DBuf<unsigned long long> hub_ctr;  // n_hub: (pieces done << 40) | wins so far (zero between sweeps)
@@ -123,15 +143,19 @@ struct SweepPlan {
     int64_t n_ppieces = 0;      // pieces of those prefixes (as hp_row / hp_off)
     DBuf<int32_t> pp_row;
     DBuf<int32_t> pp_off;
+    int chunk = kChunk;         // target slots of a chunk
     int64_t n_chunks = 0;
+    DBuf<ChunkDesc> desc;       // n_chunks
     DBuf<int64_t> chunk_row;    // n_chunks + 1 (compact row index)
     DBuf<int64_t> cwo;          // n_chunks + 1 word offsets
     DBuf<uint64_t> head;        // chunk_words words: row-start flags
     int64_t chunk_words = 0, hub_words = 0, total_words = 0;
+    DBuf<uint64_t> wdesc;       // total_words, plans of at most kWordDescSlots slots without a 2D part
+    bool wdesc_built = false;
     DBuf<int64_t> bitbase;      // per compact row: bit index of its first slot (-1: heavy row)
     HeavyPlan heavy;            // edge plans of large graphs only
     size_t device_bytes() const {
-        return own_rid.bytes() + own_rp.bytes() + own_py.bytes() + own_tos.bytes() + own_row_of.bytes() + hwo.bytes() + chunk_row.bytes() + cwo.bytes() +
+        return own_rid.bytes() + own_rp.bytes() + own_py.bytes() + own_tos.bytes() + own_row_of.bytes() + hwo.bytes() + chunk_row.bytes() + cwo.bytes() + desc.bytes() + wdesc.bytes() +
                head.bytes() + bitbase.bytes() + hp_row.bytes() + hp_off.bytes() + hub_ctr.bytes() + hub_pre.bytes() +
                pp_row.bytes() + pp_off.bytes() + heavy.device_bytes();
     }

@@ -132,18 +132,18 @@ __global__ void k_hub_words(const int64_t* rp, int64_t n_hub, uint64_t* words) {
 
 // pieces of the hub rows: of each whole row, or (pre given) of its first
 // pre[r] slots
-__global__ void k_hub_pieces(const int64_t* rp, int64_t n_hub, const int32_t* pre, uint32_t* np) {
+__global__ void k_hub_pieces(const int64_t* rp, int64_t n_hub, const int32_t* pre, int piece, uint32_t* np) {
     const int64_t r = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (r < n_hub) np[r] = (uint32_t)(((pre ? (int64_t)pre[r] : rp[r + 1] - rp[r]) + kPiece - 1) / kPiece);
+    if (r < n_hub) np[r] = (uint32_t)(((pre ? (int64_t)pre[r] : rp[r + 1] - rp[r]) + piece - 1) / piece);
 }
 
-__global__ void k_hub_piece_fill(const int64_t* rp, int64_t n_hub, const int32_t* pre, const uint64_t* first,
+__global__ void k_hub_piece_fill(const int64_t* rp, int64_t n_hub, const int32_t* pre, int piece, const uint64_t* first,
                                  int32_t* hp_row, int32_t* hp_off) {
     const int64_t r = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (r >= n_hub) return;
     const int64_t len = pre ? (int64_t)pre[r] : rp[r + 1] - rp[r];
     int64_t k = (int64_t)first[r];
-    for (int64_t o = 0; o < len; o += kPiece, ++k) {
+    for (int64_t o = 0; o < len; o += piece, ++k) {
         hp_row[k] = (int32_t)r;
         hp_off[k] = (int32_t)o;
     }
@@ -165,12 +165,13 @@ __global__ void k_hub_prefix(const int64_t* rp, const int32_t* col, int64_t n_hu
     pre[r] = (int32_t)(lo - rp[r]);
 }
 
-__global__ void k_chunk_rows(const int64_t* rp, int64_t nrows, int64_t n_hub, int64_t n_chunks, int64_t* chunk_row) {
+__global__ void k_chunk_rows(const int64_t* rp, int64_t nrows, int64_t n_hub, int64_t n_chunks, int chunk,
+                             int64_t* chunk_row) {
     const int64_t r = n_hub + (int64_t)blockIdx.x * kT + threadIdx.x;
     if (r > nrows) return;
     const int64_t base = rp[n_hub];
-    const int64_t cr = (r < nrows) ? (rp[r] - base) / kChunk : n_chunks;  // r == nrows: close every chunk
-    const int64_t cp = (r == n_hub) ? -1 : (rp[r - 1] - base) / kChunk;
+    const int64_t cr = (r < nrows) ? (rp[r] - base) / chunk : n_chunks;  // r == nrows: close every chunk
+    const int64_t cp = (r == n_hub) ? -1 : (rp[r - 1] - base) / chunk;
     for (int64_t c = cp + 1; c <= cr; ++c) chunk_row[c] = r;
 }
 
@@ -180,17 +181,52 @@ __global__ void k_chunk_words(const int64_t* rp, const int64_t* chunk_row, int64
     words[c] = (uint64_t)((rp[chunk_row[c + 1]] - rp[chunk_row[c]] + 63) / 64);
 }
 
-__global__ void k_head(const int64_t* rp, int64_t nrows, int64_t n_hub, const int64_t* chunk_row,
+__global__ void k_chunk_desc(const int64_t* rp, const int64_t* chunk_row, const int64_t* cwo, int64_t n_chunks,
+                             ChunkDesc* desc) {
+    const int64_t c = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (c >= n_chunks) return;
+    ChunkDesc d;
+    const int64_t r0 = chunk_row[c], r1 = chunk_row[c + 1];
+    d.s0 = rp[r0];
+    d.w0 = cwo[c];
+    d.r0 = (int32_t)r0;
+    d.nrows = (int32_t)(r1 - r0);
+    d.nsl = (int32_t)(rp[r1] - d.s0);
+    d.pad = 0;
+    desc[c] = d;
+}
+
+__global__ void k_head(const int64_t* rp, int64_t nrows, int64_t n_hub, int chunk, const int64_t* chunk_row,
                        const int64_t* cwo, unsigned long long* head) {
     const int64_t r = n_hub + (int64_t)blockIdx.x * kT + threadIdx.x;
     if (r >= nrows) return;
     const int64_t base = rp[n_hub];
-    const int64_t c = (rp[r] - base) / kChunk;
+    const int64_t c = (rp[r] - base) / chunk;
     const int64_t pos = rp[r] - rp[chunk_row[c]];
     atomicOr(&head[cwo[c] + pos / 64], 1ull << (pos % 64));
 }
 
-__global__ void k_bitbase(const int64_t* rp, int64_t nrows, int64_t n_hub, const int64_t* chunk_row,
+// word descriptors: a thread per chunk, then a thread per hub-row piece
+__global__ void k_word_desc(const int64_t* rp, const ChunkDesc* desc, const uint64_t* head, int64_t n_chunks,
+                            const int32_t* hp_row, const int32_t* hp_off, const int64_t* hwo, int64_t n_pieces,
+                            int piece, int64_t chunk_words, uint64_t* wdesc) {
+    const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (i < n_chunks) {
+        const ChunkDesc d = desc[i];
+        int64_t row = (int64_t)d.r0 - 1;
+        for (int t = 0; t * 64 < d.nsl; ++t) {
+            wdesc[d.w0 + t] = word_desc(d.s0 + 64 * t, row, min(64, d.nsl - 64 * t));
+            row += __popcll(head[d.w0 + t]);
+        }
+    } else if (i < n_chunks + n_pieces) {
+        const int64_t k = i - n_chunks, r = hp_row[k], s0 = rp[r] + hp_off[k];
+        const int64_t len = min(rp[r + 1] - s0, (int64_t)piece), w0 = chunk_words + hwo[r] + hp_off[k] / 64;
+        for (int t = 0; t * 64 < len; ++t)
+            wdesc[w0 + t] = word_desc(s0 + 64 * t, r, (int)min<int64_t>(64, len - 64 * t));
+    }
+}
+
+__global__ void k_bitbase(const int64_t* rp, int64_t nrows, int64_t n_hub, int chunk, const int64_t* chunk_row,
                           const int64_t* cwo, const int64_t* hwo, int64_t chunk_words, bool heavy, int64_t* bitbase) {
     const int64_t r = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (r >= nrows) return;
@@ -198,7 +234,7 @@ __global__ void k_bitbase(const int64_t* rp, int64_t nrows, int64_t n_hub, const
         bitbase[r] = heavy ? -1 : (chunk_words + hwo[r]) * 64;
     } else {
         const int64_t base = rp[n_hub];
-        const int64_t c = (rp[r] - base) / kChunk;
+        const int64_t c = (rp[r] - base) / chunk;
         bitbase[r] = cwo[c] * 64 + (rp[r] - rp[chunk_row[c]]);
     }
 }
@@ -543,6 +579,34 @@ int64_t build_heavy(SweepPlan& p, int64_t n, hipStream_t s) {
 
 }  // namespace
 
+// Target slots of a chunk for a plan with `slots` slots outside the hub rows
+// and `pieces` hub pieces.  A sweep runs in rounds (every one of its kSweepWaves
+// waves takes one chunk or piece), so the size is the smallest that fills a
+// whole number of rounds.  A round costs a chain of dependent reads, then a
+// batch of 512 slots at a time: up to kOneBatch slots (one batch with the part
+// of the last row that a chunk takes beyond its target) is the best size while
+// there are few rounds, two batches once there are many, and tiny plans use
+// kChunkMin, to have more waves in flight.  Measured per sweep in us, by size:
+// 4.4M slots 1024 44, 768 35, 384 33, 256 40; 1.4M 1024 25, 320 19, 128 25;
+// 37M 1024 236, 960 221, 384 236; 24k 1024 14, 256 8.1, 128 7.7.
+// LDS_SWEEP_CHUNK (a multiple of 64 up to kChunk) overrides.
+constexpr int64_t kSweepWaves = 4096;
+constexpr int kChunkMin = 128;
+constexpr int kOneBatch = 448;
+constexpr int kTwoBatches = 960;
+int64_t chunk_slots(int64_t slots, int64_t pieces) {
+    if (slots <= kSweepWaves * kChunkMin) return kChunkMin;
+    const int64_t per = slots <= 3 * kSweepWaves * kOneBatch ? kOneBatch : kTwoBatches;
+    const int64_t rounds = (slots / per + pieces + kSweepWaves - 1) / kSweepWaves;
+    const int64_t chunks = std::max<int64_t>(1, rounds * kSweepWaves - pieces);
+    return std::max<int64_t>(kChunkMin, (slots + chunks - 1) / chunks + 63);
+}
+
+// plans with fewer slots cut their hub rows into shorter pieces
+constexpr int64_t kPieceSlots = (int64_t)1 << 22;
+constexpr int kPieceSmall = 512;
+constexpr int64_t kPushSlots = (int64_t)1 << 21;
+
 void build_sweep_plan(SweepPlan& p, hipStream_t s, int64_t n_vertices) {
     const int64_t nrows = p.nrows;
     const int64_t n_heavy = n_vertices > 0 ? build_heavy(p, n_vertices, s) : 0;
@@ -584,21 +648,23 @@ void build_sweep_plan(SweepPlan& p, hipStream_t s, int64_t n_vertices) {
     } else {
         p.hub_words = 0;
     }
-    // hub pieces and their per-row counters
+    // hub pieces and their per-row counters; a piece is one wave's, so small
+    // plans cut shorter ones
+    p.piece = p.nslots >= kPieceSlots ? kPiece : kPieceSmall;
     p.n_pieces = 0;
     if (p.n_hub > 0 && n_heavy == 0) {
         DBuf<uint32_t> npc;
         DBuf<uint64_t> first;
         npc.alloc(p.n_hub, s);
         first.alloc(p.n_hub, s);
-        k_hub_pieces<<<grid_for(p.n_hub, kT), kT, 0, s>>>(p.rp, p.n_hub, nullptr, npc.p);
+        k_hub_pieces<<<grid_for(p.n_hub, kT), kT, 0, s>>>(p.rp, p.n_hub, nullptr, p.piece, npc.p);
         LDS_HIP(hipGetLastError());
         exclusive_scan_u32_to_u64(npc.p, first.p, p.n_hub, tot.p, s);
         p.n_pieces = (int64_t)d2h(tot.p, s);
         LDS_CHECK(p.n_pieces < INT32_MAX, ST_INVALID, "too many hub pieces");
         p.hp_row.alloc(p.n_pieces, s);
         p.hp_off.alloc(p.n_pieces, s);
-        k_hub_piece_fill<<<grid_for(p.n_hub, kT), kT, 0, s>>>(p.rp, p.n_hub, nullptr, first.p, p.hp_row.p,
+        k_hub_piece_fill<<<grid_for(p.n_hub, kT), kT, 0, s>>>(p.rp, p.n_hub, nullptr, p.piece, first.p, p.hp_row.p,
                                                               p.hp_off.p);
         LDS_HIP(hipGetLastError());
         p.hub_ctr.alloc(p.n_hub, s);
@@ -609,12 +675,18 @@ void build_sweep_plan(SweepPlan& p, hipStream_t s, int64_t n_vertices) {
     // and no hub row may have 2^16 slots (a counter never wraps into the next)
     p.n_push = p.push_nc = p.n_ppieces = 0;
     if (p.h == 2 && p.rid == nullptr && n_heavy == 0 && p.n_hub > 0) {
-        int64_t r01[2] = {0, 0};
+        int64_t r01[2] = {0, 0}, hub_slots = 0;
         LDS_HIP(hipMemcpyAsync(r01, p.rp, sizeof(r01), hipMemcpyDeviceToHost, s));
+        LDS_HIP(hipMemcpyAsync(&hub_slots, p.rp + p.n_hub, sizeof(int64_t), hipMemcpyDeviceToHost, s));
         LDS_HIP(hipStreamSynchronize(s));
         const int64_t nc = ((kSweepLds - 4 * ((p.n_hub + 1) / 2)) / 2) & ~(int64_t)1;
         const int64_t ncache = std::min<int64_t>(n_vertices, nc);
-        if (r01[1] - r01[0] < 65536 && ncache >= std::min<int64_t>(n_vertices, p.n_hub)) {
+        // The push costs its finishing kernel (6 us an iteration with the gap
+        // between launches) and saves the hub rows' slots against the rest (the
+        // sweep takes about 2.4e11 slots/s): it pays from about kPushSlots hub
+        // slots on (LDS_PUSH_SLOTS overrides).
+        const bool pays = hub_slots >= env_int("LDS_PUSH_SLOTS", kPushSlots);
+        if (pays && r01[1] - r01[0] < 65536 && ncache >= std::min<int64_t>(n_vertices, p.n_hub)) {
             p.n_push = p.n_hub;
             p.push_nc = ncache;
             p.hub_pre.alloc(p.n_hub, s);
@@ -624,14 +696,14 @@ void build_sweep_plan(SweepPlan& p, hipStream_t s, int64_t n_vertices) {
             DBuf<uint64_t> first;
             npc.alloc(p.n_hub, s);
             first.alloc(p.n_hub, s);
-            k_hub_pieces<<<grid_for(p.n_hub, kT), kT, 0, s>>>(p.rp, p.n_hub, p.hub_pre.p, npc.p);
+            k_hub_pieces<<<grid_for(p.n_hub, kT), kT, 0, s>>>(p.rp, p.n_hub, p.hub_pre.p, p.piece, npc.p);
             LDS_HIP(hipGetLastError());
             exclusive_scan_u32_to_u64(npc.p, first.p, p.n_hub, tot.p, s);
             p.n_ppieces = (int64_t)d2h(tot.p, s);
             p.pp_row.alloc(p.n_ppieces, s);
             p.pp_off.alloc(p.n_ppieces, s);
             if (p.n_ppieces > 0) {
-                k_hub_piece_fill<<<grid_for(p.n_hub, kT), kT, 0, s>>>(p.rp, p.n_hub, p.hub_pre.p, first.p,
+                k_hub_piece_fill<<<grid_for(p.n_hub, kT), kT, 0, s>>>(p.rp, p.n_hub, p.hub_pre.p, p.piece, first.p,
                                                                       p.pp_row.p, p.pp_off.p);
                 LDS_HIP(hipGetLastError());
             }
@@ -642,11 +714,13 @@ void build_sweep_plan(SweepPlan& p, hipStream_t s, int64_t n_vertices) {
     LDS_HIP(hipMemcpyAsync(&base, p.rp + p.n_hub, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     LDS_HIP(hipStreamSynchronize(s));
     const int64_t nonhub = p.nslots - base;
-    p.n_chunks = (nonhub + kChunk - 1) / kChunk;
+    p.chunk = (int)env_int("LDS_SWEEP_CHUNK", chunk_slots(nonhub, p.n_push > 0 ? p.n_ppieces : p.n_pieces));
+    p.chunk = std::min(std::max(64, p.chunk / 64 * 64), kChunk);
+    p.n_chunks = (nonhub + p.chunk - 1) / p.chunk;
     p.chunk_row.alloc(p.n_chunks + 1, s);
     p.cwo.alloc(p.n_chunks + 1, s);
     if (p.n_chunks > 0) {
-        k_chunk_rows<<<grid_for(nrows - p.n_hub + 1, kT), kT, 0, s>>>(p.rp, nrows, p.n_hub, p.n_chunks,
+        k_chunk_rows<<<grid_for(nrows - p.n_hub + 1, kT), kT, 0, s>>>(p.rp, nrows, p.n_hub, p.n_chunks, p.chunk,
                                                                        p.chunk_row.p);
         LDS_HIP(hipGetLastError());
         k_chunk_words<<<grid_for(p.n_chunks, kT), kT, 0, s>>>(p.rp, p.chunk_row.p, p.n_chunks,
@@ -659,18 +733,31 @@ void build_sweep_plan(SweepPlan& p, hipStream_t s, int64_t n_vertices) {
     k_set_last<<<1, 1, 0, s>>>(p.cwo.p, p.n_chunks, tot.p);
     LDS_HIP(hipGetLastError());
     p.chunk_words = (int64_t)d2h(tot.p, s);
+    p.desc.alloc(p.n_chunks, s);
+    if (p.n_chunks > 0) {
+        k_chunk_desc<<<grid_for(p.n_chunks, kT), kT, 0, s>>>(p.rp, p.chunk_row.p, p.cwo.p, p.n_chunks, p.desc.p);
+        LDS_HIP(hipGetLastError());
+    }
     p.heavy.word0 = p.chunk_words + p.hub_words;
     p.total_words = p.chunk_words + p.hub_words + p.heavy.positions / 64;
     p.head.alloc(p.chunk_words, s);
     if (p.chunk_words) LDS_HIP(hipMemsetAsync(p.head.p, 0, p.head.bytes(), s));
     if (nrows > p.n_hub) {
-        k_head<<<grid_for(nrows - p.n_hub, kT), kT, 0, s>>>(p.rp, nrows, p.n_hub, p.chunk_row.p, p.cwo.p,
+        k_head<<<grid_for(nrows - p.n_hub, kT), kT, 0, s>>>(p.rp, nrows, p.n_hub, p.chunk, p.chunk_row.p, p.cwo.p,
                                                            (unsigned long long*)p.head.p);
+        LDS_HIP(hipGetLastError());
+    }
+    p.wdesc_built = n_heavy == 0 && p.nslots <= kWordDescSlots && nrows < (1 << 26) - 1;
+    if (p.wdesc_built && p.n_chunks + p.n_pieces > 0) {
+        p.wdesc.alloc(p.total_words, s);
+        k_word_desc<<<grid_for(p.n_chunks + p.n_pieces, kT), kT, 0, s>>>(
+            p.rp, p.desc.p, p.head.p, p.n_chunks, p.hp_row.p, p.hp_off.p, p.hwo.p, p.n_pieces, p.piece,
+            p.chunk_words, p.wdesc.p);
         LDS_HIP(hipGetLastError());
     }
     p.bitbase.alloc(nrows, s);
     if (nrows > 0) {
-        k_bitbase<<<grid_for(nrows, kT), kT, 0, s>>>(p.rp, nrows, p.n_hub, p.chunk_row.p, p.cwo.p, p.hwo.p,
+        k_bitbase<<<grid_for(nrows, kT), kT, 0, s>>>(p.rp, nrows, p.n_hub, p.chunk, p.chunk_row.p, p.cwo.p, p.hwo.p,
                                                     p.chunk_words, n_heavy > 0, p.bitbase.p);
         LDS_HIP(hipGetLastError());
     }
@@ -882,6 +969,7 @@ void view_plan(SweepPlan& d, const SweepPlan& p, hipStream_t s) {
     d.n_big = p.n_big;
     d.n_hub = p.n_hub;
     d.hwo.borrow(p.hwo);
+    d.piece = p.piece;
     d.n_pieces = p.n_pieces;
     d.hp_row.borrow(p.hp_row);
     d.hp_off.borrow(p.hp_off);
@@ -896,6 +984,10 @@ void view_plan(SweepPlan& d, const SweepPlan& p, hipStream_t s) {
         LDS_HIP(hipMemsetAsync(d.hub_ctr.p, 0, d.hub_ctr.bytes(), s));
     }
     d.n_chunks = p.n_chunks;
+    d.chunk = p.chunk;
+    d.desc.borrow(p.desc);
+    d.wdesc.borrow(p.wdesc);
+    d.wdesc_built = p.wdesc_built;
     d.chunk_row.borrow(p.chunk_row);
     d.cwo.borrow(p.cwo);
     d.head.borrow(p.head);

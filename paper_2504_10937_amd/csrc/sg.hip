@@ -112,7 +112,7 @@ __device__ inline uint64_t wave_transpose64(uint64_t x) {
     return x;
 }
 
-__global__ __launch_bounds__(kT) void k_slot_splits(const int64_t* rp, int64_t n_pieces, const int32_t* hp_row,
+__global__ __launch_bounds__(kT) void k_slot_splits(const int64_t* rp, int64_t n_pieces, int piece, const int32_t* hp_row,
                                                     const int32_t* hp_off, const int64_t* hwo, int64_t n_chunks,
                                                     const int64_t* chunk_row, const int64_t* cwo, int64_t chunk_words,
                                                     const uint64_t* bits, int64_t total_words, int iters, int tri,
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kT) void k_slot_splits(const int64_t* rp, int64_t n
     if (b < n_pieces) {  // a hub row's piece (word-aligned, at most kPiece slots)
         const int64_t r = hp_row[b];
         s0 = rp[r] + hp_off[b];
-        s1 = min(rp[r + 1], s0 + (int64_t)kPiece);
+        s1 = min(rp[r + 1], s0 + (int64_t)piece);
         word0 = chunk_words + hwo[r] + hp_off[b] / 64;
     } else if (b < n_pieces + n_chunks) {
         const int64_t c = b - n_pieces;
@@ -1572,7 +1572,7 @@ void sg_sort_prefix(Graph& g, int mode, hipStream_t s) {
         const bool push = p.n_push > 0;
         const int64_t npc = push ? p.n_ppieces : p.n_pieces;
         const int64_t blocks = npc + p.n_chunks + (hv.positions + kPiece - 1) / kPiece;
-        k_slot_splits<<<grid_for(blocks, 1), kT, 0, s>>>(p.rp, npc, push ? p.pp_row.p : p.hp_row.p,
+        k_slot_splits<<<grid_for(blocks, 1), kT, 0, s>>>(p.rp, npc, p.piece, push ? p.pp_row.p : p.hp_row.p,
                                                          push ? p.pp_off.p : p.hp_off.p, p.hwo.p, p.n_chunks,
                                                          p.chunk_row.p, p.cwo.p, p.chunk_words, f.bits.p,
                                                          p.total_words, f.iters, mode == 3, hv.positions, hv.word0,

@@ -62,6 +62,21 @@ __device__ inline long long min_all(long long v) {
                                   [](int64_t a, int64_t b) { return a < b ? a : b; }));
 }
 
+// the wave's 128-bit sum, in lane 63
+__device__ inline unsigned __int128 sum128_lane63(unsigned __int128 v) {
+#define LDS_SUM128_STEP(C, R)                                                                                      \
+    v += ((unsigned __int128)(uint64_t)dpp<C, R>((int64_t)(uint64_t)(v >> 64), (int64_t)0) << 64) |                \
+         (uint64_t)dpp<C, R>((int64_t)(uint64_t)v, (int64_t)0);
+    LDS_SUM128_STEP(kRowShr1, 0xf)
+    LDS_SUM128_STEP(kRowShr2, 0xf)
+    LDS_SUM128_STEP(kRowShr4, 0xf)
+    LDS_SUM128_STEP(kRowShr8, 0xf)
+    LDS_SUM128_STEP(kRowBcast15, 0xa)
+    LDS_SUM128_STEP(kRowBcast31, 0xc)
+#undef LDS_SUM128_STEP
+    return v;
+}
+
 // Segmented inclusive prefix sum: lanes with equal keys must be contiguous
 // (runs); lane i ends with the sum of its run's values up to lane i, so the
 // last lane of a run holds the run's total.  A lane adds a shifted partial
