@@ -4,6 +4,7 @@ walked and probed, and per-vertex counts past the histogram's ids; exactly
 against the oracle."""
 import numpy as np
 import pytest
+import torch  # noqa: F401  (its HIP runtime first, as a program that shares tensors with the library loads it)
 
 import oracle
 import paper_2504_10937_amd as lds

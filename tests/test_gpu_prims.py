@@ -3,6 +3,7 @@ calls that use them: ingest (sort of 2 keys per pair, scans over vertices),
 the order of the loads, prefix counts and the candidate set."""
 import numpy as np
 import pytest
+import torch  # noqa: F401  (its HIP runtime first, as a program that shares tensors with the library loads it)
 
 import oracle
 import paper_2504_10937_amd as lds

@@ -3,6 +3,7 @@ from one word to the largest, hub rows in short and long pieces, pulled and
 pushed; loads, splits and gap exactly as the oracle's."""
 import numpy as np
 import pytest
+import torch  # noqa: F401  (its HIP runtime first, as a program that shares tensors with the library loads it)
 
 import oracle
 import paper_2504_10937_amd as lds
