@@ -18,6 +18,7 @@
 
 #include "graph.hpp"
 #include "gridsync.hpp"
+#include "wave.hpp"
 
 namespace lds {
 
@@ -28,33 +29,63 @@ constexpr int32_t kUnset = -1, kOutside = -2;
 
 __device__ inline void push(int32_t* list, int32_t* count, int32_t v) { list[atomicAdd(count, 1)] = v; }
 
-__global__ void k_init_edges(const int64_t* rowptr, const int32_t* col, int64_t n, const uint8_t* alive,
-                             int32_t* cnt, int32_t* core, int32_t* active, int32_t* na) {
-    const int64_t v = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (v >= n) return;
-    if (alive && !alive[v]) {
-        cnt[v] = 0;
-        core[v] = kOutside;
-        return;
+// a block's pushes: one atomic on the list's counter per workgroup (one per
+// wave, on one address, took 0.18 ms for 1M vertices)
+__device__ inline void block_push(int32_t* list, int32_t* count, bool in, int32_t v) {
+    __shared__ int32_t wsum[kT / 64], first;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t m = __ballot(in);
+    if (lane == 0) wsum[w] = (int32_t)__popcll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t c = 0;
+        for (int q = 0; q < kT / 64; ++q) {
+            const int32_t x = wsum[q];
+            wsum[q] = c;
+            c += x;
+        }
+        first = c ? atomicAdd(count, c) : 0;
     }
-    int32_t c = 0;
-    for (int64_t s = rowptr[v]; s < rowptr[v + 1]; ++s) c += (!alive || alive[col[s]]) ? 1 : 0;
-    cnt[v] = c;
-    core[v] = kUnset;
-    push(active, na, (int32_t)v);
+    __syncthreads();
+    if (in) list[first + wsum[w] + (int32_t)__popcll(m & (lane == 0 ? 0ull : (~0ull >> (64 - lane))))] = v;
 }
 
-__global__ void k_init_vertices(int64_t n, const uint8_t* alive, int32_t* cnt, int32_t* core, int32_t* active,
-                                int32_t* na) {
+// the whole graph: every count is the degree, every vertex remains
+__global__ void k_init_whole(const int64_t* rowptr, int64_t n, int32_t* cnt, int32_t* core, int32_t* active,
+                             int32_t* na) {
     const int64_t v = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (v >= n) return;
-    cnt[v] = 0;
-    if (alive && !alive[v]) {
-        core[v] = kOutside;
-        return;
-    }
+    cnt[v] = rowptr ? (int32_t)(rowptr[v + 1] - rowptr[v]) : 0;
     core[v] = kUnset;
-    push(active, na, (int32_t)v);
+    active[v] = (int32_t)v;
+    if (v == 0) *na = (int32_t)n;
+}
+
+// an induced subgraph: kInitG lanes per row count its alive neighbours (one
+// thread per row took 0.22 ms on 300k vertices, most of it the longest rows)
+constexpr int kInitG = 16;
+__global__ __launch_bounds__(kT) void k_init_edges(const int64_t* rowptr, const int32_t* col, int64_t n,
+                                                   const uint8_t* alive, int32_t* cnt) {
+    const int64_t v = ((int64_t)blockIdx.x * kT + threadIdx.x) / kInitG;
+    const int e = threadIdx.x % kInitG;
+    int32_t c = 0;
+    if (v < n && alive[v])
+        for (int64_t s = rowptr[v] + e; s < rowptr[v + 1]; s += kInitG) c += alive[col[s]] ? 1 : 0;
+#pragma unroll
+    for (int m = kInitG / 2; m > 0; m >>= 1) c += __shfl_xor(c, m, 64);
+    if (v < n && e == 0) cnt[v] = c;
+}
+
+// the alive vertices, with counts still to be made when zero is set
+__global__ __launch_bounds__(kT) void k_init_vertices(int64_t n, const uint8_t* alive, int zero, int32_t* cnt,
+                                                      int32_t* core, int32_t* active, int32_t* na) {
+    const int64_t v = (int64_t)blockIdx.x * kT + threadIdx.x;
+    const bool in = v < n && alive[v];
+    if (v < n) {
+        if (zero) cnt[v] = 0;
+        core[v] = in ? kUnset : kOutside;
+    }
+    block_push(active, na, in, (int32_t)v);
 }
 
 __global__ void k_init_triangles(const int32_t* tri, int64_t T, const uint8_t* alive, int32_t* cnt,
@@ -81,12 +112,58 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
     if (i < n) p[i] = v;
 }
 
+// Walk over the slots of the fc listed vertices by the waves of a phase.  A
+// wave takes up to 64 vertices at a time (fewer when the list would otherwise
+// leave waves without work), numbers their slots consecutively and deals them
+// to its lanes, U per lane in flight, so that short rows fill the wave and
+// the dependent reads of many slots overlap: with a wave per vertex and one
+// slot per lane, the peel of 1M vertices of 16 slots took 7.4 ms, now 2.3 ms.  range(v, q0, q1) gives
+// a vertex's slots, body(q, in) handles U slots per lane.  pre: 64 words of
+// LDS of the wave's own.
+template <int U, class RANGE, class BODY>
+__device__ inline void walk_slots(const int32_t* f, int32_t fc, int64_t gw, int64_t nwave, uint32_t* pre, RANGE range,
+                                  BODY body) {
+    const int lane = threadIdx.x & 63;
+    const int64_t per = max<int64_t>(1, min<int64_t>(64, (fc + nwave - 1) / nwave));
+    for (int64_t base = gw * per; base < fc; base += nwave * per) {
+        int64_t q0 = 0, q1 = 0;
+        if (lane < per && base + lane < fc) range(f[base + lane], q0, q1);
+        const uint32_t inc =
+            (uint32_t)wave::scan(q1 - q0, (int64_t)0, [](int64_t a, int64_t b) { return a + b; });
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        pre[lane] = inc;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int64_t from = q0 - (int64_t)(inc - (uint32_t)(q1 - q0));  // slot of number c: from + c
+        for (uint32_t c0 = 0; c0 < total; c0 += 64 * U) {
+            int64_t q[U];
+            bool in[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t c = c0 + 64 * u + (uint32_t)lane;
+                in[u] = c < total;
+                int e = 0;  // the vertex of slot c: first e with pre[e] > c
+                if (per > 1) {
+#pragma unroll
+                    for (int st = 32; st > 0; st >>= 1)
+                        if (pre[e + st - 1] <= c) e += st;
+                }
+                const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)from, e, 64);
+                const int hi = __shfl((int)(from >> 32), e, 64);
+                q[u] = (int64_t)(((uint64_t)(uint32_t)hi << 32) | lo) + (int64_t)c;
+            }
+            body(q, in);
+        }
+        __builtin_amdgcn_wave_barrier();  // pre is rewritten by the next vertices
+    }
+}
+
 // The rest of the peeling in one workgroup once few vertices remain (small
 // graphs from the start, the dense cores of large ones, the residual graphs of
 // Pruning rule 2): the same levels, frontiers and cascades, separated by
 // workgroup barriers.  The remaining vertices get local ids (their index in
 // the remaining list; loc maps a vertex to it, -1 for every other vertex), and
-// their counts, peeled flags, remaining lists and frontiers live in LDS, so a
+// their counts, peeled flags, remaining lists and frontiers live in LDS (144 KB), so a
 // level touches global memory only to walk the frontier's adjacency (and, for
 // triangles, to kill each triangle once).  Every level assigns a vertex or
 // jumps to a larger count, so the loops are bounded by the number of
@@ -105,8 +182,10 @@ __global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_
     __shared__ uint8_t gone[kTailMax];
     __shared__ uint16_t lrem[2][kTailMax];  // remaining local ids, double-buffered
     __shared__ uint16_t lfr[2][kTailMax];   // frontier of a cascade round / the next one
+    __shared__ int32_t fvert[kTailMax];     // vertices of the frontier
+    __shared__ uint32_t pre[kTailT / 64][64];
     __shared__ int32_t sc[4];               // [0] frontier, [1] next, [2] minimum, [3] remaining
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, wv = tid >> 6;
     for (int32_t i = tid; i < na; i += kTailT) {
         const int32_t v = act[i];
         loc[v] = i;
@@ -170,41 +249,33 @@ __global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_
             if (tid == 0) sc[1] = 0;
             __syncthreads();
             uint16_t* nx = lfr[f ^ 1];
-            for (int32_t i = wv; i < fc; i += kTailT / 64) {
-                const int32_t v = act[lfr[f][i]];
-                int64_t q0, q1;
-                if (!TRI) {
-                    q0 = rowptr[v];
-                    q1 = rowptr[v + 1];
-                } else {
-                    const int32_t r = row_of[v];
-                    if (r < 0) continue;
-                    q0 = rp[r];
-                    q1 = rp[r + 1];
-                }
-                for (int64_t qb = q0 + lane; qb < q1; qb += 64 * kTailU) {
+            for (int32_t i = tid; i < fc; i += kTailT) fvert[i] = act[lfr[f][i]];
+            __syncthreads();
+            walk_slots<kTailU>(
+                fvert, fc, wv, kTailT / 64, pre[wv],
+                [&](int32_t v, int64_t& q0, int64_t& q1) {
+                    const int32_t r = TRI ? row_of[v] : v;
+                    if (r < 0) return;
+                    q0 = TRI ? rp[r] : rowptr[r];
+                    q1 = TRI ? rp[r + 1] : rowptr[r + 1];
+                },
+                [&](const int64_t (&q)[kTailU], const bool (&in)[kTailU]) {
                     if (!TRI) {
                         int32_t lw[kTailU];
 #pragma unroll
-                        for (int u = 0; u < kTailU; ++u) {
-                            const int64_t q = qb + 64 * u;
-                            lw[u] = q < q1 ? loc[col[q]] : -1;
-                        }
+                        for (int u = 0; u < kTailU; ++u) lw[u] = in[u] ? loc[col[q[u]]] : -1;
 #pragma unroll
                         for (int u = 0; u < kTailU; ++u) lower_local(lw[u], nx);
                     } else {
                         bool live[kTailU];
 #pragma unroll
-                        for (int u = 0; u < kTailU; ++u) {
-                            const int64_t q = qb + 64 * u;
-                            live[u] = q < q1 && atomicExch(&talive[tos[q]], 0u) != 0u;  // killed once
-                        }
+                        for (int u = 0; u < kTailU; ++u)
+                            live[u] = in[u] && atomicExch(&talive[tos[q[u]]], 0u) != 0u;  // killed once
                         int32_t lw[kTailU][2];
 #pragma unroll
                         for (int u = 0; u < kTailU; ++u) {
-                            const int64_t q = qb + 64 * u;
-                            lw[u][0] = live[u] ? loc[py[2 * q]] : -1;
-                            lw[u][1] = live[u] ? loc[py[2 * q + 1]] : -1;
+                            lw[u][0] = live[u] ? loc[py[2 * q[u]]] : -1;
+                            lw[u][1] = live[u] ? loc[py[2 * q[u] + 1]] : -1;
                         }
 #pragma unroll
                         for (int u = 0; u < kTailU; ++u) {
@@ -212,8 +283,7 @@ __global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_
                             lower_local(lw[u][1], nx);
                         }
                     }
-                }
-            }
+                });
             __syncthreads();
             fc = sc[1];
             f ^= 1;
@@ -251,7 +321,7 @@ __global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_
 // uniform.  It stops once at most tail_max vertices remain and leaves
 // (remaining count, level, which list is current) in ctr for the
 // one-workgroup tail.
-constexpr int kPT = 512;
+constexpr int kPT = 1024;
 constexpr int64_t kPeelMaxWG = 64;
 // ctr words: results, the ring, and per level parity the smallest remaining
 // count (G_MIN) and the next frontier's counter (G_NF), written by a closing
@@ -278,19 +348,39 @@ struct PeelArgs {
     int32_t na, k, tail_max;
 };
 
-__device__ inline void lower(int32_t* cnt, int32_t* core, int32_t w, int32_t k, int32_t* next, int32_t* nc) {
-    if (core[w] != kUnset) return;
-    const int32_t old = atomicSub(&cnt[w], 1);
-    if (old == k + 1) {  // the decrement from k + 1 to k happens once
-        core[w] = k;
-        push(next, nc, w);
-    }
+// Pushes of a workgroup collected in LDS (those past its kPushBuf entries go
+// to the list one by one) and added to the list with one atomic on its
+// counter, which every workgroup shares.  Flushed by all threads.
+constexpr int kPushBuf = 4096;
+constexpr int32_t kBufferFrom = 8192;  // frontiers longer than this push through LDS
+constexpr int kWalkU = 4;              // slots per lane in flight
+__device__ inline void push_local(int32_t* buf, int32_t* count, int32_t* list, int32_t* lcount, int32_t v) {
+    const int32_t i = atomicAdd(count, 1);
+    if (i < kPushBuf)
+        buf[i] = v;
+    else
+        push(list, lcount, v);
+}
+__device__ inline void flush_local(int32_t* buf, int32_t* count, int32_t* list, int32_t* lcount, int32_t* first) {
+    __syncthreads();
+    const int32_t c = min(*count, kPushBuf);
+    if (threadIdx.x == 0) *first = c ? atomicAdd(lcount, c) : 0;
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i < c; i += kPT) list[*first + i] = buf[i];
+    __syncthreads();
+    if (threadIdx.x == 0) *count = 0;
+    __syncthreads();
 }
 
 template <bool TRI>
 __global__ __launch_bounds__(kPT) void k_peel_grid(PeelArgs a) {
     __shared__ int64_t s_err;
-    if (threadIdx.x == 0) s_err = 0;
+    __shared__ int32_t pbuf[kPushBuf], pbuf2[kPushBuf], pcount[2], pfirst;
+    __shared__ uint32_t pre[kPT / 64][64];
+    if (threadIdx.x == 0) {
+        s_err = 0;
+        pcount[0] = pcount[1] = 0;
+    }
     __syncthreads();
     const unsigned nwg = gridDim.x;
     const int64_t t = (int64_t)blockIdx.x * kPT + threadIdx.x, nthr = (int64_t)nwg * kPT;
@@ -333,9 +423,10 @@ __global__ __launch_bounds__(kPT) void k_peel_grid(PeelArgs a) {
                 const int32_t v = act[i];
                 if (a.core[v] == kUnset && a.cnt[v] <= k) {
                     a.core[v] = k;
-                    push(f, slot, v);
+                    push_local(pbuf, &pcount[0], f, slot, v);
                 }
             }
+            flush_local(pbuf, &pcount[0], f, slot, &pfirst);
             zero_next();
             grid_sync(a.bar, nwg, &s_err);
             fc = *slot;
@@ -347,21 +438,57 @@ __global__ __launch_bounds__(kPT) void k_peel_grid(PeelArgs a) {
                 break;
             }
             int32_t* slot = ring + (ph & 3);
-            for (int64_t i = gw; i < fc; i += nwave) {
-                const int32_t v = f[i];
-                if (!TRI) {
-                    for (int64_t q = a.rowptr[v] + lane; q < a.rowptr[v + 1]; q += 64)
-                        lower(a.cnt, a.core, a.col[q], k, nx, slot);
-                } else {
-                    const int32_t r = a.row_of[v];
-                    if (r < 0) continue;
-                    for (int64_t q = a.rp[r] + lane; q < a.rp[r + 1]; q += 64) {
-                        if (atomicExch(&a.talive[a.tos[q]], 0u) == 0u) continue;  // killed before
-                        lower(a.cnt, a.core, a.py[2 * q], k, nx, slot);
-                        lower(a.cnt, a.core, a.py[2 * q + 1], k, nx, slot);
+            // a long frontier pushes through LDS, a short one spares itself the
+            // two workgroup barriers
+            const bool buffered = fc > kBufferFrom;
+            auto join = [&](int32_t w) {
+                if (buffered)
+                    push_local(pbuf, &pcount[0], nx, slot, w);
+                else
+                    push(nx, slot, w);
+            };
+            walk_slots<kWalkU>(
+                f, fc, gw, nwave, pre[threadIdx.x >> 6],
+                [&](int32_t v, int64_t& q0, int64_t& q1) {
+                    const int32_t r = TRI ? a.row_of[v] : v;
+                    if (r < 0) return;
+                    q0 = TRI ? a.rp[r] : a.rowptr[r];
+                    q1 = TRI ? a.rp[r + 1] : a.rowptr[r + 1];
+                },
+                [&](const int64_t (&q)[kWalkU], const bool (&in)[kWalkU]) {
+                    constexpr int M = TRI ? 2 : 1;
+                    int32_t w[kWalkU][M];
+                    bool live[kWalkU];
+#pragma unroll
+                    for (int u = 0; u < kWalkU; ++u) {
+                        live[u] = in[u];
+                        if (TRI) live[u] = in[u] && atomicExch(&a.talive[a.tos[q[u]]], 0u) != 0u;  // killed once
                     }
-                }
-            }
+#pragma unroll
+                    for (int u = 0; u < kWalkU; ++u)
+#pragma unroll
+                        for (int j = 0; j < M; ++j)
+                            w[u][j] = live[u] ? (TRI ? a.py[2 * q[u] + j] : a.col[q[u]]) : 0;
+                    bool open[kWalkU][M];
+#pragma unroll
+                    for (int u = 0; u < kWalkU; ++u)
+#pragma unroll
+                        for (int j = 0; j < M; ++j) open[u][j] = live[u] && a.core[w[u][j]] == kUnset;
+                    int32_t old[kWalkU][M];
+#pragma unroll
+                    for (int u = 0; u < kWalkU; ++u)
+#pragma unroll
+                        for (int j = 0; j < M; ++j) old[u][j] = open[u][j] ? atomicSub(&a.cnt[w[u][j]], 1) : 0;
+#pragma unroll
+                    for (int u = 0; u < kWalkU; ++u)
+#pragma unroll
+                        for (int j = 0; j < M; ++j)
+                            if (open[u][j] && old[u][j] == k + 1) {  // the decrement from k + 1 to k happens once
+                                a.core[w[u][j]] = k;
+                                join(w[u][j]);
+                            }
+                });
+            if (buffered) flush_local(pbuf, &pcount[0], nx, slot, &pfirst);
             zero_next();
             grid_sync(a.bar, nwg, &s_err);
             fc = *slot;
@@ -387,14 +514,16 @@ __global__ __launch_bounds__(kPT) void k_peel_grid(PeelArgs a) {
             for (int64_t i = t; i < na; i += nthr) {
                 const int32_t v = act[i];
                 if (a.core[v] != kUnset) continue;
-                push(act2, slot, v);
+                push_local(pbuf, &pcount[0], act2, slot, v);
                 const int32_t c = a.cnt[v];
                 m = min(m, c);
                 if (c == k + 1) {
                     a.core[v] = k + 1;
-                    push(f, &a.ctr[G_NF + nl], v);
+                    push_local(pbuf2, &pcount[1], f, &a.ctr[G_NF + nl], v);
                 }
             }
+            flush_local(pbuf, &pcount[0], act2, slot, &pfirst);
+            flush_local(pbuf2, &pcount[1], f, &a.ctr[G_NF + nl], &pfirst);
             for (int o = 32; o > 0; o >>= 1) m = min(m, __shfl_xor(m, o, 64));
             if (lane == 0 && m != INT32_MAX) atomicMin(&a.ctr[G_MIN + nl], m);
         }
@@ -451,10 +580,14 @@ void core_numbers_gpu(Graph& g, int mode, const uint8_t* alive, int32_t* core, h
     next.alloc(n, s);
     ctr.alloc(8, s);  // C_* counters; [7] error flag of the one-workgroup tail
     k_fill8<<<1, 8, 0, s>>>(ctr.p);
+    if (!alive)
+        k_init_whole<<<grid_for(n, kT), kT, 0, s>>>(mode == 2 ? g.rowptr.p : nullptr, n, cnt.p, core, act.p, ctr.p);
+    else
+        k_init_vertices<<<grid_for(n, kT), kT, 0, s>>>(n, alive, mode != 2, cnt.p, core, act.p, ctr.p);
     if (mode == 2) {
-        k_init_edges<<<grid_for(n, kT), kT, 0, s>>>(g.rowptr.p, g.col.p, n, alive, cnt.p, core, act.p, ctr.p);
+        if (alive)
+            k_init_edges<<<grid_for(n, kT / kInitG), kT, 0, s>>>(g.rowptr.p, g.col.p, n, alive, cnt.p);
     } else {
-        k_init_vertices<<<grid_for(n, kT), kT, 0, s>>>(n, alive, cnt.p, core, act.p, ctr.p);
         if (g.T > 0) {
             talive.alloc(g.T, s);
             k_init_triangles<<<grid_for(g.T, kT), kT, 0, s>>>(g.tri.p, g.T, alive, cnt.p, talive.p);
