@@ -185,7 +185,7 @@ struct SgState {
     bool valid = false;
     int iters = -1;
     DBuf<int32_t> order;         // position -> internal vertex (r descending, caller id ascending)
-    DBuf<int64_t> pos;           // internal vertex -> position
+    DBuf<int32_t> pos;           // internal vertex -> position
     DBuf<int64_t> E;             // patterns inside the first j+1 positions
     DBuf<uint8_t> inI;           // position j+1 (1-based) is a strict suffix maximum of E/j
     DBuf<uint32_t> a_slot;       // split numerator of every incidence slot

@@ -63,12 +63,12 @@ __global__ void k_sort_init(const uint64_t* K, int64_t n, uint64_t* keys, uint32
     vals[u] = (uint32_t)u;
 }
 
-__global__ void k_order(const uint32_t* vals, int64_t n, int32_t* order, int64_t* pos) {
+__global__ void k_order(const uint32_t* vals, int64_t n, int32_t* order, int32_t* pos) {
     const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (i >= n) return;
     const int64_t j = n - 1 - i;  // ascending keys read backwards: r descending
     order[j] = (int32_t)vals[i];
-    pos[vals[i]] = j;
+    pos[vals[i]] = (int32_t)j;
 }
 
 // --------------------------------------------------- split numerators per slot
@@ -283,13 +283,13 @@ struct PassArgs {
     const int32_t* tri;
     const uint32_t* a_slot;
     const uint32_t* a_tri;
-    const int64_t* pos;
+    const int32_t* pos;
     const int32_t* row_of;  // triangles: internal vertex -> row (edges: identity below nrows)
     int64_t nrows, n_big;
     uint64_t D;
 };
 
-__device__ inline int grp(int64_t p, int64_t t1, int64_t t2) { return p < t1 ? 0 : (p < t2 ? 1 : 2); }
+__device__ inline int grp(int32_t p, int32_t t1, int32_t t2) { return p < t1 ? 0 : (p < t2 ? 1 : 2); }
 
 __global__ void k_inclusive(const uint64_t* excl, const int64_t* c, int64_t n, int64_t* E) {
     const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
@@ -407,8 +407,9 @@ __global__ void k_fill_i64(int64_t* p, int64_t n, int64_t v) {
 // ---- incremental maintenance of T and restricted verification passes
 // group of position p under thresholds: 0 above (< t1), 1 tested ([t1, t2)), 2 below
 // contribution of pattern vertex k (of h) given positions and split numerators
+// (a pattern's numerators sum to D, which 32 bits hold)
 template <int H>
-__device__ inline int64_t pat_contrib(int k, const int64_t* p, const int64_t* al, uint64_t D, int64_t t1, int64_t t2) {
+__device__ inline uint32_t pat_contrib(int k, const int32_t* p, const uint32_t* al, int32_t t1, int32_t t2) {
     int g[H];
     int gl = 0;
 #pragma unroll
@@ -417,31 +418,30 @@ __device__ inline int64_t pat_contrib(int k, const int64_t* p, const int64_t* al
         gl = max(gl, g[i]);
     }
     if (g[k] < gl) return 0;
-    int64_t freed = 0;
+    uint32_t freed = 0;
     bool recv = true;
 #pragma unroll
     for (int i = 0; i < H; ++i) {
         if (g[i] < gl) freed += al[i];
         else if (i != k && p[i] > p[k]) recv = false;
     }
-    (void)D;
     return al[k] + (recv ? freed : 0);
 }
 
 // positions, numerators and internal ids of the pattern at slot s of row x
 template <int H>
-__device__ inline void load_pattern(const PassArgs& a, int64_t s, int32_t x, int64_t* p, int64_t* al, int32_t* id);
+__device__ inline void load_pattern(const PassArgs& a, int64_t s, int32_t x, int32_t* p, uint32_t* al, int32_t* id);
 template <>
-__device__ inline void load_pattern<2>(const PassArgs& a, int64_t s, int32_t x, int64_t* p, int64_t* al, int32_t* id) {
+__device__ inline void load_pattern<2>(const PassArgs& a, int64_t s, int32_t x, int32_t* p, uint32_t* al, int32_t* id) {
     id[0] = x;
     id[1] = a.py[s];
     p[0] = a.pos[x];
     p[1] = a.pos[id[1]];
     al[0] = a.a_slot[s];
-    al[1] = (int64_t)a.D - al[0];
+    al[1] = (uint32_t)a.D - al[0];
 }
 template <>
-__device__ inline void load_pattern<3>(const PassArgs& a, int64_t s, int32_t x, int64_t* p, int64_t* al, int32_t* id) {
+__device__ inline void load_pattern<3>(const PassArgs& a, int64_t s, int32_t x, int32_t* p, uint32_t* al, int32_t* id) {
     const int32_t v = a.py[2 * s], w = a.py[2 * s + 1];
     const int64_t t = a.tos[s];
     const int jx = tri_index(a.tri, t, v, w);
@@ -571,17 +571,17 @@ struct ScanArgs {
 
 // the pattern of record k, from the records
 template <int H>
-__device__ inline void rec_pattern(const ScanArgs& g, int64_t k, int64_t* p, int64_t* al);
+__device__ inline void rec_pattern(const ScanArgs& g, int64_t k, int32_t* p, uint32_t* al);
 template <>
-__device__ inline void rec_pattern<2>(const ScanArgs& g, int64_t k, int64_t* p, int64_t* al) {
+__device__ inline void rec_pattern<2>(const ScanArgs& g, int64_t k, int32_t* p, uint32_t* al) {
     const int2 r = g.rec2[k];
     p[0] = g.own[k];
     p[1] = r.x;
     al[0] = (uint32_t)r.y;
-    al[1] = (int64_t)g.a.D - al[0];
+    al[1] = (uint32_t)g.a.D - al[0];
 }
 template <>
-__device__ inline void rec_pattern<3>(const ScanArgs& g, int64_t k, int64_t* p, int64_t* al) {
+__device__ inline void rec_pattern<3>(const ScanArgs& g, int64_t k, int32_t* p, uint32_t* al) {
     const int4 r = g.rec3[k];
     p[0] = g.own[k];
     p[1] = r.x;
@@ -591,7 +591,7 @@ __device__ inline void rec_pattern<3>(const ScanArgs& g, int64_t k, int64_t* p, 
     al[2] = g.rec3w[k];
 }
 
-// Record walks.  A wave takes kRecRows(H) rows of 64 consecutive records per
+// Record walks.  A wave takes kRecRows rows of 64 consecutive records per
 // trip (lane l reads record 64 r + l of row r, so every load is coalesced)
 // and keeps the loads, the atomics and the reads that depend on them of all
 // its rows in flight together: the walks are bound by the latency of these
@@ -601,8 +601,7 @@ __device__ inline void rec_pattern<3>(const ScanArgs& g, int64_t k, int64_t* p, 
 // workgroup of its phase: a compute unit issues its scattered atomics and
 // reads about one address per cycle, and a walk that filled the first
 // workgroups' waves alone queued them on a few compute units.
-template <int H>
-constexpr int kRecRows = (H == 2) ? 8 : 4;
+constexpr int kRecRows = 4;
 
 
 // Adds, per position, the values of one row of 64 records into V.  The
@@ -627,52 +626,86 @@ __device__ inline void add_by_position(int64_t* V, int32_t key, int64_t val) {
 // the change of T that accepting S would make (accept_walk's); a rejected
 // boundary takes it back with accept_walk's negation.
 // Records [k0, k1) = [P[f0], P[b]); wave gw of nwave.
+// A trip's rows past the walk's end are skipped by scalar branches: most
+// walks of the leader have a row or two per wave, and the instructions of
+// eight masked rows (with 64-bit positions, spilling registers), not the
+// reads, were most of their time: 637 walks of a 120k-vertex graph 3.0 -> 2.1
+// ms, 2139 of a 4M-vertex graph 19.0 -> 15.6 ms; 1024 threads per workgroup
+// made the searches and min / max phases slower by more than they gave here.
 template <int H>
-__device__ inline void update_walk(const ScanArgs& g, int64_t S0, int64_t f0, int64_t b, int64_t k0, int64_t k1,
+__device__ inline void update_walk(const ScanArgs& g, int64_t S0_, int64_t f0_, int64_t b_, int64_t k0, int64_t k1,
                                    int64_t gw, int64_t nwave, bool spec) {
-    constexpr int U = kRecRows<H>;
+    constexpr int U = kRecRows;
     const int lane = threadIdx.x & 63;
-    const uint64_t D = g.a.D;
-    for (int64_t r0 = gw; k0 + 64 * r0 < k1; r0 += nwave * U) {  // this trip: rows r0 + nwave u
-        int64_t p[U][H], al[U][H];
+    const int32_t S0 = (int32_t)S0_, f0 = (int32_t)f0_, b = (int32_t)b_;
+    const int64_t rows = (k1 - k0 + 63) >> 6;
+    for (int64_t r0 = gw; r0 < rows; r0 += nwave * U) {  // this trip: rows r0 + nwave u
+        int32_t p[U][H];
+        uint32_t al[U][H];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            p[u][0] = -1;
+            if (r0 + nwave * u >= rows) continue;
             const int64_t k = k0 + 64 * (r0 + nwave * u) + lane;
             if (k < k1) rec_pattern<H>(g, k, p[u], al[u]);
-            else p[u][0] = -1;
         }
-        int64_t own[U], fd[U][H - 1], fo[U][H - 1];
+        uint32_t own[U], fd[U][H - 1];
+        int64_t fo[U][H - 1];
         long long bm[U][H - 1];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             own[u] = 0;
 #pragma unroll
             for (int i = 0; i < H - 1; ++i) fd[u][i] = 0;
+            if (r0 + nwave * u >= rows) continue;
             if (p[u][0] < 0) continue;
-            own[u] = pat_contrib<H>(0, p[u], al[u], D, S0, b);
-            bool latest = true;
-#pragma unroll
-            for (int i = 1; i < H; ++i)
-                if (p[u][i] >= f0 && p[u][i] < b && p[u][i] > p[u][0]) latest = false;
-            if (!latest) continue;
-#pragma unroll
-            for (int i = 1; i < H; ++i) {
-                if (p[u][i] >= b) {  // stays below
-                    if (spec) {
-                        const int64_t dt = pat_contrib<H>(i, p[u], al[u], D, b, p[u][i] + 1) -
-                                           pat_contrib<H>(i, p[u], al[u], D, S0, p[u][i] + 1);
-                        if (dt != 0) atomicAdd((unsigned long long*)&g.T[p[u][i]], (unsigned long long)dt);
+            if constexpr (H == 2) {
+                // the contributions of an edge of the joining vertex x to the
+                // other end y, in closed form: y above S leaves x the whole
+                // edge, y in S or joining its own share, y below nothing; x
+                // frees its share to a y below (of T as of F) and takes y's
+                // share back from an earlier member
+                const int32_t y = p[u][1];
+                const uint32_t ax = al[u][0], ay = al[u][1];
+                own[u] = y < S0 ? ax + ay : (y < b ? ax : 0u);
+                if (y >= b) {
+                    if (ax != 0) {
+                        if (spec) atomicAdd((unsigned long long*)&g.T[y], (unsigned long long)ax);
+                        fd[u][0] = ax;
+                        fo[u][0] = (int64_t)atomicAdd((unsigned long long*)&g.F[y], (unsigned long long)ax);
+                        bm[u][0] = g.bmax[y / kFB];
                     }
-                    const int64_t d = pat_contrib<H>(i, p[u], al[u], D, b, b) - pat_contrib<H>(i, p[u], al[u], D, f0, f0);
-                    if (d != 0) {
-                        fd[u][i - 1] = d;
-                        fo[u][i - 1] = (int64_t)atomicAdd((unsigned long long*)&g.F[p[u][i]], (unsigned long long)d);
-                        bm[u][i - 1] = g.bmax[p[u][i] / kFB];
+                } else if (y >= S0 && y < f0 && ay != 0) {
+                    atomicAdd((unsigned long long*)&g.V[y], (unsigned long long)ay);
+                }
+            } else {
+                own[u] = pat_contrib<H>(0, p[u], al[u], S0, b);
+                bool latest = true;
+#pragma unroll
+                for (int i = 1; i < H; ++i)
+                    if (p[u][i] >= f0 && p[u][i] < b && p[u][i] > p[u][0]) latest = false;
+                if (!latest) continue;
+#pragma unroll
+                for (int i = 1; i < H; ++i) {
+                    if (p[u][i] >= b) {  // stays below
+                        if (spec) {
+                            const int64_t dt = (int64_t)pat_contrib<H>(i, p[u], al[u], b, p[u][i] + 1) -
+                                               (int64_t)pat_contrib<H>(i, p[u], al[u], S0, p[u][i] + 1);
+                            if (dt != 0) atomicAdd((unsigned long long*)&g.T[p[u][i]], (unsigned long long)dt);
+                        }
+                        // (F only grows: the difference is not negative)
+                        const uint32_t d = pat_contrib<H>(i, p[u], al[u], b, b) - pat_contrib<H>(i, p[u], al[u], f0, f0);
+                        if (d != 0) {
+                            fd[u][i - 1] = d;
+                            fo[u][i - 1] =
+                                (int64_t)atomicAdd((unsigned long long*)&g.F[p[u][i]], (unsigned long long)d);
+                            bm[u][i - 1] = g.bmax[p[u][i] / kFB];
+                        }
+                    } else if (p[u][i] >= S0 && p[u][i] < f0) {  // earlier member of S
+                        const int64_t d = (int64_t)pat_contrib<H>(i, p[u], al[u], S0, b) -
+                                          (int64_t)pat_contrib<H>(i, p[u], al[u], S0, f0);
+                        if (d != 0) atomicAdd((unsigned long long*)&g.V[p[u][i]], (unsigned long long)d);
                     }
-                } else if (p[u][i] >= S0 && p[u][i] < f0) {  // earlier member of S
-                    const int64_t d =
-                        pat_contrib<H>(i, p[u], al[u], D, S0, b) - pat_contrib<H>(i, p[u], al[u], D, S0, f0);
-                    if (d != 0) atomicAdd((unsigned long long*)&g.V[p[u][i]], (unsigned long long)d);
                 }
             }
         }
@@ -680,21 +713,24 @@ __device__ inline void update_walk(const ScanArgs& g, int64_t S0, int64_t f0, in
         // no value the returning atomics above bring back, so they run while
         // those are in flight
 #pragma unroll
-        for (int u = 0; u < U; ++u) add_by_position(g.V, (int32_t)p[u][0], own[u]);
+        for (int u = 0; u < U; ++u)
+            if (r0 + nwave * u < rows) add_by_position(g.V, p[u][0], (int64_t)own[u]);
         // block maxima only grow (F only grows, bmax only by atomicMax): a
         // read that is at least the new value, even a stale one or one made
         // before the add, makes the atomic redundant
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+            if (r0 + nwave * u >= rows) continue;
 #pragma unroll
             for (int i = 0; i < H - 1; ++i)
                 if (fd[u][i] != 0) {
-                    const long long nv = (long long)(fo[u][i] + fd[u][i]);
+                    const long long nv = (long long)(fo[u][i] + (int64_t)fd[u][i]);
                     if (nv > bm[u][i]) {  // the superblock maximum is raised with its block's
                         atomicMax(&g.bmax[p[u][i + 1] / kFB], nv);
-                        atomicMax(&g.bmax2[p[u][i + 1] / ((int64_t)kFB * kSB)], nv);
+                        atomicMax(&g.bmax2[p[u][i + 1] / (kFB * kSB)], nv);
                     }
                 }
+        }
     }
 }
 
@@ -704,33 +740,42 @@ __device__ inline void update_walk(const ScanArgs& g, int64_t S0, int64_t f0, in
 // decision that rejected b.
 // Records [k0, k1) = [P[S0], P[b]); wave gw of nwave.
 template <int H>
-__device__ inline void accept_walk(const ScanArgs& g, int64_t S0, int64_t b, int64_t k0, int64_t k1, int64_t gw,
+__device__ inline void accept_walk(const ScanArgs& g, int64_t S0_, int64_t b_, int64_t k0, int64_t k1, int64_t gw,
                                    int64_t nwave, int64_t sgn) {
-    constexpr int U = kRecRows<H>;
+    constexpr int U = kRecRows;
     const int lane = threadIdx.x & 63;
-    const uint64_t D = g.a.D;
-    for (int64_t r0 = gw; k0 + 64 * r0 < k1; r0 += nwave * U) {  // this trip: rows r0 + nwave u
-        int64_t p[U][H], al[U][H];
+    const int32_t S0 = (int32_t)S0_, b = (int32_t)b_;
+    const int64_t rows = (k1 - k0 + 63) >> 6;
+    for (int64_t r0 = gw; r0 < rows; r0 += nwave * U) {  // this trip: rows r0 + nwave u
+        int32_t p[U][H];
+        uint32_t al[U][H];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            p[u][0] = -1;
+            if (r0 + nwave * u >= rows) continue;
             const int64_t k = k0 + 64 * (r0 + nwave * u) + lane;
             if (k < k1) rec_pattern<H>(g, k, p[u], al[u]);
-            else p[u][0] = -1;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            if (r0 + nwave * u >= rows) continue;
             if (p[u][0] < 0) continue;
-            bool latest = true;
+            if constexpr (H == 2) {  // the other end below takes the freed share
+                if (p[u][1] >= b && al[u][0] != 0)
+                    atomicAdd((unsigned long long*)&g.T[p[u][1]], (unsigned long long)(sgn * (int64_t)al[u][0]));
+            } else {
+                bool latest = true;
 #pragma unroll
-            for (int i = 1; i < H; ++i)
-                if (p[u][i] >= S0 && p[u][i] < b && p[u][i] > p[u][0]) latest = false;
-            if (!latest) continue;
+                for (int i = 1; i < H; ++i)
+                    if (p[u][i] >= S0 && p[u][i] < b && p[u][i] > p[u][0]) latest = false;
+                if (!latest) continue;
 #pragma unroll
-            for (int i = 1; i < H; ++i) {
-                if (p[u][i] < b) continue;
-                const int64_t d = pat_contrib<H>(i, p[u], al[u], D, b, p[u][i] + 1) -
-                                  pat_contrib<H>(i, p[u], al[u], D, S0, p[u][i] + 1);
-                if (d != 0) atomicAdd((unsigned long long*)&g.T[p[u][i]], (unsigned long long)(sgn * d));
+                for (int i = 1; i < H; ++i) {
+                    if (p[u][i] < b) continue;
+                    const int64_t d = (int64_t)pat_contrib<H>(i, p[u], al[u], b, p[u][i] + 1) -
+                                      (int64_t)pat_contrib<H>(i, p[u], al[u], S0, p[u][i] + 1);
+                    if (d != 0) atomicAdd((unsigned long long*)&g.T[p[u][i]], (unsigned long long)(sgn * d));
+                }
             }
         }
     }
@@ -765,12 +810,12 @@ __global__ __launch_bounds__(kT) void k_slot_records(PassArgs a, int64_t r0, int
     if (rw >= r1) return;  // uniform over the wave
     const int64_t r = rw + lane / G;
     const bool live = r < r1;
-    int64_t cs = 0, rs = 0, ts = 0, px = 0;
+    int64_t cs = 0, rs = 0, ts = 0;
+    int32_t px = 0;
     if (live) {
         const int32_t x = a.rid ? a.rid[r] : (int32_t)r;
         px = a.pos[x];
         const int64_t shift = P[px] - a.rp[r];
-        const uint64_t D = a.D;
         // an edge row per wave: U slots per lane and trip, all loaded before
         // any is used, so that a long row's trips overlap their gathers
         // (lds_large 1.82 against 1.88 ms; triangle rows, with three times
@@ -778,8 +823,8 @@ __global__ __launch_bounds__(kT) void k_slot_records(PassArgs a, int64_t r0, int
         constexpr int U = (G == 64 && H == 2) ? 4 : 1;
         const int64_t e = a.rp[r + 1];
         for (int64_t s0 = a.rp[r] + lane % G; s0 < e; s0 += (int64_t)G * U) {
-            int64_t p[U][H], al[U][H];
-            int32_t id[U][H];
+            int32_t p[U][H], id[U][H];
+            uint32_t al[U][H];
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (s0 + (int64_t)u * G < e) load_pattern<H>(a, s0 + (int64_t)u * G, x, p[u], al[u], id[u]);
@@ -787,20 +832,20 @@ __global__ __launch_bounds__(kT) void k_slot_records(PassArgs a, int64_t r0, int
             for (int u = 0; u < U; ++u) {
                 const int64_t s = s0 + (int64_t)u * G;
                 if (s >= e) break;
-                own[shift + s] = (int32_t)px;
+                own[shift + s] = px;
                 if (H == 2) {
-                    rec2[shift + s] = make_int2((int)p[u][1], (int)(uint32_t)al[u][0]);
+                    rec2[shift + s] = make_int2(p[u][1], (int)al[u][0]);
                 } else {
                     rec3[shift + s] =
-                        make_int4((int)p[u][1], (int)p[u][2], (int)(uint32_t)al[u][0], (int)(uint32_t)al[u][1]);
-                    rec3w[shift + s] = (uint32_t)al[u][2];
+                        make_int4(p[u][1], p[u][2], (int)al[u][0], (int)al[u][1]);
+                    rec3w[shift + s] = al[u][2];
                 }
                 bool latest = true;
 #pragma unroll
                 for (int i = 1; i < H; ++i) latest = latest && p[u][i] < p[u][0];
                 cs += latest ? 1 : 0;
-                rs += pat_contrib<H>(0, p[u], al[u], D, p[u][0], p[u][0]);
-                ts += pat_contrib<H>(0, p[u], al[u], D, 0, p[u][0] + 1);
+                rs += pat_contrib<H>(0, p[u], al[u], p[u][0], p[u][0]);
+                ts += pat_contrib<H>(0, p[u], al[u], 0, p[u][0] + 1);
             }
         }
     }
@@ -926,34 +971,33 @@ __device__ inline void put_partial(const ScanArgs& g, int ph, long long v0, long
     __syncthreads();
 }
 
-// WG-level reduction of per-thread values into sh[0..3] (min, max, max, min)
-__device__ inline void reduce_local(long long v0, long long v1, long long v2, long long v3, long long (*sred)[4],
-                                    long long* sh) {
+// The leader's reduction of per-thread values (min, max, max), the same in
+// every thread afterwards: one workgroup barrier, then every thread reads the
+// waves' values.  Two buffers in turn, so that a reduction may follow another
+// without a barrier between them.
+struct LeadRed {
+    long long (*buf)[kRW][3];
+    int turn;
+};
+__device__ inline void reduce_lead(LeadRed& r, long long& v0, long long& v1, long long& v2) {
+    long long (*x)[3] = r.buf[r.turn];
+    r.turn ^= 1;
     v0 = wave::min_all(v0);
     v1 = wave::max_all(v1);
     v2 = wave::max_all(v2);
-    v3 = wave::min_all(v3);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (lane == 0) {
-        sred[w][0] = v0;
-        sred[w][1] = v1;
-        sred[w][2] = v2;
-        sred[w][3] = v3;
+        x[w][0] = v0;
+        x[w][1] = v1;
+        x[w][2] = v2;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 1; q < kRW; ++q) {
-            v0 = min(v0, sred[q][0]);
-            v1 = max(v1, sred[q][1]);
-            v2 = max(v2, sred[q][2]);
-            v3 = min(v3, sred[q][3]);
-        }
-        sh[0] = v0;
-        sh[1] = v1;
-        sh[2] = v2;
-        sh[3] = v3;
+#pragma unroll
+    for (int q = 0; q < kRW; ++q) {
+        v0 = min(v0, x[q][0]);
+        v1 = max(v1, x[q][1]);
+        v2 = max(v2, x[q][2]);
     }
-    __syncthreads();
 }
 
 // First event in [lo, hi) among this thread's positions lo + t + i * nthr:
@@ -989,21 +1033,35 @@ __device__ inline long long search_part(const ScanArgs& g, int64_t lo, int64_t h
 // restricted load below b, over this thread's share
 __device__ inline void minmax_part(const ScanArgs& g, int64_t S0, int64_t b, int64_t t, int64_t nthr, long long& vmn,
                                    long long& vmx, long long& fmx) {
+    // the first reads of every array are issued before any is used
+    const int64_t bend = b < g.n ? min(g.n, (b / kFB + 1) * kFB) : b;
+    const int64_t sb = b / ((int64_t)kFB * kSB), blk_end = b < g.n ? min(g.nblk, (sb + 1) * kSB) : 0;
+    const int64_t q_end = b < g.n ? g.nsb : 0;
+    const int64_t blk0 = b / kFB + 1 + t, q0 = sb + 1 + t;
+    long long f[2], m0 = LLONG_MIN, m1 = LLONG_MIN, v[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) f[u] = b + t + u * nthr < bend ? (long long)g.F[b + t + u * nthr] : LLONG_MIN;
+    if (blk0 < blk_end) m0 = g.bmax[blk0];
+    if (q0 < q_end) m1 = g.bmax2[q0];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) v[u] = S0 + t + u * nthr < b ? (long long)g.V[S0 + t + u * nthr] : 0;
     vmn = LLONG_MAX;
     vmx = LLONG_MIN;
-    fmx = LLONG_MIN;
-    for (int64_t j = S0 + t; j < b; j += nthr) {
-        const long long v = (long long)g.V[j];
-        vmn = min(vmn, v);
-        vmx = max(vmx, v);
+    fmx = max(max(f[0], f[1]), max(m0, m1));
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+        if (S0 + t + u * nthr < b) {
+            vmn = min(vmn, v[u]);
+            vmx = max(vmx, v[u]);
+        }
+    for (int64_t j = S0 + t + 2 * nthr; j < b; j += nthr) {
+        const long long x = (long long)g.V[j];
+        vmn = min(vmn, x);
+        vmx = max(vmx, x);
     }
-    if (b < g.n) {
-        const int64_t bend = min(g.n, (b / kFB + 1) * kFB);
-        const int64_t sb = b / ((int64_t)kFB * kSB), blk_end = min(g.nblk, (sb + 1) * kSB);
-        for (int64_t j = b + t; j < bend; j += nthr) fmx = max(fmx, (long long)g.F[j]);
-        for (int64_t blk = b / kFB + 1 + t; blk < blk_end; blk += nthr) fmx = max(fmx, g.bmax[blk]);
-        for (int64_t q = sb + 1 + t; q < g.nsb; q += nthr) fmx = max(fmx, g.bmax2[q]);
-    }
+    for (int64_t j = b + t + 2 * nthr; j < bend; j += nthr) fmx = max(fmx, (long long)g.F[j]);
+    for (int64_t blk = blk0 + nthr; blk < blk_end; blk += nthr) fmx = max(fmx, g.bmax[blk]);
+    for (int64_t q = q0 + nthr; q < q_end; q += nthr) fmx = max(fmx, g.bmax2[q]);
 }
 
 // bounds of the accepted group S = [S0, b) and the change of T below it
@@ -1024,7 +1082,8 @@ __device__ inline void accept_part(const ScanArgs& g, int64_t S0, int64_t b, int
 template <int H>
 __device__ inline void run_posted(const ScanArgs& g, const long long* d, long long (*sred)[4]) {
     const int64_t t = (int64_t)blockIdx.x * kRT + threadIdx.x, nthr = d[8] * kRT;
-    const int64_t gw = t >> 6, nwave = nthr >> 6;
+    const int64_t gw = (int64_t)blockIdx.x * kRW + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t nwave = __builtin_amdgcn_readfirstlane((int)(nthr >> 6));
     const int ph = (int)d[1];
     if (d[0] == PH_SEARCH) {
         const long long first = search_part(g, d[2], d[3], d[4] != 0, d[5], t, nthr);
@@ -1129,50 +1188,47 @@ __device__ void scan_helper(const ScanArgs& g, long long (*sred)[4], int64_t* s_
 constexpr int kEvWords = 128;  // windows of at most 8192 positions are kept
 
 // first event at or after position `from` in the kept window [lo, hi) as a
-// search code (2 j + 1 stop, 2 j candidate; LLONG_MAX none), in sh[0] and
-// returned to every thread
+// search code (2 j + 1 stop, 2 j candidate; LLONG_MAX none); every wave finds
+// it by itself
 __device__ inline long long first_kept(int64_t lo, int64_t hi, int64_t from, const uint64_t* evb,
-                                       const uint64_t* stb, long long* sh) {
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        const int64_t w0 = (from - lo) / 64, w1 = (hi - lo + 63) / 64;
-        long long code = LLONG_MAX;
-        for (int64_t wb = w0; wb < w1 && code == LLONG_MAX; wb += 64) {
-            const int64_t wi = wb + lane;
-            uint64_t e = 0, st = 0;
-            if (wi < w1) {
-                e = evb[wi];
-                st = stb[wi];
-                const int64_t p0 = lo + 64 * wi;  // position of bit 0
-                uint64_t keep = ~0ull;
-                if (p0 < from) keep &= ~0ull << (from - p0);
-                if (p0 + 64 > hi) keep &= (hi - p0 >= 64) ? ~0ull : ((1ull << (hi - p0)) - 1);
-                e &= keep;
-                st &= keep;
-            }
-            const uint64_t any = __ballot((e | st) != 0);
-            if (any) {
-                const int src = __ffsll((long long)any) - 1;  // first word with an event
-                const uint64_t be = (uint64_t)__shfl((unsigned long long)e, src, 64);
-                const uint64_t bs = (uint64_t)__shfl((unsigned long long)st, src, 64);
-                const int bit = __ffsll((long long)(be | bs)) - 1;
-                const int64_t j = lo + 64 * (wb + src) + bit;
-                code = ((bs >> bit) & 1) ? 2 * j + 1 : 2 * j;
-            }
+                                       const uint64_t* stb) {
+    const int lane = threadIdx.x & 63;
+    const int w0 = (int)((from - lo) / 64), w1 = (int)((hi - lo + 63) / 64);
+    for (int wb = w0; wb < w1; wb += 64) {
+        const int wi = wb + lane;
+        uint64_t e = 0, st = 0;
+        if (wi < w1) {
+            e = evb[wi];
+            st = stb[wi];
+            const int64_t p0 = lo + 64 * (int64_t)wi;  // position of bit 0
+            uint64_t keep = ~0ull;
+            if (p0 < from) keep &= ~0ull << (from - p0);
+            if (p0 + 64 > hi) keep &= (hi - p0 >= 64) ? ~0ull : ((1ull << (hi - p0)) - 1);
+            e &= keep;
+            st &= keep;
         }
-        if (lane == 0) sh[0] = code;
+        const uint64_t any = __ballot((e | st) != 0);
+        if (any) {
+            const int src = __ffsll((long long)any) - 1;  // first word with an event
+            const uint64_t be = (uint64_t)wave::lane_of((int64_t)e, src), bs = (uint64_t)wave::lane_of((int64_t)st, src);
+            const int bit = __ffsll((long long)(be | bs)) - 1;
+            const int64_t j = lo + 64 * (int64_t)(wb + src) + bit;
+            return ((bs >> bit) & 1) ? 2 * j + 1 : 2 * j;
+        }
     }
-    __syncthreads();
-    return sh[0];
+    return LLONG_MAX;
 }
 
-// leader: the events of [lo, hi) (hi - lo <= 64 kEvWords) into the bitmaps,
-// then the first one; the loads of up to 4 kRT positions are in flight at once
+// leader: the events of [lo, hi) (hi - lo <= 64 kEvWords) into the bitmaps
+// and the low words of the record offsets P after each position into pw,
+// then the first event; the loads of up to 4 kRT positions are in flight at
+// once
 __device__ inline long long search_kept(const ScanArgs& g, int64_t lo, int64_t hi, bool hasH, long long minH,
-                                        uint64_t* evb, uint64_t* stb, long long* sh) {
+                                        uint64_t* evb, uint64_t* stb, uint32_t* pw) {
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    __syncthreads();  // no wave still reads the last window
     for (int64_t base = 0; base < hi - lo; base += 4 * kRT) {
-        int64_t Tv[4], Rn[4];
+        int64_t Tv[4], Rn[4], Pn[4];
         uint8_t in[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -1180,6 +1236,7 @@ __device__ inline long long search_kept(const ScanArgs& g, int64_t lo, int64_t h
             Tv[u] = j < hi ? g.T[j] : 0;
             in[u] = j < hi ? g.inI[j] : 0;
             Rn[u] = (j < hi && j + 1 < g.n) ? g.R[j + 1] : LLONG_MIN;
+            Pn[u] = j < hi ? g.P[j + 1] : 0;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -1188,21 +1245,26 @@ __device__ inline long long search_kept(const ScanArgs& g, int64_t lo, int64_t h
             const bool ev = j < hi && !st && in[u] && Rn[u] < Tv[u];
             const uint64_t be = __ballot(ev), bs = __ballot(st);
             const int64_t wi = (base + u * kRT) / 64 + w;
-            if (lane == 0 && wi < kEvWords) {
-                evb[wi] = be;
-                stb[wi] = bs;
+            if (wi < kEvWords) {
+                if (lane == 0) {
+                    evb[wi] = be;
+                    stb[wi] = bs;
+                }
+                pw[64 * wi + lane] = (uint32_t)(uint64_t)Pn[u];
             }
         }
     }
     __syncthreads();
-    return first_kept(lo, hi, lo, evb, stb, sh);
+    return first_kept(lo, hi, lo, evb, stb);
 }
 
 template <int H>
 __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* sh, int64_t* s_err) {
+    __shared__ long long lred[2][kRW][3];
+    LeadRed red{lred, 0};
     const unsigned nwg = gridDim.x;
     const bool grid = nwg > 1;
-    const int64_t t = threadIdx.x, w = threadIdx.x >> 6;
+    const int64_t t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t n = g.n;
     int ph = 0;
     unsigned posted = 0, beat = 0;
@@ -1233,6 +1295,14 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
         if (posted >= (1u << 23) - 2) *s_err = 1;  // the post word holds 23 bits of sequence
     };
     __shared__ uint64_t evb[kEvWords], stb[kEvWords];  // the kept search window's events
+    __shared__ uint32_t pw[64 * kEvWords];             // and record offsets
+    // the profile's clock: a phase's time runs from the end of the last one
+    long long clk = (long long)wall_clock64();
+    auto tick = [&](int kind) {
+        const long long now = (long long)wall_clock64();
+        ticks[kind] += now - clk;
+        clk = now;
+    };
     while (S0 < n && !failed) {
         ++rounds;
         bool accepted = false, stop = false;
@@ -1246,30 +1316,31 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
             // `from`, else by a new search
             const bool inkept = from >= kept_lo && from < kept_hi;
             const int64_t hi = inkept ? kept_hi : min(n, from + win);
-            long long t0 = (long long)wall_clock64();
+            long long code = LLONG_MAX;
             if (inkept) {
-                first_kept(kept_lo, kept_hi, from, evb, stb, sh);
+                code = first_kept(kept_lo, kept_hi, from, evb, stb);
             } else if (grid && hi - from > g.lead_pos) {
                 kept_lo = kept_hi = 0;
                 searched += hi - from;
                 ++gridc[0];
                 long long d[kDesc] = {PH_SEARCH, ph, from, hi, hasH ? 1 : 0, minH, 0, 0, parts_for(hi - from), 0};
                 grid_phase(d, true);
+                code = sh[0];
             } else if (hi - from <= 64 * kEvWords) {
                 searched += hi - from;
-                search_kept(g, from, hi, hasH, minH, evb, stb, sh);
+                code = search_kept(g, from, hi, hasH, minH, evb, stb, pw);
                 kept_lo = from;
                 kept_hi = hi;
             } else {
                 searched += hi - from;
                 kept_lo = kept_hi = 0;
-                const long long first = search_part(g, from, hi, hasH, minH, t, kRT);
-                reduce_local(first, LLONG_MIN, LLONG_MIN, LLONG_MAX, sred, sh);
+                long long none = LLONG_MIN, none2 = LLONG_MIN;
+                code = search_part(g, from, hi, hasH, minH, t, kRT);
+                reduce_lead(red, code, none, none2);
             }
-            ticks[0] += (long long)wall_clock64() - t0;
+            tick(0);
             ++ph;
             failed = *s_err != 0;
-            const long long code = sh[0];
             if (failed) break;
             if (code == LLONG_MAX) {
                 from = hi;
@@ -1286,8 +1357,11 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
             // positions [fb, b) join the pending group S = [S0, b); the
             // frontier of the loads below and the end of S always coincide:
             // both start at the accepted boundary and move to every verified b
-            const int64_t k1 = g.P[b];
-            t0 = (long long)wall_clock64();
+            // P[b], from the kept window when it holds e (a walk has fewer than
+            // 2^32 records: the low words give its length)
+            const int64_t k1 = e >= kept_lo && e < kept_hi
+                                   ? kfb + (int64_t)(uint32_t)(pw[e - kept_lo] - (uint32_t)(uint64_t)kfb)
+                                   : g.P[b];
             walked += k1 - kfb;
             // ahead only where the separate acceptance walk would be a grid
             // phase: a walk the leader runs alone costs less than the extra
@@ -1301,30 +1375,31 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
                 update_walk<H>(g, S0, fb, b, kfb, k1, w, kRW, spec);
                 __syncthreads();
             }
-            ticks[1] += (long long)wall_clock64() - t0;
+            tick(1);
             fb = b;
             kfb = k1;
             failed = *s_err != 0;
             if (failed) break;
             // min and max of the restricted loads of S, largest load below b
             const int64_t mm = (b - S0) + (b < n ? kFB + kSB + g.nsb - b / ((int64_t)kFB * kSB) : 0);
-            t0 = (long long)wall_clock64();
+            long long vmn, vmx, below;
             if (grid && mm > g.lead_pos) {
                 ++gridc[2];
                 long long d[kDesc] = {PH_MINMAX, ph, S0, b, 0, 0, 0, 0, parts_for(mm), 0};
                 grid_phase(d, true);
+                vmn = sh[0];
+                vmx = sh[1];
+                below = sh[2];
             } else {
-                long long vmn, vmx, fmx;
-                minmax_part(g, S0, b, t, kRT, vmn, vmx, fmx);
-                reduce_local(vmn, vmx, fmx, LLONG_MAX, sred, sh);
+                minmax_part(g, S0, b, t, kRT, vmn, vmx, below);
+                reduce_lead(red, vmn, vmx, below);
             }
-            ticks[2] += (long long)wall_clock64() - t0;
+            tick(2);
             ++ph;
             failed = *s_err != 0;
             if (failed) break;
-            mnS = sh[0];
-            mxS = sh[1];
-            const long long below = sh[2];
+            mnS = vmn;
+            mxS = vmx;
             bool ok = !(hasH && !(mxS < minH));
             ok = ok && (b == n || below < mnS);
             if (ok) {
@@ -1333,7 +1408,6 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
             } else {
                 from = b;  // resume after the boundary examined
                 if (spec) {  // take back the change of T applied ahead
-                    t0 = (long long)wall_clock64();
                     walked += kfb - kS0;
                     if (grid && kfb - kS0 > g.lead_recs) {
                         ++gridc[3];
@@ -1343,7 +1417,7 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
                         accept_walk<H>(g, S0, b, kS0, kfb, w, kRW, -1);
                         __syncthreads();
                     }
-                    ticks[3] += (long long)wall_clock64() - t0;
+                    tick(3);
                     spec = false;
                     failed = *s_err != 0;
                 }
@@ -1351,7 +1425,6 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
         }
         if (!accepted || failed) break;  // the rest is never accepted: no bounds
         const int64_t b = accb;  // == fb, so P[b] == kfb
-        const long long t0 = (long long)wall_clock64();
         // the change of T is still to make unless the boundary's update walk
         // applied it ahead
         const int64_t k0 = spec ? kfb : kS0;
@@ -1364,7 +1437,7 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
             accept_part<H>(g, S0, b, k0, kfb, mnS, mxS, t, kRT, w, kRW);
             __syncthreads();
         }
-        ticks[3] += (long long)wall_clock64() - t0;
+        tick(3);
         if (threadIdx.x == 0) {
             g.groups[2 * ng] = S0;
             g.groups[2 * ng + 1] = b;

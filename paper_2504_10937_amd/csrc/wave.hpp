@@ -40,6 +40,13 @@ __device__ inline int64_t lane63(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// the value of lane `lane` (uniform), the same in every lane
+__device__ inline int64_t lane_of(int64_t v, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 // inclusive scan: lane i ends with op over lanes 0..i (id: op's identity)
 template <class Op>
 __device__ inline int64_t scan(int64_t v, int64_t id, Op op) {
