@@ -380,6 +380,50 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
     const int nc = a.ncache;
     // the 2D part first (its LDS layout), then the hot codes for the rest
     heavy_parts<H == 2 && IDENT>(a, reinterpret_cast<uint8_t*>(qc), reinterpret_cast<int64_t*>(&words[0][0]));
+    // Triangles: the wave's first chunk is read before the codes are staged, so
+    // that its chain of reads (descriptor; payload, row vertices, keys) runs
+    // behind the staging, and the hub pieces come last (24k slots 7.8 -> 6.9 us
+    // a sweep, 84k 10.0 -> 9.1, 1.6M 16.1 -> 15.3).  Edges, whose rows need one
+    // read less, lost by the registers it holds (3M slots 17.7 -> 18.5, 206M
+    // 822 -> 841), and 4-cliques spill.
+    constexpr bool kAhead = H == 3;
+    // Pieces and chunks are dealt to the waves in turn (the chunks from the wave
+    // after the last piece's on), so no wave has two more than another.
+    // Neighbouring chunks (rows with cached codes in common) go to the waves of
+    // one workgroup, except in a plan that leaves waves without work, which is
+    // dealt over the compute units first.
+    const bool few = a.n_pieces + a.n_chunks <= (int64_t)gridDim.x * kWaves;
+    const int64_t cstep = (int64_t)gridDim.x * kWaves;
+    int64_t c0 = few ? (int64_t)w * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * kWaves + w;
+    c0 -= a.n_pieces % cstep;
+    if (c0 < 0) c0 += cstep;
+    ChunkDesc d{}, dn{};
+    if (c0 < a.n_chunks) d = a.desc[c0];
+    if (kAhead && c0 + cstep < a.n_chunks) dn = a.desc[c0 + cstep];
+    // row-start flags of the chunk's words (lane t: word t), bounds, vertex and
+    // key of its first 64 rows (lane l: row l), and its first batch's payload
+    uint64_t hreg, pk;
+    int pa, pb;
+    uint32_t pu;
+    Slot<H> sl[kG];
+    auto load_batch = [&](int t0) {
+#pragma unroll
+        for (int j = 0; j < kG; ++j) {
+            const int off = (t0 + j) * 64 + lane;
+            if (off < d.nsl) sl[j] = load_slot<H>(a.py + d.s0 * (H - 1), off);
+        }
+    };
+    auto load_chunk = [&]() {
+        if (d.nrows <= 0) return;
+        if (kAhead) load_batch(0);
+        hreg = (lane < ((d.nsl + 63) >> 6)) ? __builtin_nontemporal_load(a.head + d.w0 + lane) : 0ull;
+        const int64_t rl = (int64_t)d.r0 + min(lane, d.nrows - 1);
+        pa = (int)(a.rp[rl] - d.s0);
+        pb = (int)(a.rp[rl + 1] - d.s0);
+        pu = IDENT ? (uint32_t)rl : (uint32_t)a.rid[rl];
+        pk = a.Kin[pu];
+    };
+    if (kAhead) load_chunk();
     // the hot codes, 16 bytes per load and all of a thread's loads in flight
     // (2-byte loads took 10 of the 28 us of a 3M-slot sweep)
     {
@@ -403,61 +447,63 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
     //      counter for the next sweep.  With the hub push a piece covers only
     //      the row's hub prefix and adds its wins alone: k_push_finish adds
     //      the pushed wins and writes the key.
-    const bool few = a.n_pieces + a.n_chunks <= (int64_t)gridDim.x * kWaves;
-    for (int64_t pc = few ? (int64_t)w * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * kWaves + w; pc < a.n_pieces;
-         pc += (int64_t)gridDim.x * kWaves) {
-        const int64_t r = a.hp_row[pc];
-        const uint32_t u = IDENT ? (uint32_t)r : (uint32_t)a.rid[r];
-        const int64_t rs = a.rp[r], re = a.rp[r + 1];
-        const int64_t s0 = rs + a.hp_off[pc];
-        // offsets within the piece in 32 bits
-        const int len = (int)min((Hp > 0 ? rs + a.hub_pre[r] : re) - s0, (int64_t)a.piece);
-        const int32_t* __restrict__ pyc = a.py + s0 * (H - 1);
-        const uint64_t Ku = a.Kin[u];
-        const uint16_t Qu = qcode(Ku >> a.B);
-        uint64_t* bw = a.bits + a.chunk_words + a.hwo[r] + (s0 - rs) / 64;
-        uint32_t cnt = 0;
-        for (int base = 0; base < len; base += 64 * kG) {
-            Slot<H> sl[kG];
-            bool in[kG];
-#pragma unroll
-            for (int j = 0; j < kG; ++j) {
-                const int off = base + 64 * j + lane;
-                in[j] = off < len;
-                if (in[j]) sl[j] = load_slot<H>(pyc, off);
-            }
-            uint16_t qu[kG];
-            bool win[kG];
-#pragma unroll
-            for (int j = 0; j < kG; ++j) qu[j] = Qu;
-            decide<H, kG>(qc, nc, a.Qin, a.Kin, sl, in, qu, [&](int) { return Ku; }, win);
-#pragma unroll
-            for (int j = 0; j < kG; ++j) {
-                const uint64_t W = __ballot(win[j]);
-                const int wb = base + 64 * j;  // first slot of this word
-                if (lane == 0 && wb < len) __builtin_nontemporal_store(W, bw + wb / 64);
-                cnt += (uint32_t)__popcll(W);
-            }
-        }
-        if (lane == 0 && Hp > 0) {
-            atomicAdd(a.hub_ctr + r, (unsigned long long)cnt);
-        } else if (lane == 0) {
-            const unsigned long long npc = (unsigned long long)((re - rs + a.piece - 1) / a.piece);
-            const unsigned long long old = atomicAdd(a.hub_ctr + r, (1ull << 40) | (unsigned long long)cnt);
-            if ((old >> 40) == npc - 1) {
-                const uint64_t tot = (old & ((1ull << 40) - 1)) + cnt;
-                const uint64_t Kn = Ku + ((tot * a.inc) << a.B);
-                a.Kout[u] = Kn;
-                a.Qout[u] = qcode(Kn >> a.B);
-                if (GAP) {
-                    const uint64_t A = Ku >> a.B;
-                    sq += (u128)A * A;
-                    mn += (u128)A * tot;
+    auto sweep_pieces = [&]() {
+        for (int64_t pc = few ? (int64_t)w * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * kWaves + w; pc < a.n_pieces;
+             pc += (int64_t)gridDim.x * kWaves) {
+            const int64_t r = a.hp_row[pc];
+            const uint32_t u = IDENT ? (uint32_t)r : (uint32_t)a.rid[r];
+            const int64_t rs = a.rp[r], re = a.rp[r + 1];
+            const int64_t s0 = rs + a.hp_off[pc];
+            // offsets within the piece in 32 bits
+            const int len = (int)min((Hp > 0 ? rs + a.hub_pre[r] : re) - s0, (int64_t)a.piece);
+            const int32_t* __restrict__ pyc = a.py + s0 * (H - 1);
+            const uint64_t Ku = a.Kin[u];
+            const uint16_t Qu = qcode(Ku >> a.B);
+            uint64_t* bw = a.bits + a.chunk_words + a.hwo[r] + (s0 - rs) / 64;
+            uint32_t cnt = 0;
+            for (int base = 0; base < len; base += 64 * kG) {
+                Slot<H> sl[kG];
+                bool in[kG];
+    #pragma unroll
+                for (int j = 0; j < kG; ++j) {
+                    const int off = base + 64 * j + lane;
+                    in[j] = off < len;
+                    if (in[j]) sl[j] = load_slot<H>(pyc, off);
                 }
-                atomicExch(a.hub_ctr + r, 0ull);
+                uint16_t qu[kG];
+                bool win[kG];
+    #pragma unroll
+                for (int j = 0; j < kG; ++j) qu[j] = Qu;
+                decide<H, kG>(qc, nc, a.Qin, a.Kin, sl, in, qu, [&](int) { return Ku; }, win);
+    #pragma unroll
+                for (int j = 0; j < kG; ++j) {
+                    const uint64_t W = __ballot(win[j]);
+                    const int wb = base + 64 * j;  // first slot of this word
+                    if (lane == 0 && wb < len) __builtin_nontemporal_store(W, bw + wb / 64);
+                    cnt += (uint32_t)__popcll(W);
+                }
+            }
+            if (lane == 0 && Hp > 0) {
+                atomicAdd(a.hub_ctr + r, (unsigned long long)cnt);
+            } else if (lane == 0) {
+                const unsigned long long npc = (unsigned long long)((re - rs + a.piece - 1) / a.piece);
+                const unsigned long long old = atomicAdd(a.hub_ctr + r, (1ull << 40) | (unsigned long long)cnt);
+                if ((old >> 40) == npc - 1) {
+                    const uint64_t tot = (old & ((1ull << 40) - 1)) + cnt;
+                    const uint64_t Kn = Ku + ((tot * a.inc) << a.B);
+                    a.Kout[u] = Kn;
+                    a.Qout[u] = qcode(Kn >> a.B);
+                    if (GAP) {
+                        const uint64_t A = Ku >> a.B;
+                        sq += (u128)A * A;
+                        mn += (u128)A * tot;
+                    }
+                    atomicExch(a.hub_ctr + r, 0ull);
+                }
             }
         }
-    }
+    };
+    if (!kAhead) sweep_pieces();
     // ---- chunks: one wave each
     //   A. decision words: kG words per batch, slot payloads then codes in
     //      flight; each word's ballot is kept by lane t
@@ -465,43 +511,28 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
     //      decision words (staged in LDS), key and code update
     // A wave's time is a chain of dependent reads, so what does not depend on
     // the decisions is read ahead: the next chunk's descriptor during this
-    // chunk, and the bounds and keys of the first 64 rows before the first
+    // chunk (two ahead with kAhead), and the bounds and keys of the first 64 rows before the first
     // batch (their codes also serve the slots of chunks of at most 64 rows).
-    // Pieces and chunks are dealt to the waves in turn (the chunks from the wave
-    // after the last piece's on), so no wave has two more than another.
-    // Neighbouring chunks (rows with cached codes in common) go to the waves of
-    // one workgroup, except in a plan that leaves waves without work, which is
-    // dealt over the compute units first.
-    const int64_t cstep = (int64_t)gridDim.x * kWaves;
-    int64_t c0 = few ? (int64_t)w * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * kWaves + w;
-    c0 -= a.n_pieces % cstep;
-    if (c0 < 0) c0 += cstep;
-    ChunkDesc dn{};
-    if (c0 < a.n_chunks) dn = a.desc[c0];
-    for (int64_t c = c0; c < a.n_chunks; c += cstep) {
-        const ChunkDesc d = dn;
-        if (c + cstep < a.n_chunks) dn = a.desc[c + cstep];
+    ChunkDesc dnn{};
+    for (int64_t c = c0; c < a.n_chunks; c += cstep, d = kAhead ? dn : dnn, dn = dnn) {
+        dnn = ChunkDesc{};
+        constexpr int kDescAhead = kAhead ? 2 : 1;
+        if (c + kDescAhead * cstep < a.n_chunks) dnn = a.desc[c + kDescAhead * cstep];
+        if (!kAhead || c != c0) load_chunk();
         const int nrows = d.nrows;
         if (nrows <= 0) continue;
         const int64_t r0 = d.r0, s0 = d.s0, w0 = d.w0;
         const int nsl = d.nsl, nw = (nsl + 63) >> 6;  // <= 32: a chunk spans < 2048 slots
-        const int32_t* __restrict__ pyc = a.py + s0 * (H - 1);
-        const uint64_t hreg = (lane < nw) ? __builtin_nontemporal_load(a.head + w0 + lane) : 0ull;
         const uint64_t le = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
-        // the first 64 rows: bounds, vertex, key, code
-        const int64_t rl = r0 + min(lane, nrows - 1);
-        int pa = (int)(a.rp[rl] - s0), pb = (int)(a.rp[rl + 1] - s0);
-        uint32_t pu = IDENT ? (uint32_t)rl : (uint32_t)a.rid[rl];
-        uint64_t pk = a.Kin[pu];
         const int pq = (int)qcode(pk >> a.B);
         const bool small = nrows <= 64;
         int32_t rowrel = -1;  // chunk-relative row of the slot before the current word
         uint64_t mybits = 0;
         for (int t0 = 0; t0 < nw; t0 += kG) {
+            if (!kAhead || t0 > 0) load_batch(t0);
             uint64_t Hw[kG];
 #pragma unroll
             for (int j = 0; j < kG; ++j) Hw[j] = readlane64(hreg, t0 + j);  // t0 + j < 40
-            Slot<H> sl[kG];
             int32_t row[kG];
             bool val[kG];
             int32_t rb = rowrel;
@@ -511,7 +542,6 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
                 val[j] = off < nsl;
                 row[j] = rb + (int32_t)__popcll(Hw[j] & le);
                 rb += (int32_t)__popcll(Hw[j]);
-                if (val[j]) sl[j] = load_slot<H>(pyc, off);
             }
             rowrel = rb;
             uint16_t qu[kG];
@@ -576,6 +606,7 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();  // words[w] is rewritten by the next chunk
     }
+    if (kAhead) sweep_pieces();
     if (Hp > 0) {  // this workgroup's hub counters (uniform branch)
         __syncthreads();
         uint32_t* o = a.push_part + (int64_t)blockIdx.x * a.pstride;
@@ -591,17 +622,21 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
             red[w][3] = (uint64_t)(mn >> 64);
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
+        if (w == 0) {
             u128 S = 0, M = 0;
-            for (int q = 0; q < kWaves; ++q) {
-                S += ((u128)red[q][1] << 64) | red[q][0];
-                M += ((u128)red[q][3] << 64) | red[q][2];
+            if (lane < kWaves) {
+                S = ((u128)red[lane][1] << 64) | red[lane][0];
+                M = ((u128)red[lane][3] << 64) | red[lane][2];
             }
-            uint64_t* o = a.partial + (int64_t)blockIdx.x * 4;
-            o[0] = (uint64_t)S;
-            o[1] = (uint64_t)(S >> 64);
-            o[2] = (uint64_t)M;
-            o[3] = (uint64_t)(M >> 64);
+            S = wave::sum128_lane63(S);
+            M = wave::sum128_lane63(M);
+            if (lane == 63) {
+                uint64_t* o = a.partial + (int64_t)blockIdx.x * 4;
+                o[0] = (uint64_t)S;
+                o[1] = (uint64_t)(S >> 64);
+                o[2] = (uint64_t)M;
+                o[3] = (uint64_t)(M >> 64);
+            }
         }
     }
 }
