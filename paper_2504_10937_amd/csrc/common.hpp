@@ -118,4 +118,12 @@ void exclusive_scan_u32_to_u64(const uint32_t* in, uint64_t* out, int64_t n, uin
 void radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int begin_bit, int end_bit, uint64_t* tmp_keys,
                     uint32_t* tmp_vals, hipStream_t s);
 
+// Both orientations (a << vb | b) of every pair of distinct ids below n,
+// grouped by the top `bits` (at most 16) of their 2 vb bits: ka and kb hold
+// 2 np keys each, the result is one of them and *count_dev the keys in it.
+// *err gets bit 0 for an id out of range and, when strict, bit 1 for a loop.
+const uint64_t* bucket_pairs(const int32_t* src, const int32_t* dst, int64_t np, int64_t n, int vb, int bits,
+                             bool strict, uint64_t* ka, uint64_t* kb, uint64_t* count_dev, unsigned* err,
+                             hipStream_t s);
+
 }  // namespace lds

@@ -54,6 +54,168 @@ __global__ void k_compact(const uint64_t* keys, const uint32_t* flag, const uint
     out[pos[i]] = keys[i];
 }
 
+// ------------------------------------------------------------- buckets
+// The symmetric rows without a full sort.  The pairs' keys are grouped by the
+// top bits of their row (one or two radix passes), so that a bucket's keys
+// (those of 2^rowbits consecutive rows) fit a workgroup's LDS; the workgroup
+// drops duplicates with a hash set and groups the rest by row.  Rows come out
+// unsorted: they are sorted once, after the renumbering.  Compared with the
+// full sort of both ids (6 passes, then flags, a scan and a compaction over
+// all keys) the ingest of 2.1e8 keys went from 20 to 12.2 ms (the buckets
+// themselves 1.6) and of 4e7 keys from 4.8 to 2.3.  Bound: HBM (16 B per key
+// and pass, 12 for the buckets) and, in the buckets, LDS atomics.
+constexpr int kBucketSmall = 8192;   // keys of a bucket for a workgroup with half a CU's LDS
+constexpr int kBucketLarge = 24576;  // and for one with all of it
+constexpr int kBucketRowBits = 12;   // most rows of a bucket: 2^12 counters in LDS
+
+__global__ void k_bucket_starts(const uint64_t* keys, const uint64_t* count, int shift, int64_t buckets,
+                                int64_t* start) {
+    const int64_t q = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (q > buckets) return;
+    int64_t lo = 0, hi = (int64_t)*count;  // first key of bucket q or a later one
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if ((int64_t)(keys[mid] >> shift) < q) lo = mid + 1;
+        else hi = mid;
+    }
+    start[q] = lo;
+}
+
+// one bucket: CAP keys at most, in registers; tab: a table of up to TAB (a
+// power of two) 32-bit keys, cnt: the rows' counts, part: the waves' sums
+template <int NT, int CAP, int TAB>
+__device__ inline void bucket_rows(const uint64_t* keys, int64_t q, int64_t s0, int len, int vb, int rowbits,
+                                   int64_t n, int strict, uint32_t* out, uint32_t* bucket_n, int32_t* deg,
+                                   int64_t* rstart, unsigned* err, uint32_t* tab, uint32_t* cnt, uint32_t* part) {
+    constexpr int PER = CAP / NT;
+    constexpr uint32_t kEmpty = 0xffffffffu;  // no key: both ids would be all ones, which n never is
+    const int R = 1 << rowbits, t = threadIdx.x, lane = t & 63, w = t >> 6;
+    int size = 1024;  // of the table: at least twice the keys, or all of it
+    while (size < 2 * len && size < TAB) size <<= 1;
+    const uint32_t slot = (uint32_t)size - 1;
+    for (int i = t; i < size; i += NT) tab[i] = kEmpty;
+    for (int i = t; i < R; i += NT) cnt[i] = 0;
+    const uint64_t mask = (1ull << (vb + rowbits)) - 1;
+    uint32_t key[PER], rank[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) key[k] = k * NT + t < len ? (uint32_t)(keys[s0 + k * NT + t] & mask) : kEmpty;
+    __syncthreads();
+    bool dup = false;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        rank[k] = kEmpty;  // not a row's entry (no key, or a duplicate)
+        if (key[k] == kEmpty) continue;
+        uint32_t p = (key[k] * 2654435769u) >> 8;
+        for (;; ++p) {  // ends: more than a quarter of the table stays empty
+            const uint32_t old = atomicCAS(&tab[p & slot], kEmpty, key[k]);
+            if (old == kEmpty) {
+                rank[k] = atomicAdd(&cnt[key[k] >> vb], 1u);
+                break;
+            }
+            if (old == key[k]) {
+                dup = true;
+                break;
+            }
+        }
+    }
+    if (strict && dup) atomicOr(err, 4u);
+    __syncthreads();
+    // counts to first places (rows in order, PERR consecutive ones a thread)
+    const int perr = (R + NT - 1) / NT, r0 = min(R, t * perr), r1 = min(R, r0 + perr);
+    uint32_t sum = 0;
+    for (int r = r0; r < r1; ++r) sum += cnt[r];
+    uint32_t inc = sum;
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)inc, m, 64);
+        if (lane >= m) inc += y;
+    }
+    if (lane == 63) part[w] = inc;
+    __syncthreads();
+    uint32_t run = inc - sum;
+    for (int x = 0; x < w; ++x) run += part[x];
+    if (t == NT - 1) bucket_n[q] = run + sum;
+    for (int r = r0; r < r1; ++r) {
+        const uint32_t c = cnt[r];
+        const int64_t o = (q << rowbits) + r;
+        if (o < n) {
+            deg[o] = (int32_t)c;
+            rstart[o] = s0 + run;
+        }
+        cnt[r] = run;
+        run += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+        if (rank[k] != kEmpty) out[s0 + cnt[key[k] >> vb] + rank[k]] = key[k];
+}
+
+// small buckets; the others go to the list of large ones (list[0]: their
+// number), those past kBucketLarge raise err bit 3
+__global__ __launch_bounds__(1024) void k_buckets(const uint64_t* keys, const int64_t* start, int64_t buckets, int vb,
+                                                 int rowbits, int64_t n, int strict, uint32_t* out,
+                                                 uint32_t* bucket_n, int32_t* deg, int64_t* rstart, int32_t* list,
+                                                 unsigned* err) {
+    extern __shared__ uint32_t bdyn[];  // 2 * kBucketSmall table entries, the rows' counts
+    __shared__ uint32_t part[16];
+    const int64_t q = blockIdx.x, s0 = start[q], len = start[q + 1] - s0;
+    if (len > kBucketSmall) {
+        if (threadIdx.x == 0) {
+            if (len > kBucketLarge) atomicOr(err, 8u);
+            else list[1 + atomicAdd(list, 1)] = (int32_t)q;
+        }
+        return;
+    }
+    bucket_rows<1024, kBucketSmall, 2 * kBucketSmall>(keys, q, s0, (int)len, vb, rowbits, n, strict, out, bucket_n,
+                                                     deg, rstart, err, bdyn, bdyn + 2 * kBucketSmall, part);
+}
+
+__global__ __launch_bounds__(1024) void k_buckets_large(const uint64_t* keys, const int64_t* start, int vb,
+                                                        int rowbits, int64_t n, int strict, uint32_t* out,
+                                                        uint32_t* bucket_n, int32_t* deg, int64_t* rstart,
+                                                        const int32_t* list, unsigned* err) {
+    extern __shared__ uint32_t bdyn[];  // 32768 table entries, the rows' counts
+    __shared__ uint32_t part[16];
+    for (int k = blockIdx.x; k < list[0]; k += gridDim.x) {
+        const int64_t q = list[1 + k], s0 = start[q];
+        bucket_rows<1024, kBucketLarge, 32768>(keys, q, s0, (int)(start[q + 1] - s0), vb, rowbits, n, strict, out,
+                                               bucket_n, deg, rstart, err, bdyn, bdyn + 32768, part);
+        __syncthreads();
+    }
+}
+
+// the buckets' slots to their internal rows: row o's move from the bucket's
+// order to rowptr[int_of[o]], columns renumbered.  Bound: the random reads of
+// int_of (4 bytes a slot).
+__global__ __launch_bounds__(kT) void k_bucket_permute(const uint32_t* in, const int64_t* start,
+                                                       const uint32_t* bucket_n, int vb, int rowbits, int64_t n,
+                                                       const int64_t* rstart, const int32_t* int_of,
+                                                       const int64_t* rowptr, int32_t* col) {
+    extern __shared__ int64_t shift_of[];  // per row: first internal slot less the first bucket slot
+    const int64_t q = blockIdx.x, s0 = start[q];
+    const int len = (int)bucket_n[q], R = 1 << rowbits;
+    if (len == 0) return;
+    for (int r = threadIdx.x; r < R; r += kT) {
+        const int64_t o = (q << rowbits) + r;
+        if (o < n) shift_of[r] = rowptr[int_of[o]] - rstart[o];
+    }
+    __syncthreads();
+    const uint32_t mask = (uint32_t)((1ull << vb) - 1);
+    constexpr int U = 4;
+    for (int j = threadIdx.x; j < len; j += kT * U) {
+        uint32_t k[U];
+        int32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = j + u * kT < len ? in[s0 + j + u * kT] : 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = j + u * kT < len ? int_of[k[u] & mask] : 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (j + u * kT < len) col[shift_of[k[u] >> vb] + s0 + j + u * kT] = c[u];
+    }
+}
+
 // run boundaries of the sorted symmetric keys: first slot and one-past-last
 // slot of every row that has slots
 __global__ void k_row_bounds(const uint64_t* sk, int64_t ns, int vbits, int64_t* rstart, int64_t* rend) {
@@ -70,24 +232,31 @@ __global__ void k_row_deg(const int64_t* rstart, const int64_t* rend, int64_t n,
     deg[v] = (int32_t)(rend[v] - rstart[v]);
 }
 
+// out: the largest degree; nz[0]: vertices with slots, nz[1]: slots
 __global__ void k_maxdeg(const int32_t* deg, int64_t n, int* out, unsigned long long* nz) {
     // grid-stride (the launch is capped at kReduceWG workgroups): one atomic
     // per wave on each of the two counters; with a wave per 64 entries the
     // waves of a 4M-entry array queued ~125k atomics on two addresses (0.75 ms)
     int d = 0;
     unsigned c = 0;  // entries > 0 (fewer than 2^32)
+    unsigned long long sum = 0;
     for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT) {
         const int x = deg[i];
+        sum += (unsigned)x;
         d = max(d, x);
         c += x > 0 ? 1 : 0;
     }
     for (int off = 32; off > 0; off >>= 1) {
         d = max(d, __shfl_xor(d, off, 64));
         c += (unsigned)__shfl_xor((int)c, off, 64);
+        sum += __shfl_xor(sum, off, 64);
     }
     if ((threadIdx.x & 63) == 0) {
         atomicMax(out, d);
-        if (c) atomicAdd(nz, (unsigned long long)c);
+        if (c) {
+            atomicAdd(nz, (unsigned long long)c);
+            atomicAdd(nz + 1, sum);
+        }
     }
 }
 
@@ -778,8 +947,8 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
     const int vb = g.vbits;
     const uint64_t sentinel = ((uint64_t)n << vb) | (uint64_t)n;
 
-    // 1. both orientations of every pair -> sort -> drop duplicates and
-    //    self-loops: the symmetric CSR in original ids, rows ascending
+    // 1. both orientations of every pair, without duplicates and self-loops,
+    //    by row: the symmetric rows and their degrees in original ids
     DBuf<int32_t> dsrc, ddst;
     const int32_t *ps = src, *pd = dst;
     if (!on_device && npairs > 0) {
@@ -790,71 +959,132 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         ps = dsrc.p;
         pd = ddst.p;
     }
-    DBuf<unsigned> err;
-    err.alloc(1, s);
-    LDS_HIP(hipMemsetAsync(err.p, 0, sizeof(unsigned), s));
-    DBuf<uint64_t> skeys;
-    int64_t ns = 0;
-    if (npairs > 0) {
-        const int64_t nk = 2 * npairs;
-        DBuf<uint64_t> keys, tmp;
-        keys.alloc(nk, s);
-        tmp.alloc(nk, s);
-        k_canon<<<grid_for(npairs, kT), kT, 0, s>>>(ps, pd, npairs, n, vb, strict, keys.p, err.p);
-        LDS_HIP(hipGetLastError());
-        dsrc.release();
-        ddst.release();
-        radix_sort_u64(keys.p, nullptr, nk, 0, 2 * vb, tmp.p, nullptr, s);
-        DBuf<uint32_t> flag;
-        flag.alloc(nk, s);
-        k_unique_flags<<<grid_for(nk, kT), kT, 0, s>>>(keys.p, nk, sentinel, strict, flag.p, err.p);
-        LDS_HIP(hipGetLastError());
-        DBuf<uint64_t> total;
-        total.alloc(1, s);
-        exclusive_scan_u32_to_u64(flag.p, tmp.p, nk, total.p, s);
-        ns = (int64_t)d2h(total.p, s);
-        skeys.alloc(ns, s);
-        k_compact<<<grid_for(nk, kT), kT, 0, s>>>(keys.p, flag.p, tmp.p, nk, skeys.p);
-        LDS_HIP(hipGetLastError());
-    }
-    const unsigned e = d2h(err.p, s);
-    LDS_CHECK(!(e & 1u), ST_INVALID, "vertex id out of range [0, n)");
-    LDS_CHECK(!(e & 2u), ST_INVALID, "self-loop in strict mode");
-    LDS_CHECK(!(e & 4u), ST_INVALID, "duplicate pair in strict mode");
-    g.m = ns / 2;
-
-    // 2. degrees from the row runs (no atomics), renumbering by degree desc,
-    //    original id asc
+    // what the host reads of the device's findings, in one copy
+    struct Found {
+        unsigned long long nz, slots;
+        int dmax;
+        unsigned err;
+    };
+    DBuf<Found> found;
+    found.alloc(1, s);
+    Found h{};
+    auto read_found = [&]() {
+        h = d2h(found.p, s);
+        LDS_CHECK(!(h.err & 1u), ST_INVALID, "vertex id out of range [0, n)");
+        LDS_CHECK(!(h.err & 2u), ST_INVALID, "self-loop in strict mode");
+        LDS_CHECK(!(h.err & 4u), ST_INVALID, "duplicate pair in strict mode");
+    };
+    auto degrees_found = [&](const int32_t* deg) {
+        if (n > 0) {
+            k_maxdeg<<<std::min(grid_for(n, kT), kReduceWG), kT, 0, s>>>(deg, n, &found.p->dmax, &found.p->nz);
+            LDS_HIP(hipGetLastError());
+        }
+    };
+    LDS_HIP(hipMemsetAsync(found.p, 0, sizeof(Found), s));
     DBuf<int32_t> deg_orig;
-    DBuf<int64_t> rstart, rend;
+    DBuf<int64_t> rstart;
     deg_orig.alloc(n, s);
     rstart.alloc(n, s);
-    rend.alloc(n, s);
-    if (n) {
-        LDS_HIP(hipMemsetAsync(rstart.p, 0, n * sizeof(int64_t), s));
-        LDS_HIP(hipMemsetAsync(rend.p, 0, n * sizeof(int64_t), s));
-    }
-    if (ns > 0) {
-        k_row_bounds<<<grid_for(ns, kT), kT, 0, s>>>(skeys.p, ns, vb, rstart.p, rend.p);
+    // 1a. by buckets of rows: bits of the row that number the buckets, so that
+    //     a bucket holds 2048 to 4096 keys in the mean, at most 2^12 rows, and
+    //     a key's other bits fit 32; graphs past 2^16 such buckets, a bucket
+    //     past kBucketLarge keys (a vertex of that degree, ids that crowd) and
+    //     inputs that one workgroup sorts go by the full sort
+    const int64_t nk = 2 * npairs;
+    int bits = std::max({bits_for((uint64_t)(nk >> 12)), vb - kBucketRowBits, 2 * vb - 32, 1});
+    const int rowbits = vb - bits;
+    bool bucketed = nk > 4096 && bits <= 16 && rowbits >= 0;
+    DBuf<uint32_t> bkeys, bucket_n;
+    DBuf<int64_t> bstart;
+    if (bucketed) {
+        const int64_t buckets = (int64_t)1 << bits;
+        DBuf<uint64_t> ka, kb, count;
+        DBuf<int32_t> list;
+        ka.alloc(nk, s);
+        if (bits > 8) kb.alloc(nk, s);
+        count.alloc(1, s);
+        const uint64_t* keys = bucket_pairs(ps, pd, npairs, n, vb, bits, strict, ka.p, kb.p, count.p,
+                                            &found.p->err, s);
+        bstart.alloc(buckets + 1, s);
+        k_bucket_starts<<<grid_for(buckets + 1, kT), kT, 0, s>>>(keys, count.p, 2 * vb - bits, buckets, bstart.p);
         LDS_HIP(hipGetLastError());
-    }
-    if (n > 0) {
-        k_row_deg<<<grid_for(n, kT), kT, 0, s>>>(rstart.p, rend.p, n, deg_orig.p);
+        bkeys.alloc(nk, s);
+        bucket_n.alloc(buckets, s);
+        list.alloc(buckets + 1, s);
+        LDS_HIP(hipMemsetAsync(list.p, 0, sizeof(int32_t), s));
+        LDS_HIP(hipMemsetAsync(bucket_n.p, 0, bucket_n.bytes(), s));
+        const size_t rows_lds = ((size_t)1 << rowbits) * sizeof(uint32_t);
+        const size_t small_lds = 2 * kBucketSmall * sizeof(uint32_t) + rows_lds;
+        const size_t large_lds = 32768 * sizeof(uint32_t) + rows_lds;
+        LDS_HIP(hipFuncSetAttribute((const void*)k_buckets, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)(2 * kBucketSmall * sizeof(uint32_t) + ((size_t)4 << kBucketRowBits))));
+        LDS_HIP(hipFuncSetAttribute((const void*)k_buckets_large, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)(32768 * sizeof(uint32_t) + ((size_t)4 << kBucketRowBits))));
+        k_buckets<<<(unsigned)buckets, 1024, small_lds, s>>>(keys, bstart.p, buckets, vb, rowbits, n, strict, bkeys.p,
+                                                           bucket_n.p, deg_orig.p, rstart.p, list.p, &found.p->err);
         LDS_HIP(hipGetLastError());
-    }
-    rend.release();
-    DBuf<int> dmax;
-    DBuf<unsigned long long> nz;
-    dmax.alloc(1, s);
-    nz.alloc(1, s);
-    LDS_HIP(hipMemsetAsync(dmax.p, 0, sizeof(int), s));
-    LDS_HIP(hipMemsetAsync(nz.p, 0, sizeof(unsigned long long), s));
-    if (n > 0) {
-        k_maxdeg<<<std::min(grid_for(n, kT), kReduceWG), kT, 0, s>>>(deg_orig.p, n, dmax.p, nz.p);
+        k_buckets_large<<<(unsigned)std::min<int64_t>(buckets, kReduceWG), 1024, large_lds, s>>>(
+            keys, bstart.p, vb, rowbits, n, strict, bkeys.p, bucket_n.p, deg_orig.p, rstart.p, list.p, &found.p->err);
         LDS_HIP(hipGetLastError());
+        degrees_found(deg_orig.p);
+        read_found();
+        if (h.err & 8u) {  // a bucket too large
+            bucketed = false;
+            bkeys.release();
+            bucket_n.release();
+            bstart.release();
+            LDS_HIP(hipMemsetAsync(found.p, 0, sizeof(Found), s));
+        }
     }
-    g.max_deg = d2h(dmax.p, s);
-    g.n_nz = (int64_t)d2h(nz.p, s);
+    // 1b. by a full sort of both orientations: duplicates are adjacent, rows
+    //     are runs
+    DBuf<uint64_t> skeys;
+    int64_t ns = bucketed ? (int64_t)h.slots : 0;
+    if (!bucketed) {
+        if (npairs > 0) {
+            DBuf<uint64_t> keys, tmp;
+            keys.alloc(nk, s);
+            tmp.alloc(nk, s);
+            k_canon<<<grid_for(npairs, kT), kT, 0, s>>>(ps, pd, npairs, n, vb, strict, keys.p, &found.p->err);
+            LDS_HIP(hipGetLastError());
+            radix_sort_u64(keys.p, nullptr, nk, 0, 2 * vb, tmp.p, nullptr, s);
+            DBuf<uint32_t> flag;
+            flag.alloc(nk, s);
+            k_unique_flags<<<grid_for(nk, kT), kT, 0, s>>>(keys.p, nk, sentinel, strict, flag.p, &found.p->err);
+            LDS_HIP(hipGetLastError());
+            DBuf<uint64_t> total;
+            total.alloc(1, s);
+            exclusive_scan_u32_to_u64(flag.p, tmp.p, nk, total.p, s);
+            ns = (int64_t)d2h(total.p, s);
+            skeys.alloc(ns, s);
+            k_compact<<<grid_for(nk, kT), kT, 0, s>>>(keys.p, flag.p, tmp.p, nk, skeys.p);
+            LDS_HIP(hipGetLastError());
+        }
+        // degrees from the row runs (no atomics)
+        DBuf<int64_t> rend;
+        rend.alloc(n, s);
+        if (n) {
+            LDS_HIP(hipMemsetAsync(rstart.p, 0, n * sizeof(int64_t), s));
+            LDS_HIP(hipMemsetAsync(rend.p, 0, n * sizeof(int64_t), s));
+        }
+        if (ns > 0) {
+            k_row_bounds<<<grid_for(ns, kT), kT, 0, s>>>(skeys.p, ns, vb, rstart.p, rend.p);
+            LDS_HIP(hipGetLastError());
+        }
+        if (n > 0) {
+            k_row_deg<<<grid_for(n, kT), kT, 0, s>>>(rstart.p, rend.p, n, deg_orig.p);
+            LDS_HIP(hipGetLastError());
+        }
+        degrees_found(deg_orig.p);
+        read_found();
+    }
+    dsrc.release();
+    ddst.release();
+    g.m = ns / 2;
+
+    // 2. renumbering by degree desc, original id asc
+    g.max_deg = h.dmax;
+    g.n_nz = (int64_t)h.nz;
     g.orig_of.alloc(n, s);
     g.int_of.alloc(n, s);
     g.deg.alloc(n, s);
@@ -886,9 +1116,14 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         LDS_HIP(hipGetLastError());
     }
     if (ns > 0) {
-        k_permute<<<grid_for(ns, kT), kT, 0, s>>>(skeys.p, ns, vb, rstart.p, g.int_of.p, g.rowptr.p, g.col.p);
+        if (bucketed)
+            k_bucket_permute<<<(unsigned)((int64_t)1 << bits), kT, ((size_t)1 << rowbits) * sizeof(int64_t), s>>>(
+                bkeys.p, bstart.p, bucket_n.p, vb, rowbits, n, rstart.p, g.int_of.p, g.rowptr.p, g.col.p);
+        else
+            k_permute<<<grid_for(ns, kT), kT, 0, s>>>(skeys.p, ns, vb, rstart.p, g.int_of.p, g.rowptr.p, g.col.p);
         LDS_HIP(hipGetLastError());
     }
+    bkeys.release();
     skeys.release();
     sort_rows(g, s);
 
