@@ -612,14 +612,19 @@ void d2h_fill(V& v, const void* dev, size_t count, hipStream_t s) {
 }  // namespace
 
 void HostGraph::load(const Graph& g, int mode, hipStream_t s) {
-    n = g.n;
-    rp.assign(n + 1, 0);
-    orig.assign(n, 0);
-    if (n > 0) {
-        LDS_HIP(hipMemcpyAsync(rp.data(), g.rowptr.p, (n + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        LDS_HIP(hipMemcpyAsync(orig.data(), g.orig_of.p, n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    // a first triangle query adds the triangles to a graph whose adjacency is
+    // already here: edge queries running on it read that and nothing of the
+    // triangles, so it is left untouched
+    if (rp.empty()) {
+        n = g.n;
+        rp.assign(n + 1, 0);
+        orig.assign(n, 0);
+        if (n > 0) {
+            LDS_HIP(hipMemcpyAsync(rp.data(), g.rowptr.p, (n + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, s));
+            LDS_HIP(hipMemcpyAsync(orig.data(), g.orig_of.p, n * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        }
+        d2h_fill(col, g.col.p, (size_t)(2 * g.m), s);
     }
-    d2h_fill(col, g.col.p, (size_t)(2 * g.m), s);
     tri.clear();
     if (mode == 3 && g.T > 0) d2h_fill(tri, g.tri.p, (size_t)(3 * g.T), s);
     LDS_HIP(hipStreamSynchronize(s));
