@@ -118,34 +118,49 @@ __device__ inline uint16_t qcode(uint64_t A) {
 
 // the h-1 other vertices of the pattern stored at a slot; the slot arrays
 // are streamed once per iteration, so they are read non-temporally to keep
-// the caches for the gathered keys
-template <int H>
+// the caches for the gathered keys.  PK: packed (4-cliques), kept packed until
+// a member is used
+template <int H, bool PK>
 struct Slot {
     int32_t v[H - 1];
+    static constexpr int kWords = H - 1;
+    __device__ inline uint32_t id(int q) const { return (uint32_t)v[q]; }
+};
+template <>
+struct Slot<4, true> {
+    uint64_t x;
+    static constexpr int kWords = 2;
+    __device__ inline uint32_t id(int q) const { return (uint32_t)PackedSlot::id(x, q); }
 };
 
-template <int H>
-__device__ inline Slot<H> load_slot(const int32_t* __restrict__ py, int64_t s);
+template <int H, bool PK>
+__device__ inline Slot<H, PK> load_slot(const int32_t* __restrict__ py, int64_t s);
 template <>
-__device__ inline Slot<2> load_slot<2>(const int32_t* __restrict__ py, int64_t s) {
-    Slot<2> r;
+__device__ inline Slot<2, false> load_slot<2, false>(const int32_t* __restrict__ py, int64_t s) {
+    Slot<2, false> r;
     r.v[0] = __builtin_nontemporal_load(py + s);
     return r;
 }
 template <>
-__device__ inline Slot<3> load_slot<3>(const int32_t* __restrict__ py, int64_t s) {
+__device__ inline Slot<3, false> load_slot<3, false>(const int32_t* __restrict__ py, int64_t s) {
     const long long x = __builtin_nontemporal_load(reinterpret_cast<const long long*>(py) + s);
-    Slot<3> r;
+    Slot<3, false> r;
     r.v[0] = (int32_t)(uint32_t)(unsigned long long)x;
     r.v[1] = (int32_t)(uint32_t)((unsigned long long)x >> 32);
     return r;
 }
 template <>
-__device__ inline Slot<4> load_slot<4>(const int32_t* __restrict__ py, int64_t s) {
-    Slot<4> r;
+__device__ inline Slot<4, false> load_slot<4, false>(const int32_t* __restrict__ py, int64_t s) {
+    Slot<4, false> r;
     r.v[0] = __builtin_nontemporal_load(py + 3 * s);
     r.v[1] = __builtin_nontemporal_load(py + 3 * s + 1);
     r.v[2] = __builtin_nontemporal_load(py + 3 * s + 2);
+    return r;
+}
+template <>
+__device__ inline Slot<4, true> load_slot<4, true>(const int32_t* __restrict__ py, int64_t s) {
+    Slot<4, true> r;
+    r.x = (uint64_t)__builtin_nontemporal_load(reinterpret_cast<const long long*>(py) + s);
     return r;
 }
 
@@ -187,9 +202,9 @@ __device__ inline uint16_t qload(const uint16_t* __restrict__ qc, int nc, const 
 // compared, all reads of a few slots in flight together: ties are 0.1-2% of
 // the slots, but most batches hold one, and a read and wait per tied word was
 // the longest part of a batch's chain of dependent reads.
-template <int H, int G, class KU>
+template <int H, int G, bool PK, class KU>
 __device__ inline void decide(const uint16_t* __restrict__ qc, int nc, const uint16_t* __restrict__ Q,
-                              const uint64_t* __restrict__ K, const Slot<H> (&sl)[G], const bool (&in)[G],
+                              const uint64_t* __restrict__ K, const Slot<H, PK> (&sl)[G], const bool (&in)[G],
                               const uint16_t (&qu)[G], KU ku, bool (&win)[G]) {
     uint32_t tied[G];
 #pragma unroll
@@ -201,7 +216,7 @@ __device__ inline void decide(const uint16_t* __restrict__ qc, int nc, const uin
     for (int q = H - 2; q >= 0; --q) {
         uint16_t qv[G];
 #pragma unroll
-        for (int j = 0; j < G; ++j) qv[j] = win[j] ? qload(qc, nc, Q, (uint32_t)sl[j].v[q]) : (uint16_t)0;
+        for (int j = 0; j < G; ++j) qv[j] = win[j] ? qload(qc, nc, Q, sl[j].id(q)) : (uint16_t)0;
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             if (qu[j] == qv[j]) tied[j] |= 1u << q;
@@ -222,7 +237,7 @@ __device__ inline void decide(const uint16_t* __restrict__ qc, int nc, const uin
                 k0[j] = ku(x);
 #pragma unroll
                 for (int q = 0; q < H - 1; ++q)
-                    if (H == 2 || ((tied[x] >> q) & 1u)) kv[j][q] = K[(uint32_t)sl[x].v[q]];
+                    if (H == 2 || ((tied[x] >> q) & 1u)) kv[j][q] = K[sl[x].id(q)];
             }
         }
 #pragma unroll
@@ -371,7 +386,7 @@ __device__ inline void heavy_parts(const SweepArgs& a, uint8_t* dyn, int64_t* sg
 // into LDS; those vertices take most of the gathers of a power-law graph.
 // It then processes hub rows (whole workgroup each) and chunks (one wave
 // each), both strided over the grid.
-template <int H, bool IDENT, bool GAP>
+template <int H, bool IDENT, bool GAP, bool PK>
 __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
     extern __shared__ __align__(16) uint16_t qc[];
     __shared__ uint64_t red[kWaves][4];
@@ -405,12 +420,13 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
     uint64_t hreg, pk;
     int pa, pb;
     uint32_t pu;
-    Slot<H> sl[kG];
+    Slot<H, PK> sl[kG];
+    constexpr int PW = Slot<H, PK>::kWords;
     auto load_batch = [&](int t0) {
 #pragma unroll
         for (int j = 0; j < kG; ++j) {
             const int off = (t0 + j) * 64 + lane;
-            if (off < d.nsl) sl[j] = load_slot<H>(a.py + d.s0 * (H - 1), off);
+            if (off < d.nsl) sl[j] = load_slot<H, PK>(a.py + d.s0 * PW, off);
         }
     };
     auto load_chunk = [&]() {
@@ -456,25 +472,25 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
             const int64_t s0 = rs + a.hp_off[pc];
             // offsets within the piece in 32 bits
             const int len = (int)min((Hp > 0 ? rs + a.hub_pre[r] : re) - s0, (int64_t)a.piece);
-            const int32_t* __restrict__ pyc = a.py + s0 * (H - 1);
+            const int32_t* __restrict__ pyc = a.py + s0 * PW;
             const uint64_t Ku = a.Kin[u];
             const uint16_t Qu = qcode(Ku >> a.B);
             uint64_t* bw = a.bits + a.chunk_words + a.hwo[r] + (s0 - rs) / 64;
             uint32_t cnt = 0;
             for (int base = 0; base < len; base += 64 * kG) {
-                Slot<H> sl[kG];
+                Slot<H, PK> sl[kG];
                 bool in[kG];
     #pragma unroll
                 for (int j = 0; j < kG; ++j) {
                     const int off = base + 64 * j + lane;
                     in[j] = off < len;
-                    if (in[j]) sl[j] = load_slot<H>(pyc, off);
+                    if (in[j]) sl[j] = load_slot<H, PK>(pyc, off);
                 }
                 uint16_t qu[kG];
                 bool win[kG];
     #pragma unroll
                 for (int j = 0; j < kG; ++j) qu[j] = Qu;
-                decide<H, kG>(qc, nc, a.Qin, a.Kin, sl, in, qu, [&](int) { return Ku; }, win);
+                decide<H, kG, PK>(qc, nc, a.Qin, a.Kin, sl, in, qu, [&](int) { return Ku; }, win);
     #pragma unroll
                 for (int j = 0; j < kG; ++j) {
                     const uint64_t W = __ballot(win[j]);
@@ -556,13 +572,13 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
                                    : (uint16_t)0;
             }
             bool win[kG];
-            decide<H, kG>(qc, nc, a.Qin, a.Kin, sl, val, qu,
+            decide<H, kG, PK>(qc, nc, a.Qin, a.Kin, sl, val, qu,
                           [&](int j) { return a.Kin[IDENT ? (uint32_t)(r0 + row[j]) : (uint32_t)a.rid[r0 + row[j]]]; },
                           win);
 #pragma unroll
             for (int j = 0; j < kG; ++j) {
                 if (H == 2 && Hp > 0 && val[j] && !win[j]) {  // a hub's win, pushed to its counter
-                    const uint32_t v = (uint32_t)sl[j].v[0];
+                    const uint32_t v = sl[j].id(0);
                     if (v < (uint32_t)Hp) atomicAdd(&hcnt[v >> 1], 1u << ((v & 1u) * 16));
                 }
                 const uint64_t W = __ballot(win[j]);
@@ -812,7 +828,7 @@ __global__ void k_loads(const uint64_t* K, const int32_t* orig_of, int64_t n, in
 
 // exact split numerator of every incidence slot from the stored decision
 // words: a = a0 + sum_i inc_i [slot won in iteration i], inc_i = incm (i+1)
-template <int H>
+template <int H, bool PK>
 __global__ void k_splits(const int64_t* rp, const int32_t* rid, const int32_t* py, const int64_t* bitbase,
                          int64_t nrows, int64_t nslots, const uint64_t* bits, int64_t total_words, int iters,
                          uint64_t a0, uint64_t incm, const int32_t* orig_of, int32_t* verts, uint64_t* num) {
@@ -834,7 +850,8 @@ __global__ void k_splits(const int64_t* rp, const int32_t* rid, const int32_t* p
     }
     const int32_t x = rid ? rid[r] : (int32_t)r;
     verts[H * s] = orig_of[x];
-    for (int j = 0; j < H - 1; ++j) verts[H * s + 1 + j] = orig_of[py[(H - 1) * s + j]];
+    const Slot<H, PK> sl = load_slot<H, PK>(py, s);
+    for (int j = 0; j < H - 1; ++j) verts[H * s + 1 + j] = orig_of[sl.id(j)];
     num[s] = a;
 }
 
@@ -865,7 +882,7 @@ __global__ void k_splits_heavy(const uint32_t* csr, const uint32_t* pay, int64_t
 
 uint64_t denom(int mode, int64_t i) { return fw_denom(mode, i); }
 
-template <int H, bool IDENT>
+template <int H, bool IDENT, bool PK = false>
 void launch_sweep(const SweepArgs& a, unsigned blocks, bool gap, hipStream_t s) {
     const bool heavy = H == 2 && IDENT && a.n_parts > 0;
     const size_t push_lds = a.n_push > 0 ? (size_t)((a.ncache + 1) & ~1) * 2 + (size_t)a.pstride * 4 : 0;
@@ -874,19 +891,19 @@ void launch_sweep(const SweepArgs& a, unsigned blocks, bool gap, hipStream_t s) 
     if (gap) {
         static bool attr = false;
         if (!attr) {
-            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, IDENT, true>,
+            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, IDENT, true, PK>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
             attr = true;
         }
-        k_fw_sweep<H, IDENT, true><<<blocks, kPT, lds, s>>>(a);
+        k_fw_sweep<H, IDENT, true, PK><<<blocks, kPT, lds, s>>>(a);
     } else {
         static bool attr = false;
         if (!attr) {
-            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, IDENT, false>,
+            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, IDENT, false, PK>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
             attr = true;
         }
-        k_fw_sweep<H, IDENT, false><<<blocks, kPT, lds, s>>>(a);
+        k_fw_sweep<H, IDENT, false, PK><<<blocks, kPT, lds, s>>>(a);
     }
 }
 
@@ -985,6 +1002,8 @@ void sweep_iteration(FwState& f, const SweepPlan& p, SweepArgs& a, int mode, int
         launch_sweep<2, true>(a, blocks, gap, s);
     else if (mode == 3)
         launch_sweep<3, false>(a, blocks, gap, s);
+    else if (p.packed)
+        launch_sweep<4, false, true>(a, blocks, gap, s);
     else
         launch_sweep<4, false>(a, blocks, gap, s);
     LDS_HIP(hipGetLastError());
@@ -1266,7 +1285,7 @@ void fw_splits(const Graph& g, int mode, int32_t* verts_host, uint64_t* num_host
     // a0 = D_0 / h; inc_i = D_i - D_{i-1} = incm (i+1) with incm = inc_1 / 2
     const uint64_t a0 = denom(mode, 0) / (uint64_t)H, incm = (denom(mode, 1) - denom(mode, 0)) / 2;
     if (mode == 2) {
-        k_splits<2><<<grid_for(ns, 256), 256, 0, s>>>(p.rp, p.rid, p.py, p.bitbase.p, p.nrows, ns, f.bits.p,
+        k_splits<2, false><<<grid_for(ns, 256), 256, 0, s>>>(p.rp, p.rid, p.py, p.bitbase.p, p.nrows, ns, f.bits.p,
                                                       p.total_words, f.iters, a0, incm, g.orig_of.p, v.p, a.p);
         const HeavyPlan& h = p.heavy;
         if (h.positions > 0)
@@ -1278,11 +1297,12 @@ void fw_splits(const Graph& g, int mode, int32_t* verts_host, uint64_t* num_host
                 p.rp, p.py, p.hub_pre.p, p.n_push, denom(mode, f.iters), a.p);
     }
     else if (mode == 3)
-        k_splits<3><<<grid_for(ns, 256), 256, 0, s>>>(p.rp, p.rid, p.py, p.bitbase.p, p.nrows, ns, f.bits.p,
+        k_splits<3, false><<<grid_for(ns, 256), 256, 0, s>>>(p.rp, p.rid, p.py, p.bitbase.p, p.nrows, ns, f.bits.p,
                                                       p.total_words, f.iters, a0, incm, g.orig_of.p, v.p, a.p);
     else
-        k_splits<4><<<grid_for(ns, 256), 256, 0, s>>>(p.rp, p.rid, p.py, p.bitbase.p, p.nrows, ns, f.bits.p,
-                                                      p.total_words, f.iters, a0, incm, g.orig_of.p, v.p, a.p);
+        (p.packed ? k_splits<4, true> : k_splits<4, false>)<<<grid_for(ns, 256), 256, 0, s>>>(
+            p.rp, p.rid, p.py, p.bitbase.p, p.nrows, ns, f.bits.p, p.total_words, f.iters, a0, incm, g.orig_of.p, v.p,
+            a.p);
     LDS_HIP(hipGetLastError());
     LDS_HIP(hipMemcpyAsync(verts_host, v.p, v.bytes(), hipMemcpyDeviceToHost, s));
     LDS_HIP(hipMemcpyAsync(num_host, a.p, a.bytes(), hipMemcpyDeviceToHost, s));

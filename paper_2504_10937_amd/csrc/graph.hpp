@@ -111,6 +111,17 @@ __host__ __device__ inline uint32_t word_slot(uint64_t d) { return (uint32_t)d; 
 __host__ __device__ inline int word_slots(uint64_t d) { return (int)((d >> 32) & 63) + 1; }
 __host__ __device__ inline int32_t word_row(uint64_t d) { return (int32_t)(d >> 38) - 1; }
 
+// A 4-clique slot in 8 bytes, the three other members' ids at bits 0, 21 and
+// 42, for plans whose ids fit 21 bits: the sweep's payload is a third smaller
+// and one 8-byte load a slot.
+struct PackedSlot {
+    static constexpr int kBits = 21;
+    static constexpr int64_t kMaxVertices = (int64_t)1 << kBits;
+    static __host__ __device__ inline int32_t id(uint64_t x, int q) {
+        return (int32_t)((x >> (kBits * q)) & ((1u << kBits) - 1));
+    }
+};
+
 struct SweepPlan {
     int h = 2;                  // pattern arity: 2 edges, 3 triangles
     int64_t nrows = 0;          // compact rows
@@ -118,6 +129,7 @@ struct SweepPlan {
     const int32_t* rid = nullptr;  // compact row -> internal vertex (nullptr: identity)
     const int64_t* rp = nullptr;   // nrows + 1 slot offsets
     const int32_t* py = nullptr;   // nslots * (h - 1) vertex ids (internal)
+    bool packed = false;           // 4-cliques: three ids in the 64 bits of a slot (PackedSlot)
     DBuf<int32_t> own_rid;         // storage when the plan owns rid / rp / py
     DBuf<int64_t> own_rp;
     DBuf<int32_t> own_py;

@@ -1196,6 +1196,7 @@ void view_plan(SweepPlan& d, const SweepPlan& p, hipStream_t s) {
     d.rid = p.rid;
     d.rp = p.rp;
     d.py = p.py;
+    d.packed = p.packed;
     d.own_rid.borrow(p.own_rid);
     d.own_rp.borrow(p.own_rp);
     d.own_py.borrow(p.own_py);

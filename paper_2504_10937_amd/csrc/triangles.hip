@@ -281,8 +281,9 @@ __global__ void k_inc_keys(const int32_t* pat, int64_t np, const int32_t* row_of
     for (int j = 0; j < H; ++j) keys[H * t + j] = ((uint64_t)row_of[pat[H * t + j]] << tb) | (uint64_t)t;
 }
 
-// slot s: the other H-1 members of its pattern, in pattern order
-template <int H>
+// slot s: the other H-1 members of its pattern, in pattern order, and for
+// triangles the pattern
+template <int H, bool PACKED>
 __global__ void k_inc_pay(const uint64_t* keys, int64_t ns, int tb, const int32_t* pat, const int32_t* rid,
                           int32_t* pay, int32_t* tos) {
     const int64_t s = (int64_t)blockIdx.x * kT + threadIdx.x;
@@ -290,12 +291,19 @@ __global__ void k_inc_pay(const uint64_t* keys, int64_t ns, int tb, const int32_
     const uint64_t k = keys[s];
     const int64_t t = (int64_t)(k & ((1ull << tb) - 1));
     const int32_t x = rid[k >> tb];
+    if (PACKED) {
+        const int4 y = reinterpret_cast<const int4*>(pat)[t];
+        const bool i0 = y.x == x, i1 = i0 || y.y == x, i2 = i1 || y.z == x;  // x found by then
+        const uint64_t a = (uint32_t)(i0 ? y.y : y.x), b = (uint32_t)(i1 ? y.z : y.y), c = (uint32_t)(i2 ? y.w : y.z);
+        reinterpret_cast<uint64_t*>(pay)[s] = a | (b << PackedSlot::kBits) | (c << (2 * PackedSlot::kBits));
+        return;
+    }
     int o = 0;
     for (int j = 0; j < H; ++j) {
         const int32_t y = pat[H * t + j];
         if (y != x) pay[(H - 1) * s + o++] = y;
     }
-    tos[s] = (int32_t)t;
+    if (H == 3) tos[s] = (int32_t)t;
 }
 
 __global__ void k_set_last(int64_t* rowptr, int64_t idx, const uint64_t* total) { rowptr[idx] = (int64_t)*total; }
@@ -379,7 +387,8 @@ void build_incidence_plan(Graph& g, const int32_t* pat, int64_t np, const int32_
     p.nslots = H * np;
     p.own_rid.alloc(nrows, s);
     p.own_rp.alloc(nrows + 1, s);
-    p.own_py.alloc((H - 1) * H * np, s);
+    p.packed = H == 4 && n <= PackedSlot::kMaxVertices;
+    p.own_py.alloc((p.packed ? 2 : H - 1) * H * np, s);
     DBuf<int32_t>& row_of = p.own_row_of;
     row_of.alloc(n, s);
     if (n) LDS_HIP(hipMemsetAsync(row_of.p, 0xff, n * sizeof(int32_t), s));  // -1: no pattern
@@ -414,9 +423,13 @@ void build_incidence_plan(Graph& g, const int32_t* pat, int64_t np, const int32_
         // the keys are made in pattern order and the sort is stable, so the
         // row bits alone order them
         radix_sort_u64(ik.p, nullptr, H * np, tb, tb + rb, it.p, nullptr, s);
-        p.own_tos.alloc(H * np, s);
-        k_inc_pay<H><<<grid_for(H * np, kT), kT, 0, s>>>(ik.p, H * np, tb, pat, p.own_rid.p, p.own_py.p,
-                                                       p.own_tos.p);
+        if (H == 3) p.own_tos.alloc(H * np, s);
+        if (p.packed)
+            k_inc_pay<H, H == 4><<<grid_for(H * np, kT), kT, 0, s>>>(ik.p, H * np, tb, pat, p.own_rid.p, p.own_py.p,
+                                                                   nullptr);
+        else
+            k_inc_pay<H, false><<<grid_for(H * np, kT), kT, 0, s>>>(ik.p, H * np, tb, pat, p.own_rid.p, p.own_py.p,
+                                                                  p.own_tos.p);
         LDS_HIP(hipGetLastError());
     }
     p.rid = p.own_rid.p;
