@@ -32,6 +32,7 @@
 #include "wave.hpp"
 
 #include <mutex>
+#include <type_traits>
 
 // Scratch of lds_frank_wolfe_noalloc, for callers that cannot allocate device
 // memory: the per-workgroup gap partial sums of every iteration, their
@@ -164,9 +165,6 @@ __device__ inline Slot<4, true> load_slot<4, true>(const int32_t* __restrict__ p
     return r;
 }
 
-#ifndef LDS_SWEEP_WORDS
-#define LDS_SWEEP_WORDS 8
-#endif
 #ifndef LDS_SWEEP_THREADS
 #define LDS_SWEEP_THREADS 1024
 #endif
@@ -176,7 +174,13 @@ __device__ inline Slot<4, true> load_slot<4, true>(const int32_t* __restrict__ p
 #ifndef LDS_SWEEP_WG_PER_CU
 #define LDS_SWEEP_WG_PER_CU 1
 #endif
-constexpr int kG = LDS_SWEEP_WORDS;         // 64-slot words of a chunk in flight per wave
+// 64-slot words of a chunk or piece in flight per wave.  A batch costs its
+// instructions whether its words are there or not, and a chunk of a small plan
+// has few: 4 words up to kWideSlots slots (24k slots 7.0 -> 5.8 us a sweep, 2.9M
+// 17.9 -> 17.2; triangles 84k 8.5 -> 7.8, 1.6M 16.2 -> 15.3), 8 above (4.8M slots
+// 32 us, 34 with 4; 206M 823 and 837; triangles 37M 213 and 218).
+constexpr int kWordsSmall = 4, kWordsLarge = 8;
+constexpr int64_t kWideSlots = (int64_t)1 << 22;
 constexpr int kPT = LDS_SWEEP_THREADS;      // threads of a persistent workgroup
 constexpr int kWaves = kPT / 64;
 constexpr int kCacheQ = LDS_SWEEP_CACHE;    // codes of the first (highest-degree) vertices staged in LDS
@@ -206,6 +210,56 @@ template <int H, int G, bool PK, class KU>
 __device__ inline void decide(const uint16_t* __restrict__ qc, int nc, const uint16_t* __restrict__ Q,
                               const uint64_t* __restrict__ K, const Slot<H, PK> (&sl)[G], const bool (&in)[G],
                               const uint16_t (&qu)[G], KU ku, bool (&win)[G]) {
+    // Triangles and 4-cliques, whose first member has the largest id: a batch
+    // with every code in LDS reads them all without masks and compares once
+    // with the smallest (the sweep of 195M clique slots, 20,000 hub rows among
+    // 41,000: 504 -> 404 us; half of its cycles went into the masked gathers,
+    // 51 vector instructions a word).  Members of a slot that is not lower than
+    // the smallest code have larger keys, so a tie is settled by all of them.
+    if (H > 2) {
+        uint32_t top = 0;
+#pragma unroll
+        for (int j = 0; j < G; ++j) top = max(top, sl[j].id(0));
+        if (__ballot(top >= (uint32_t)nc) == 0) {
+            uint16_t q[G][H - 1];
+#pragma unroll
+            for (int j = 0; j < G; ++j)
+#pragma unroll
+                for (int x = 0; x < H - 1; ++x) q[j][x] = qc[sl[j].id(x)];
+            bool tie[G], any = false;
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                uint32_t m = q[j][0];
+#pragma unroll
+                for (int x = 1; x < H - 1; ++x) m = min(m, (uint32_t)q[j][x]);
+                win[j] = in[j] && qu[j] <= m;
+                tie[j] = in[j] && qu[j] == m;
+                any = any || tie[j];
+            }
+            if (__ballot(any) == 0) return;
+            constexpr int S = G % 4 == 0 ? 4 : G % 3 == 0 ? 3 : G;
+#pragma unroll
+            for (int j0 = 0; j0 < G; j0 += S) {
+                uint64_t k0[S], kv[S][H - 1];
+#pragma unroll
+                for (int j = 0; j < S; ++j) {
+                    k0[j] = 0;
+#pragma unroll
+                    for (int x = 0; x < H - 1; ++x) kv[j][x] = ~0ull;
+                    if (tie[j0 + j]) {
+                        k0[j] = ku(j0 + j);
+#pragma unroll
+                        for (int x = 0; x < H - 1; ++x) kv[j][x] = K[sl[j0 + j].id(x)];
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < S; ++j)
+#pragma unroll
+                    for (int x = 0; x < H - 1; ++x) win[j0 + j] = win[j0 + j] && k0[j] < kv[j][x];
+            }
+            return;
+        }
+    }
     uint32_t tied[G];
 #pragma unroll
     for (int j = 0; j < G; ++j) {
@@ -223,7 +277,7 @@ __device__ inline void decide(const uint16_t* __restrict__ qc, int nc, const uin
             win[j] = win[j] && qu[j] <= qv[j];
         }
     }
-    constexpr int S = H == 2 ? G : (G >= 4 ? 4 : G);  // slots whose keys are in flight together
+    constexpr int S = H == 2 ? G : (G % 4 == 0 ? 4 : G % 3 == 0 ? 3 : G);  // slots whose keys are in flight together
 #pragma unroll
     for (int j0 = 0; j0 < G; j0 += S) {
         uint64_t k0[S], kv[S][H - 1];
@@ -386,7 +440,7 @@ __device__ inline void heavy_parts(const SweepArgs& a, uint8_t* dyn, int64_t* sg
 // into LDS; those vertices take most of the gathers of a power-law graph.
 // It then processes hub rows (whole workgroup each) and chunks (one wave
 // each), both strided over the grid.
-template <int H, bool IDENT, bool GAP, bool PK>
+template <int H, bool IDENT, bool GAP, bool PK, int kG>
 __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
     extern __shared__ __align__(16) uint16_t qc[];
     __shared__ uint64_t red[kWaves][4];
@@ -426,7 +480,7 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
 #pragma unroll
         for (int j = 0; j < kG; ++j) {
             const int off = (t0 + j) * 64 + lane;
-            if (off < d.nsl) sl[j] = load_slot<H, PK>(a.py + d.s0 * PW, off);
+            if (H > 2 || off < d.nsl) sl[j] = load_slot<H, PK>(a.py + d.s0 * PW, H > 2 ? min(off, d.nsl - 1) : off);
         }
     };
     auto load_chunk = [&]() {
@@ -479,25 +533,24 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
             uint32_t cnt = 0;
             for (int base = 0; base < len; base += 64 * kG) {
                 Slot<H, PK> sl[kG];
-                bool in[kG];
-    #pragma unroll
+                bool in[kG], win[kG];
+                uint16_t qu[kG];
+#pragma unroll
                 for (int j = 0; j < kG; ++j) {
                     const int off = base + 64 * j + lane;
                     in[j] = off < len;
-                    if (in[j]) sl[j] = load_slot<H, PK>(pyc, off);
+                    if (H > 2 || in[j]) sl[j] = load_slot<H, PK>(pyc, H > 2 ? min(off, len - 1) : off);
+                    qu[j] = Qu;
                 }
-                uint16_t qu[kG];
-                bool win[kG];
-    #pragma unroll
-                for (int j = 0; j < kG; ++j) qu[j] = Qu;
                 decide<H, kG, PK>(qc, nc, a.Qin, a.Kin, sl, in, qu, [&](int) { return Ku; }, win);
-    #pragma unroll
+                uint64_t mine = 0;
+#pragma unroll
                 for (int j = 0; j < kG; ++j) {
                     const uint64_t W = __ballot(win[j]);
-                    const int wb = base + 64 * j;  // first slot of this word
-                    if (lane == 0 && wb < len) __builtin_nontemporal_store(W, bw + wb / 64);
+                    if (lane == j) mine = W;
                     cnt += (uint32_t)__popcll(W);
                 }
+                if (lane < kG && base + 64 * lane < len) __builtin_nontemporal_store(mine, bw + base / 64 + lane);
             }
             if (lane == 0 && Hp > 0) {
                 atomicAdd(a.hub_ctr + r, (unsigned long long)cnt);
@@ -882,7 +935,7 @@ __global__ void k_splits_heavy(const uint32_t* csr, const uint32_t* pay, int64_t
 
 uint64_t denom(int mode, int64_t i) { return fw_denom(mode, i); }
 
-template <int H, bool IDENT, bool PK = false>
+template <int H, bool IDENT, bool PK, int W>
 void launch_sweep(const SweepArgs& a, unsigned blocks, bool gap, hipStream_t s) {
     const bool heavy = H == 2 && IDENT && a.n_parts > 0;
     const size_t push_lds = a.n_push > 0 ? (size_t)((a.ncache + 1) & ~1) * 2 + (size_t)a.pstride * 4 : 0;
@@ -891,19 +944,19 @@ void launch_sweep(const SweepArgs& a, unsigned blocks, bool gap, hipStream_t s) 
     if (gap) {
         static bool attr = false;
         if (!attr) {
-            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, IDENT, true, PK>,
+            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, IDENT, true, PK, W>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
             attr = true;
         }
-        k_fw_sweep<H, IDENT, true, PK><<<blocks, kPT, lds, s>>>(a);
+        k_fw_sweep<H, IDENT, true, PK, W><<<blocks, kPT, lds, s>>>(a);
     } else {
         static bool attr = false;
         if (!attr) {
-            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, IDENT, false, PK>,
+            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, IDENT, false, PK, W>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
             attr = true;
         }
-        k_fw_sweep<H, IDENT, false, PK><<<blocks, kPT, lds, s>>>(a);
+        k_fw_sweep<H, IDENT, false, PK, W><<<blocks, kPT, lds, s>>>(a);
     }
 }
 
@@ -998,14 +1051,21 @@ void sweep_iteration(FwState& f, const SweepPlan& p, SweepArgs& a, int mode, int
     a.bits = f.bits.p + (size_t)(i - 1) * p.total_words;
     a.inc = denom(mode, i) - denom(mode, i - 1);
     a.partial = partial;
-    if (mode == 2)
-        launch_sweep<2, true>(a, blocks, gap, s);
-    else if (mode == 3)
-        launch_sweep<3, false>(a, blocks, gap, s);
-    else if (p.packed)
-        launch_sweep<4, false, true>(a, blocks, gap, s);
+    auto launch = [&](auto words) {
+        constexpr int W = decltype(words)::value;
+        if (mode == 2)
+            launch_sweep<2, true, false, W>(a, blocks, gap, s);
+        else if (mode == 3)
+            launch_sweep<3, false, false, W>(a, blocks, gap, s);
+        else if (p.packed)
+            launch_sweep<4, false, true, W>(a, blocks, gap, s);
+        else
+            launch_sweep<4, false, false, kWordsLarge>(a, blocks, gap, s);
+    };
+    if (p.nslots < kWideSlots)
+        launch(std::integral_constant<int, kWordsSmall>{});
     else
-        launch_sweep<4, false>(a, blocks, gap, s);
+        launch(std::integral_constant<int, kWordsLarge>{});
     LDS_HIP(hipGetLastError());
     if (a.n_push > 0) {
         const unsigned pg = push_grid(p);

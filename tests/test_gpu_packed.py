@@ -1,4 +1,4 @@
-"""4-clique slots of three 21-bit
+"""Batches of triangle and 4-clique slots, and 4-clique slots of three 21-bit
 ids (plans up to 2^21 vertices) and of three 32-bit ids (above): for these,
 small components of cliques at the far end of the internal ids, next to a
 clique-free graph of larger degree that fills the ids below them.  Their
@@ -9,6 +9,7 @@ import pytest
 import torch  # noqa: F401  (its HIP runtime first, as a program that shares tensors with the library loads it)
 
 import paper_2504_10937_amd as lds
+import synth
 from gpu_helpers import announce, check_fw
 
 pytestmark = pytest.mark.gpu
@@ -49,3 +50,29 @@ def test_packed_edge(n):
     bv, bn = lds.lds_splits(g, 4)
     np.testing.assert_array_equal(bv, sv + f)
     np.testing.assert_array_equal(bn, sn)
+
+
+def _dense(k, seed):
+    """K_k without a few edges, some of its vertices tied to a sparse tail"""
+    rng = np.random.default_rng(seed)
+    u, v = np.triu_indices(k, 1)
+    keep = rng.random(len(u)) > 0.02
+    n, s, d = synth.holme_kim(2_000, 6, 0.8, seed=seed)
+    a, b = rng.integers(0, k, 500), rng.integers(k, k + n, 500)
+    return k + n, np.concatenate([u[keep], s + k, a]).astype(np.int32), np.concatenate([v[keep], d + k, b]).astype(np.int32)
+
+
+@pytest.mark.parametrize("mode,k", [(3, 150), (3, 230), (4, 40), (4, 82)])
+def test_batches_of_words(mode, k):
+    """fewer and more than 2^22 slots (four and eight words a batch), hub
+    pieces and chunks, every code in LDS"""
+    n, s, d = _dense(k, seed=k)
+    announce("batches of words", mode, k)
+    g = check_fw(n, s, d, mode, 7)[0]
+    assert (lds.lds_sweep_info(g, mode)["slots"] >= 1 << 22) == (k in (230, 82))
+
+
+def test_hot_and_cold_codes():
+    """more vertices than codes in LDS: batches of either kind and mixed ones"""
+    announce("hot and cold codes")
+    check_fw(*synth.holme_kim(90_000, 6, 0.7, seed=5), 3, 9)
