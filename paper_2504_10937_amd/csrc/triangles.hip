@@ -309,46 +309,55 @@ __global__ void k_inc_pay(const uint64_t* keys, int64_t ns, int tb, const int32_
 __global__ void k_set_last(int64_t* rowptr, int64_t idx, const uint64_t* total) { rowptr[idx] = (int64_t)*total; }
 
 // 4-cliques: a clique with internal ids a > b > c > d is found exactly once,
-// from its triangle (a, b, c), as the element d of N+(a) ∩ N+(b) ∩ N+(c)
-// (all of N+(c) lies below c).  One thread per triangle walks the shortest
-// of the three out-lists cut at c and probes the other two by binary search
-// with advancing lower bounds; a count pass, a scan and a write pass give
-// the order (triangle order, d ascending).
+// from its triangle (a, b, c): (a, b, d) is a triangle too, and the triangles
+// are in the order of (a, b, c), so the candidates d are the third members of
+// the triangles of (a, b) before this one, and d is confirmed by one search,
+// in N+(c).  One thread per triangle walks them downwards, galloping down
+// N+(c) as d falls.  When they are many against N+(c), it walks N+(c) instead
+// and searches N+(a) and N+(b).  A count pass, a scan and a write pass (from
+// each triangle's last place down) give the order: triangle order, d
+// ascending.  Bound: the chain of dependent reads of a search.  On 49M cliques
+// the passes take 1.26 and 1.83 ms; walking the shortest of the three
+// out-lists and searching the other two took 2.43 and 3.15.
 template <bool WRITE>
 __global__ void k_clique_tris(const int64_t* rp, const int32_t* col, const int32_t* tri, int64_t T, uint32_t* cnt,
                               const uint64_t* off, int32_t* q4) {
     const int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (t >= T) return;
-    const int32_t x[3] = {tri[3 * t], tri[3 * t + 1], tri[3 * t + 2]};  // a > b > c
-    const int32_t c = x[2];
-    int64_t lo[3], hi[3];
-    for (int j = 0; j < 3; ++j) {
-        lo[j] = rp[x[j]];
-        hi[j] = lower_bound_i32(col, rp[x[j]], rp[x[j] + 1], c);  // neighbours below c
-    }
-    int sh = 0;
-    for (int j = 1; j < 3; ++j)
-        if (hi[j] - lo[j] < hi[sh] - lo[sh]) sh = j;
-    const int o1 = sh == 0 ? 1 : 0, o2 = sh == 2 ? 1 : 2;
-    int64_t q1 = lo[o1], q2 = lo[o2];
-    uint64_t o = WRITE ? off[t] : 0;
+    if (WRITE && cnt[t] == 0) return;
+    const int32_t a = tri[3 * t], b = tri[3 * t + 1], c = tri[3 * t + 2];  // a > b > c
+    const int64_t lo = rp[c];
+    int64_t end = lower_bound_i32(col, lo, rp[c + 1], c);  // N+(c) is [lo, end)
+    const int64_t limit = 2 * (end - lo) + 16;
+    uint64_t o = WRITE ? off[t] + cnt[t] : 0;
     uint32_t k = 0;
-    for (int64_t i = lo[sh]; i < hi[sh]; ++i) {
-        const int32_t d = col[i];
-        q1 = lower_bound_i32(col, q1, hi[o1], d);
-        if (q1 >= hi[o1]) break;
-        if (col[q1] != d) continue;
-        q2 = lower_bound_i32(col, q2, hi[o2], d);
-        if (q2 >= hi[o2]) break;
-        if (col[q2] != d) continue;
-        if (WRITE) {
-            q4[4 * o + 0] = x[0];
-            q4[4 * o + 1] = x[1];
-            q4[4 * o + 2] = x[2];
-            q4[4 * o + 3] = d;
-            ++o;
-        }
+    auto found = [&](int32_t d) {
+        if (WRITE) reinterpret_cast<int4*>(q4)[--o] = make_int4(a, b, c, d);
         ++k;
+    };
+    int64_t p = end;  // the members of N+(c) from p on are above every candidate left
+    int64_t i = t - 1;
+    for (; i >= 0 && p > lo && t - i <= limit; --i) {
+        if (tri[3 * i] != a || tri[3 * i + 1] != b) break;
+        const int32_t d = tri[3 * i + 2];
+        // the first member >= d lies in (p - step, p]
+        int64_t step = 1;
+        while (p - step >= lo && col[p - step] >= d) step <<= 1;
+        p = lower_bound_i32(col, max(lo, p - step), p - (step >> 1), d);
+        if (p < end && col[p] == d) found(d);
+    }
+    if (i >= 0 && p > lo && t - i > limit) {  // the rest of N+(c), downwards
+        int64_t pa = rp[a], ea = lower_bound_i32(col, pa, rp[a + 1], c);
+        int64_t pb = rp[b], eb = lower_bound_i32(col, pb, rp[b + 1], c);
+        while (--p >= lo) {
+            const int32_t d = col[p];
+            ea = lower_bound_i32(col, pa, ea, d + 1);  // N(a) up to d
+            if (ea == pa) break;
+            if (col[ea - 1] != d) continue;
+            eb = lower_bound_i32(col, pb, eb, d + 1);
+            if (eb == pb) break;
+            if (col[eb - 1] == d) found(d);
+        }
     }
     if (!WRITE) cnt[t] = k;
 }
@@ -545,10 +554,9 @@ void list_cliques4(Graph& g, hipStream_t s) {
         LDS_HIP(hipGetLastError());
         exclusive_scan_u32_to_u64(cnt.p, off.p, T, tot.p, s);
         Q = (int64_t)d2h(tot.p, s);
-        cnt.release();
         g.q4.alloc(4 * Q, s);
         if (Q > 0) {
-            k_clique_tris<true><<<grid_for(T, kT), kT, 0, s>>>(g.rowptr.p, g.col.p, g.tri.p, T, nullptr, off.p, g.q4.p);
+            k_clique_tris<true><<<grid_for(T, kT), kT, 0, s>>>(g.rowptr.p, g.col.p, g.tri.p, T, cnt.p, off.p, g.q4.p);
             LDS_HIP(hipGetLastError());
             count_members(g.q4.p, 4 * Q, 1, n, g.qcount.p, s);
         }

@@ -89,3 +89,25 @@ def test_cliques(name):
     assert Q == want
     np.testing.assert_array_equal(cnt, per)
     np.testing.assert_array_equal(np.bincount(q.ravel(), minlength=n), per)
+
+
+@pytest.mark.parametrize("joined", [1, 3])
+@pytest.mark.parametrize("hubs", [5, 16, 17, 21, 22, 90])
+def test_clique_candidates(hubs, joined):
+    """a triangle (a, b, c) whose edge (a, b) has few or many further
+    triangles, against the few hubs that c is joined to"""
+    announce("clique candidates", hubs, joined)
+    a, b, c, leaf = 0, 1, 2, 3 + hubs
+    e = [(a, b), (a, c), (b, c)]
+    for h in range(3, 3 + hubs):
+        e += [(a, h), (b, h)]
+        e += [(h, leaf + i) for i in range(250)]
+        leaf += 250
+    e += [(c, 3 + h) for h in range(0, hubs, max(1, hubs // joined))][:joined]
+    e += [(c, leaf + i) for i in range(150)]
+    u, v = np.array(e, np.int32).T
+    n = leaf + 150
+    Q, q, _ = lds.lds_cliques4(lds.lds_create_graph(n, u, v), want_list=True, want_counts=True)
+    want, _ = oracle.cliques4(oracle.Graph(n, u, v))
+    assert Q == len(want) == joined
+    np.testing.assert_array_equal(q, want)
