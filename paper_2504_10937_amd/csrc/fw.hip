@@ -48,6 +48,16 @@ namespace {
 
 typedef unsigned __int128 u128;
 
+// the windows of an iteration's 16-bit load codes (see qcode), in one register:
+// bases of the loads read and written, mantissa bits
+struct Codes {
+    uint32_t x;
+    __host__ __device__ Codes(int in = 0, int out = 0, int mant = 11) : x((uint32_t)(in | (out << 8) | (mant << 16))) {}
+    __device__ inline int in() const { return (int)(x & 255u); }
+    __device__ inline int out() const { return (int)((x >> 8) & 255u); }
+    __device__ inline int mant() const { return (int)(x >> 16); }
+};
+
 struct SweepArgs {
     const int32_t* rid;
     const int64_t* rp;
@@ -67,6 +77,7 @@ struct SweepArgs {
     uint64_t* Kout;
     const uint16_t* Qin;  // 16-bit codes of the loads (see qcode)
     uint16_t* Qout;
+    Codes codes;         // of Qin (D_(i-1)) and Qout (D_i)
     uint64_t* bits;      // this iteration's decision words
     uint64_t inc;
     int B;
@@ -104,17 +115,25 @@ __device__ inline uint64_t readlane64(uint64_t v, int lane) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// 16-bit monotone code of a load numerator: a pseudo-float with the 6-bit
-// position of the leading one and the next 10 bits (0 for A = 0).  A < A'
-// implies qcode(A) <= qcode(A'), so different codes decide a comparison of
-// packed keys exactly and equal codes fall back to the 64-bit keys.  The code
-// array is a quarter of the key array, so the gathered working set stays in
-// the L2 caches far more often.
-__device__ inline uint16_t qcode(uint64_t A) {
-    if (A == 0) return 0;
-    const int e = 63 - __clzll(A);
-    const uint64_t mant = (e >= 10) ? (A >> (e - 10)) : (A << (10 - e));
-    return (uint16_t)(((uint32_t)e << 10) | (uint32_t)(mant & 0x3FFu));
+// 16-bit monotone code of a load numerator: a pseudo-float of `mant` mantissa
+// bits whose exponents count from `base`, the position of the leading one of
+// D_i / 2, so the code is one of the load r = A / D_i and the same window of
+// loads, 2^(16 - mant) octaves from 1/2, serves every iteration.  Numerators
+// below it have code 0, those past it 65535.  A < A' implies qcode(A) <=
+// qcode(A'), so different codes decide a comparison of packed keys exactly and
+// equal codes fall back to the 64-bit keys.  The code array is a quarter of
+// the key array, so the gathered working set stays in the L2 caches far more
+// often.  11 mantissa bits cover any load (2^31); 12 are taken where no vertex
+// has 2^16 patterns.  A tie costs its batch a wait for the keys, and each bit
+// halves them: 195M clique slots took 404 us with 10 bits and any exponent, 374
+// with this code and 361 when ties were not looked up; 206M edge slots 822,
+// 795 and 773.
+__device__ inline uint16_t qcode(uint64_t A, int base, int mant) {
+    A |= 1;  // zero: below any window
+    const int z = __clzll(A);
+    const uint32_t top = (uint32_t)((A << z) >> 32) >> (31 - mant);  // leading one and mantissa
+    const int c = ((62 - z - base) << mant) + (int)top;
+    return (uint16_t)min(max(c, 0), 65535);
 }
 
 // the h-1 other vertices of the pattern stored at a slot; the slot arrays
@@ -440,15 +459,20 @@ __device__ inline void heavy_parts(const SweepArgs& a, uint8_t* dyn, int64_t* sg
 // into LDS; those vertices take most of the gathers of a power-law graph.
 // It then processes hub rows (whole workgroup each) and chunks (one wave
 // each), both strided over the grid.
-template <int H, bool IDENT, bool GAP, bool PK, int kG>
+template <int H, bool HEAVY, bool GAP, bool PK, int kG>
 __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
+    constexpr bool IDENT = H == 2;  // compact row = vertex
     extern __shared__ __align__(16) uint16_t qc[];
     __shared__ uint64_t red[kWaves][4];
     __shared__ uint64_t words[kWaves][32];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nc = a.ncache;
+    // in a vector register: the scalar ones are full, and another of them cost a
+    // plan of 3M slots 17.2 -> 18.9 us in spills
+    Codes codes = a.codes;
+    asm("" : "+v"(codes.x));
     // the 2D part first (its LDS layout), then the hot codes for the rest
-    heavy_parts<H == 2 && IDENT>(a, reinterpret_cast<uint8_t*>(qc), reinterpret_cast<int64_t*>(&words[0][0]));
+    heavy_parts<HEAVY>(a, reinterpret_cast<uint8_t*>(qc), reinterpret_cast<int64_t*>(&words[0][0]));
     // Triangles: the wave's first chunk is read before the codes are staged, so
     // that its chain of reads (descriptor; payload, row vertices, keys) runs
     // behind the staging, and the hub pieces come last (24k slots 7.8 -> 6.9 us
@@ -504,7 +528,7 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
         for (int i = (n16 << 3) + threadIdx.x; i < nc; i += kPT) qc[i] = a.Qin[i];
     }
     // hub push: the hub rows' win counters of this workgroup, after the codes
-    const int Hp = (H == 2 && IDENT) ? (int)a.n_push : 0;
+    const int Hp = H == 2 && !HEAVY ? (int)a.n_push : 0;
     uint32_t* hcnt = reinterpret_cast<uint32_t*>(qc + ((nc + 1) & ~1));
     for (int i = threadIdx.x; i < (Hp + 1) / 2; i += kPT) hcnt[i] = 0u;
     __syncthreads();
@@ -528,7 +552,7 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
             const int len = (int)min((Hp > 0 ? rs + a.hub_pre[r] : re) - s0, (int64_t)a.piece);
             const int32_t* __restrict__ pyc = a.py + s0 * PW;
             const uint64_t Ku = a.Kin[u];
-            const uint16_t Qu = qcode(Ku >> a.B);
+            const uint16_t Qu = qcode(Ku >> a.B, codes.in(), codes.mant());
             uint64_t* bw = a.bits + a.chunk_words + a.hwo[r] + (s0 - rs) / 64;
             uint32_t cnt = 0;
             for (int base = 0; base < len; base += 64 * kG) {
@@ -561,7 +585,7 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
                     const uint64_t tot = (old & ((1ull << 40) - 1)) + cnt;
                     const uint64_t Kn = Ku + ((tot * a.inc) << a.B);
                     a.Kout[u] = Kn;
-                    a.Qout[u] = qcode(Kn >> a.B);
+                    a.Qout[u] = qcode(Kn >> a.B, codes.out(), codes.mant());
                     if (GAP) {
                         const uint64_t A = Ku >> a.B;
                         sq += (u128)A * A;
@@ -593,7 +617,7 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
         const int64_t r0 = d.r0, s0 = d.s0, w0 = d.w0;
         const int nsl = d.nsl, nw = (nsl + 63) >> 6;  // <= 32: a chunk spans < 2048 slots
         const uint64_t le = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
-        const int pq = (int)qcode(pk >> a.B);
+        const int pq = (int)qcode(pk >> a.B, codes.in(), codes.mant());
         const bool small = nrows <= 64;
         int32_t rowrel = -1;  // chunk-relative row of the slot before the current word
         uint64_t mybits = 0;
@@ -664,7 +688,7 @@ __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
                 }
                 const uint64_t Kn = Ku + (((uint64_t)cnt * a.inc) << a.B);
                 a.Kout[u] = Kn;
-                a.Qout[u] = qcode(Kn >> a.B);
+                a.Qout[u] = qcode(Kn >> a.B, codes.out(), codes.mant());
                 if (GAP) {
                     const uint64_t A = Ku >> a.B;
                     sq += (u128)A * A;
@@ -754,7 +778,7 @@ template <bool GAP>
 __global__ __launch_bounds__(256) void k_push_finish(unsigned long long* hub_ctr, const uint32_t* push_part,
                                                      int64_t pstride, int nblocks, int64_t n_push,
                                                      const uint64_t* Kin, uint64_t* Kout, uint16_t* Qout,
-                                                     uint64_t inc, int B, uint64_t* partial) {
+                                                     uint64_t inc, int B, Codes codes, uint64_t* partial) {
     __shared__ uint64_t ps[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t r = (int64_t)blockIdx.x * 64 + lane;
@@ -775,7 +799,7 @@ __global__ __launch_bounds__(256) void k_push_finish(unsigned long long* hub_ctr
         const uint64_t Ku = Kin[r];
         const uint64_t Kn = Ku + ((tot * inc) << B);
         Kout[r] = Kn;
-        Qout[r] = qcode(Kn >> B);
+        Qout[r] = qcode(Kn >> B, codes.out(), codes.mant());
         if (GAP) {
             const uint64_t A = Ku >> B;
             sq = (u128)A * A;
@@ -802,7 +826,7 @@ template <bool GAP>
 __global__ __launch_bounds__(256) void k_heavy_finish(const uint32_t* part_cnt, const int32_t* blk_part,
                                                       const int32_t* row_blk, const int64_t* blk_row, int R,
                                                       int64_t n_heavy, const uint64_t* Kin, uint64_t* Kout,
-                                                      uint16_t* Qout, uint64_t inc, int B, uint64_t* partial) {
+                                                      uint16_t* Qout, uint64_t inc, int B, Codes codes, uint64_t* partial) {
     __shared__ uint64_t red[4][4];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     u128 sq = 0, mn = 0;
@@ -822,7 +846,7 @@ __global__ __launch_bounds__(256) void k_heavy_finish(const uint32_t* part_cnt, 
         const uint64_t Ku = Kin[r];
         const uint64_t Kn = Ku + ((tot * inc) << B);
         Kout[r] = Kn;
-        Qout[r] = qcode(Kn >> B);
+        Qout[r] = qcode(Kn >> B, codes.out(), codes.mant());
         if (GAP) {
             const uint64_t A = Ku >> B;
             sq += (u128)A * A;
@@ -858,7 +882,7 @@ __global__ __launch_bounds__(256) void k_heavy_finish(const uint32_t* part_cnt, 
 // r0 = t_u/3 with D0 = 6) or q_u (4-cliques, r0 = q_u/4 with D0 = 4), packed
 // with the original-id code
 __global__ void k_init_keys(const int32_t* count, int mult, const int32_t* orig_of, int64_t n, int B,
-                            uint64_t* K0, uint64_t* K1, uint16_t* Q0, uint16_t* Q1) {
+                            uint64_t* K0, uint64_t* K1, Codes codes, uint16_t* Q0, uint16_t* Q1) {
     const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (u >= n) return;
     const uint64_t idm = (1ull << B) - 1ull;
@@ -866,7 +890,7 @@ __global__ void k_init_keys(const int32_t* count, int mult, const int32_t* orig_
     const uint64_t k = (A << B) | (idm - (uint64_t)orig_of[u]);
     K0[u] = k;
     K1[u] = k;
-    Q0[u] = Q1[u] = qcode(A);
+    Q0[u] = Q1[u] = qcode(A, codes.in(), codes.mant());
 }
 
 __global__ void k_loads(const uint64_t* K, const int32_t* orig_of, int64_t n, int B, double D, float* r32,
@@ -935,28 +959,34 @@ __global__ void k_splits_heavy(const uint32_t* csr, const uint32_t* pay, int64_t
 
 uint64_t denom(int mode, int64_t i) { return fw_denom(mode, i); }
 
-template <int H, bool IDENT, bool PK, int W>
+// the codes of iteration i's sweep (i = 0: of the initial loads)
+Codes codes_of(const Graph& g, int mode, int64_t i) {
+    const int64_t most = mode == 2 ? g.max_deg : mode == 3 ? g.t_max : g.q_max;
+    auto base = [&](int64_t k) { return 62 - __builtin_clzll(denom(mode, k)); };
+    return Codes(base(i > 0 ? i - 1 : 0), base(i), most < (int64_t)1 << 16 ? 12 : 11);
+}
+
+template <int H, bool HEAVY, bool PK, int W>
 void launch_sweep(const SweepArgs& a, unsigned blocks, bool gap, hipStream_t s) {
-    const bool heavy = H == 2 && IDENT && a.n_parts > 0;
     const size_t push_lds = a.n_push > 0 ? (size_t)((a.ncache + 1) & ~1) * 2 + (size_t)a.pstride * 4 : 0;
-    const size_t lds = std::max(std::max((size_t)a.ncache * sizeof(uint16_t), push_lds), heavy ? kHeavyLds : (size_t)0);
-    const int max_lds = (int)std::max((size_t)kCacheQ * 2 + 16, (H == 2 && IDENT) ? kHeavyLds : (size_t)0);
+    const size_t lds = std::max(std::max((size_t)a.ncache * sizeof(uint16_t), push_lds), HEAVY ? kHeavyLds : (size_t)0);
+    const int max_lds = (int)std::max((size_t)kCacheQ * 2 + 16, HEAVY ? kHeavyLds : (size_t)0);
     if (gap) {
         static bool attr = false;
         if (!attr) {
-            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, IDENT, true, PK, W>,
+            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, HEAVY, true, PK, W>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
             attr = true;
         }
-        k_fw_sweep<H, IDENT, true, PK, W><<<blocks, kPT, lds, s>>>(a);
+        k_fw_sweep<H, HEAVY, true, PK, W><<<blocks, kPT, lds, s>>>(a);
     } else {
         static bool attr = false;
         if (!attr) {
-            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, IDENT, false, PK, W>,
+            LDS_HIP(hipFuncSetAttribute((const void*)k_fw_sweep<H, HEAVY, false, PK, W>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, max_lds));
             attr = true;
         }
-        k_fw_sweep<H, IDENT, false, PK, W><<<blocks, kPT, lds, s>>>(a);
+        k_fw_sweep<H, HEAVY, false, PK, W><<<blocks, kPT, lds, s>>>(a);
     }
 }
 
@@ -1041,7 +1071,7 @@ void fill_sweep_args(const Graph& g, const SweepPlan& p, SweepArgs& a) {
 
 // iteration i: the sweep, then the heavy rows' keys; partial = this
 // iteration's gap slice (sweep workgroups, then finishing workgroups) or null
-void sweep_iteration(FwState& f, const SweepPlan& p, SweepArgs& a, int mode, int i, unsigned blocks,
+void sweep_iteration(const Graph& g, FwState& f, const SweepPlan& p, SweepArgs& a, int mode, int i, unsigned blocks,
                      uint64_t* partial, hipStream_t s) {
     const bool gap = partial != nullptr;
     a.Kin = f.K[f.cur].p;
@@ -1050,11 +1080,12 @@ void sweep_iteration(FwState& f, const SweepPlan& p, SweepArgs& a, int mode, int
     a.Qout = f.Q[f.cur ^ 1].p;
     a.bits = f.bits.p + (size_t)(i - 1) * p.total_words;
     a.inc = denom(mode, i) - denom(mode, i - 1);
+    a.codes = codes_of(g, mode, i);
     a.partial = partial;
     auto launch = [&](auto words) {
         constexpr int W = decltype(words)::value;
         if (mode == 2)
-            launch_sweep<2, true, false, W>(a, blocks, gap, s);
+            launch_sweep<2, false, false, W>(a, blocks, gap, s);
         else if (mode == 3)
             launch_sweep<3, false, false, W>(a, blocks, gap, s);
         else if (p.packed)
@@ -1062,7 +1093,9 @@ void sweep_iteration(FwState& f, const SweepPlan& p, SweepArgs& a, int mode, int
         else
             launch_sweep<4, false, false, kWordsLarge>(a, blocks, gap, s);
     };
-    if (p.nslots < kWideSlots)
+    if (a.n_parts > 0)
+        launch_sweep<2, true, false, kWordsLarge>(a, blocks, gap, s);
+    else if (p.nslots < kWideSlots)
         launch(std::integral_constant<int, kWordsSmall>{});
     else
         launch(std::integral_constant<int, kWordsLarge>{});
@@ -1071,10 +1104,10 @@ void sweep_iteration(FwState& f, const SweepPlan& p, SweepArgs& a, int mode, int
         const unsigned pg = push_grid(p);
         if (gap)
             k_push_finish<true><<<pg, 256, 0, s>>>(a.hub_ctr, a.push_part, a.pstride, (int)blocks, a.n_push, a.Kin,
-                                                   a.Kout, a.Qout, a.inc, a.B, partial + (size_t)blocks * 4);
+                                                   a.Kout, a.Qout, a.inc, a.B, a.codes, partial + (size_t)blocks * 4);
         else
             k_push_finish<false><<<pg, 256, 0, s>>>(a.hub_ctr, a.push_part, a.pstride, (int)blocks, a.n_push,
-                                                    a.Kin, a.Kout, a.Qout, a.inc, a.B, nullptr);
+                                                    a.Kin, a.Kout, a.Qout, a.inc, a.B, a.codes, nullptr);
         LDS_HIP(hipGetLastError());
     }
     const unsigned fb = finish_grid(p);
@@ -1083,10 +1116,10 @@ void sweep_iteration(FwState& f, const SweepPlan& p, SweepArgs& a, int mode, int
         uint64_t* fp = gap ? partial + (size_t)blocks * 4 : nullptr;
         if (gap)
             k_heavy_finish<true><<<fb, 256, 0, s>>>(h.part_cnt.p, h.blk_part.p, h.row_blk.p, h.blk_row.p, h.R,
-                                                    h.n_heavy, a.Kin, a.Kout, a.Qout, a.inc, a.B, fp);
+                                                    h.n_heavy, a.Kin, a.Kout, a.Qout, a.inc, a.B, a.codes, fp);
         else
             k_heavy_finish<false><<<fb, 256, 0, s>>>(h.part_cnt.p, h.blk_part.p, h.row_blk.p, h.blk_row.p, h.R,
-                                                     h.n_heavy, a.Kin, a.Kout, a.Qout, a.inc, a.B, fp);
+                                                     h.n_heavy, a.Kin, a.Kout, a.Qout, a.inc, a.B, a.codes, fp);
         LDS_HIP(hipGetLastError());
     }
     f.cur ^= 1;
@@ -1153,6 +1186,7 @@ void fw_run(Graph& g, int mode, int iters, bool want_gap, hipStream_t s) {
     if (n > 0 && !one) {
         const int32_t* cnt = (mode == 2) ? g.deg.p : (mode == 3 ? g.tcount.p : g.qcount.p);
         k_init_keys<<<grid_for(n, 256), 256, 0, s>>>(cnt, mode == 3 ? 2 : 1, g.orig_of.p, n, B, f.K[0].p, f.K[1].p,
+                                                    codes_of(g, mode, 0),
                                                     f.Q[0].p, f.Q[1].p);
         LDS_HIP(hipGetLastError());
     }
@@ -1177,7 +1211,7 @@ void fw_run(Graph& g, int mode, int iters, bool want_gap, hipStream_t s) {
         f.launches = iters;
     }
     for (int i = 1; i <= iters && blocks > 0 && p.nrows > 0 && !one; ++i) {
-        sweep_iteration(f, p, a, mode, i, blocks, want_gap ? f.partial.p + (size_t)(i - 1) * gblocks * 4 : nullptr,
+        sweep_iteration(g, f, p, a, mode, i, blocks, want_gap ? f.partial.p + (size_t)(i - 1) * gblocks * 4 : nullptr,
                         s);
         ++f.launches;
     }
@@ -1274,6 +1308,7 @@ void fw_run_noalloc(Graph& g, int mode, int iters, float* r32_dev, double* gap_h
     if (n > 0) {
         const int32_t* cnt = (mode == 2) ? g.deg.p : (mode == 3 ? g.tcount.p : g.qcount.p);
         k_init_keys<<<grid_for(n, 256), 256, 0, s>>>(cnt, mode == 3 ? 2 : 1, g.orig_of.p, n, B, f.K[0].p, f.K[1].p,
+                                                    codes_of(g, mode, 0),
                                                     f.Q[0].p, f.Q[1].p);
         LDS_HIP(hipGetLastError());
     }
@@ -1283,7 +1318,7 @@ void fw_run_noalloc(Graph& g, int mode, int iters, float* r32_dev, double* gap_h
     fill_sweep_args(g, p, a);
     const bool any = blocks > 0 && p.nrows > 0;
     for (int i = 1; i <= iters && any; ++i)
-        sweep_iteration(f, p, a, mode, i, blocks, gap ? partial + (size_t)(i - 1) * gblocks * 4 : nullptr, s);
+        sweep_iteration(g, f, p, a, mode, i, blocks, gap ? partial + (size_t)(i - 1) * gblocks * 4 : nullptr, s);
     f.iters = iters;
     f.ran = true;
     f.timed = false;

@@ -117,3 +117,15 @@ def test_batch_of_word_runs(threads, lds_vertices):
         lds.lds_batch_run(b)
         for h, m, a in zip(hs, modes, want):
             np.testing.assert_array_equal(lds.lds_loads(h, m, want_num=True)["num"], a)
+
+
+@pytest.mark.parametrize("leaves", [65_533, 65_534, 65_535, 80_000])
+def test_load_codes(leaves):
+    """the two widths of the 16-bit load codes, at the largest degree that
+    parts them, with loads from 0 to half that degree"""
+    announce("load codes", leaves)
+    hub = np.zeros(leaves, np.int32)
+    leaf = np.arange(3, 3 + leaves, dtype=np.int32)
+    u = np.concatenate([[0, 1], hub, hub[: leaves // 2] + 1, leaf[:-1:7]]).astype(np.int32)
+    v = np.concatenate([[1, 2], leaf, leaf[: leaves // 2], leaf[1::7][: len(leaf[:-1:7])]]).astype(np.int32)
+    check_fw(leaves + 5, u, v, 2, 23)
