@@ -58,7 +58,12 @@ __device__ inline uint64_t fw_inc(int h, int i) {  // D_i - D_{i-1}
     return (uint64_t)(h == 3 ? 6 : 2) * (uint64_t)(i + 1);
 }
 
-constexpr int kG = 8;      // 64-slot words in flight per wave
+// 64-slot words in flight per wave.  A batch costs its instructions whether its
+// words are there or not: the graphs that run alone in k_fw_one have few words
+// a wave (446 slots 2.03 us an iteration with 8, 1.54 with 4; 2.6k 2.78 and
+// 2.49; 10k 4.65 and 4.46; 16k 6.42 and 6.51), the largest of a batch, which
+// bound its time, many (768 graphs 9.6 and 9.9 ms).
+constexpr int kBatchWords = 8, kOneWords = 4;
 constexpr int kRows = 4;   // rows per thread whose bounds stay in registers over the iterations
 
 // LDS of a workgroup: two key buffers of kmax vertices, then the decision
@@ -83,7 +88,7 @@ struct Lds {
 // chunks, with keys through generic pointers and a barrier pair per hub row,
 // 768 graphs (half edge, half triangle density, n <= 5000) took 21 ms; now
 // 8.0 ms.
-template <int H, int NT, bool KLDS>
+template <int H, int NT, bool KLDS, int kG>
 __device__ void run_graph(const BItem& it, uint64_t* Ka, uint64_t* Kb, const Lds& l) {
     constexpr int NW = NT / 64;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -259,14 +264,14 @@ template <int NT>
 __device__ inline void run_item(const BItem& it, const Lds& l) {
     if (it.lds_keys) {
         if (it.h == 2)
-            run_graph<2, NT, true>(it, l.keys, l.keys + l.kmax, l);
+            run_graph<2, NT, true, kBatchWords>(it, l.keys, l.keys + l.kmax, l);
         else
-            run_graph<3, NT, true>(it, l.keys, l.keys + l.kmax, l);
+            run_graph<3, NT, true, kBatchWords>(it, l.keys, l.keys + l.kmax, l);
     } else {
         if (it.h == 2)
-            run_graph<2, NT, false>(it, it.K0, it.K1, l);
+            run_graph<2, NT, false, kBatchWords>(it, it.K0, it.K1, l);
         else
-            run_graph<3, NT, false>(it, it.K0, it.K1, l);
+            run_graph<3, NT, false, kBatchWords>(it, it.K0, it.K1, l);
     }
 }
 
@@ -294,9 +299,9 @@ __global__ __launch_bounds__(NT) void k_fw_one(BItem it) {
     __shared__ uint64_t red[NT / 64][4];
     const Lds l{dyn, it.n, dyn + 2 * (size_t)it.n, it.total_words, red};
     if (it.h == 2)
-        run_graph<2, NT, true>(it, l.keys, l.keys + l.kmax, l);
+        run_graph<2, NT, true, kOneWords>(it, l.keys, l.keys + l.kmax, l);
     else
-        run_graph<3, NT, true>(it, l.keys, l.keys + l.kmax, l);
+        run_graph<3, NT, true, kOneWords>(it, l.keys, l.keys + l.kmax, l);
 }
 
 __global__ void k_zero_i32(int32_t* p) { *p = 0; }
@@ -377,7 +382,7 @@ void fw_run_one(Graph& g, int mode, int iters, uint64_t* sums, hipStream_t s) {
     BItem x = make_item(g, mode, iters, kOneVertices);
     x.sums = sums;
     const size_t lds = one_lds(g, plan_of(g, mode));
-    if (x.total_words <= 4 * kG) {  // a batch of words per wave: fewer waves, cheaper barriers
+    if (x.total_words <= 4 * kOneWords) {  // a batch of words per wave: fewer waves, cheaper barriers
         LDS_HIP(hipFuncSetAttribute((const void*)k_fw_one<256>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)kMaxLds));
         k_fw_one<256><<<1, 256, lds, s>>>(x);
