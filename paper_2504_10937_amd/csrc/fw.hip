@@ -14,15 +14,15 @@
 // Sweep (one launch per iteration, keys ping-pong between two buffers so that
 // every decision reads r^(i-1)).  Pull over incidence slots: a vertex wins a
 // slot's pattern iff its key is below the keys of the other h-1 vertices.
-//   * chunk waves: a wave64 streams one row-aligned chunk in 64-slot words;
-//     the wave ballot of wins is the iteration's decision word for those
-//     slots (stored once, coalesced); row-start flags turn the ballot into
-//     per-row win counts with popcounts (segmented count, no atomics), and
-//     the lane holding a row's last slot writes the row's new key.
+//   * chunk waves: a wave64 streams one row-aligned chunk in 64-slot words, a
+//     batch of words in flight; the wave ballot of wins is a word's decision
+//     word of the iteration (stored once, coalesced); then a lane per row
+//     counts its slots' wins in the chunk's words with popcounts (no atomics)
+//     and writes the row's new key and code.
 //   * hub pieces: a row with more slots than a chunk is cut into word-aligned
-//     pieces of at most kPiece slots, one wave each, scheduled before the
-//     chunks over all waves; a piece adds its wins to the row's counter and
-//     the wave that completes the row's last piece writes the row's key.
+//     pieces, one wave each, dealt over all waves with the chunks; a piece
+//     adds its wins to the row's counter and the wave that completes the row's
+//     last piece writes the row's key.
 // The duality-gap terms sum_u A_u^2 and sum_u A_u b_u (= sum over patterns of
 // the winning numerator, i.e. the minimum) are accumulated exactly in 128-bit
 // integers per workgroup and reduced once after the last iteration.
@@ -457,8 +457,8 @@ __device__ inline void heavy_parts(const SweepArgs& a, uint8_t* dyn, int64_t* sg
 // Persistent sweep: one workgroup per CU.  The workgroup first copies the
 // codes of the kCacheQ highest-degree vertices (internal ids [0, kCacheQ))
 // into LDS; those vertices take most of the gathers of a power-law graph.
-// It then processes hub rows (whole workgroup each) and chunks (one wave
-// each), both strided over the grid.
+// It then processes hub pieces and chunks, one wave each, dealt over the
+// waves of the grid, kG words at a time.  HEAVY: with the 2D part.
 template <int H, bool HEAVY, bool GAP, bool PK, int kG>
 __global__ __launch_bounds__(kPT) void k_fw_sweep(SweepArgs a) {
     constexpr bool IDENT = H == 2;  // compact row = vertex
