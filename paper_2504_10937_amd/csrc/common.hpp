@@ -113,10 +113,11 @@ void exclusive_scan_u32_to_u64(const uint32_t* in, uint64_t* out, int64_t n, uin
                                hipStream_t s);
 
 // Stable LSD radix sort of 64-bit keys over bits [begin_bit, end_bit), with an
-// optional 32-bit payload.  Result is left in keys/vals (buffers swapped
-// internally through the provided temporaries of the same size).
-void radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int begin_bit, int end_bit, uint64_t* tmp_keys,
-                    uint32_t* tmp_vals, hipStream_t s);
+// optional 32-bit payload.  The result is left in keys / vals, which change
+// places with the temporaries of the same size after an odd number of passes
+// (a copy back took 1.2 ms a GB).
+void radix_sort_u64(DBuf<uint64_t>& keys, DBuf<uint32_t>* vals, int64_t n, int begin_bit, int end_bit,
+                    DBuf<uint64_t>& tmp_keys, DBuf<uint32_t>* tmp_vals, hipStream_t s);
 
 // Both orientations (a << vb | b) of every pair of distinct ids below n,
 // grouped by the top `bits` (at most 16) of their 2 vb bits: ka and kb hold

@@ -1047,7 +1047,7 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
             tmp.alloc(nk, s);
             k_canon<<<grid_for(npairs, kT), kT, 0, s>>>(ps, pd, npairs, n, vb, strict, keys.p, &found.p->err);
             LDS_HIP(hipGetLastError());
-            radix_sort_u64(keys.p, nullptr, nk, 0, 2 * vb, tmp.p, nullptr, s);
+            radix_sort_u64(keys, nullptr, nk, 0, 2 * vb, tmp, nullptr, s);
             DBuf<uint32_t> flag;
             flag.alloc(nk, s);
             k_unique_flags<<<grid_for(nk, kT), kT, 0, s>>>(keys.p, nk, sentinel, strict, flag.p, &found.p->err);
@@ -1095,7 +1095,7 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         k_relabel_keys<<<grid_for(n, kT), kT, 0, s>>>(deg_orig.p, n, vb, g.max_deg, rk.p);
         LDS_HIP(hipGetLastError());
         // keys in id order: the stable sort needs the degree bits only
-        radix_sort_u64(rk.p, nullptr, n, vb, vb + bits_for((uint64_t)g.max_deg), rt.p, nullptr, s);
+        radix_sort_u64(rk, nullptr, n, vb, vb + bits_for((uint64_t)g.max_deg), rt, nullptr, s);
         k_relabel_apply<<<grid_for(n, kT), kT, 0, s>>>(rk.p, n, vb, deg_orig.p, g.orig_of.p, g.int_of.p,
                                                       g.deg.p);
         LDS_HIP(hipGetLastError());
@@ -1163,7 +1163,7 @@ void sort_rows(Graph& g, hipStream_t s) {
             tmp.alloc(nk, s);
             k_row_keys<<<(unsigned)std::min<int64_t>(rb, 65535), kT, 0, s>>>(g.rowptr.p, rb, g.vbits, g.col.p, keys.p);
             LDS_HIP(hipGetLastError());
-            radix_sort_u64(keys.p, nullptr, nk, 0, g.vbits + bits_for((uint64_t)rb), tmp.p, nullptr, s);
+            radix_sort_u64(keys, nullptr, nk, 0, g.vbits + bits_for((uint64_t)rb), tmp, nullptr, s);
             k_row_unkeys<<<grid_for(nk, kT), kT, 0, s>>>(keys.p, nk, g.vbits, g.col.p);
             LDS_HIP(hipGetLastError());
         }

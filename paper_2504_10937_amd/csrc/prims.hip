@@ -457,30 +457,24 @@ void exclusive_scan_u32_to_u64(const uint32_t* in, uint64_t* out, int64_t n, uin
     scan_impl<uint32_t>(in, out, n, total_dev, s);
 }
 
-void radix_sort_u64(uint64_t* keys, uint32_t* vals, int64_t n, int begin_bit, int end_bit, uint64_t* tmp_keys,
-                    uint32_t* tmp_vals, hipStream_t s) {
+void radix_sort_u64(DBuf<uint64_t>& keys, DBuf<uint32_t>* vals, int64_t n, int begin_bit, int end_bit,
+                    DBuf<uint64_t>& tmp_keys, DBuf<uint32_t>* tmp_vals, hipStream_t s) {
     if (n <= 1 || end_bit <= begin_bit) return;
     if (n <= kTile) {
         if (vals)
-            k_radix_small<true><<<1, kThreads, 0, s>>>(keys, vals, (int)n, begin_bit, end_bit);
+            k_radix_small<true><<<1, kThreads, 0, s>>>(keys.p, vals->p, (int)n, begin_bit, end_bit);
         else
-            k_radix_small<false><<<1, kThreads, 0, s>>>(keys, nullptr, (int)n, begin_bit, end_bit);
+            k_radix_small<false><<<1, kThreads, 0, s>>>(keys.p, nullptr, (int)n, begin_bit, end_bit);
         LDS_HIP(hipGetLastError());
         return;
     }
     DBuf<uint64_t> hist;
     hist.alloc((size_t)256 * radix_blocks(n), s);
-    uint64_t *ka = keys, *kb = tmp_keys;
-    uint32_t *va = vals, *vb = tmp_vals;
-    int passes = 0;
-    for (int shift = begin_bit; shift < end_bit; shift += 8, ++passes) {
-        radix_pass(ArrayKeys{ka, nullptr, n}, va, kb, vb, n, shift, hist.p, nullptr, s);
-        std::swap(ka, kb);
-        std::swap(va, vb);
-    }
-    if (passes & 1) {
-        LDS_HIP(hipMemcpyAsync(keys, ka, (size_t)n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
-        if (vals) LDS_HIP(hipMemcpyAsync(vals, va, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
+    for (int shift = begin_bit; shift < end_bit; shift += 8) {
+        radix_pass(ArrayKeys{keys.p, nullptr, n}, vals ? vals->p : nullptr, tmp_keys.p, vals ? tmp_vals->p : nullptr, n,
+                   shift, hist.p, nullptr, s);
+        std::swap(keys, tmp_keys);
+        if (vals) std::swap(*vals, *tmp_vals);
     }
     // hist is released at scope exit: either to the stream-ordered caching
     // allocator of the caller, or through hipFree, which synchronises.

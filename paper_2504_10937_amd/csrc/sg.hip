@@ -1571,7 +1571,7 @@ void hub_suffix_splits(const SweepPlan& p, uint32_t D, uint32_t* a_slot, hipStre
     tvals.alloc(np, s);
     k_hub_nb_pairs<<<grid_for(nr, kT), kT, 0, s>>>(p.rp, p.py, r0, r1, cnt.p, off.p, a_slot, keys.p, vals.p);
     LDS_HIP(hipGetLastError());
-    radix_sort_u64(keys.p, vals.p, (int64_t)np, 0, std::max(1, bits_for((uint64_t)(Hp - 1))), tkeys.p, tvals.p, s);
+    radix_sort_u64(keys, &vals, (int64_t)np, 0, std::max(1, bits_for((uint64_t)(Hp - 1))), tkeys, &tvals, s);
     len.alloc(Hp, s);
     first.alloc(Hp, s);
     k_hub_sfx_len<<<grid_for(Hp, kT), kT, 0, s>>>(p.rp, p.hub_pre.p, Hp, len.p);
@@ -1637,7 +1637,7 @@ void sg_sort_prefix(Graph& g, int mode, hipStream_t s) {
         k_sort_init<<<grid_for(n, kT), kT, 0, s>>>(f.K[f.cur].p, n, k.p, v.p);
         LDS_HIP(hipGetLastError());
         const int kb = g.idbits + bits_for((uint64_t)fw_max_numerator(g, mode, f.iters));
-        radix_sort_u64(k.p, v.p, n, 0, std::min(kb, 64), kt.p, vt.p, s);
+        radix_sort_u64(k, &v, n, 0, std::min(kb, 64), kt, &vt, s);
         k_order<<<grid_for(n, kT), kT, 0, s>>>(v.p, n, q.order.p, q.pos.p);
         LDS_HIP(hipGetLastError());
     }

@@ -411,7 +411,7 @@ void build_incidence_plan(Graph& g, const int32_t* pat, int64_t np, const int32_
         k_row_keys<<<grid_for(n, kT), kT, 0, s>>>(count, n, vb, (int32_t)cmax, rk.p);
         LDS_HIP(hipGetLastError());
         // keys in id order: the stable sort needs the count bits only
-        radix_sort_u64(rk.p, nullptr, n, vb, vb + bits_for((uint64_t)cmax), rt.p, nullptr, s);
+        radix_sort_u64(rk, nullptr, n, vb, vb + bits_for((uint64_t)cmax), rt, nullptr, s);
         k_row_apply<<<grid_for(nrows, kT), kT, 0, s>>>(rk.p, nrows, vb, count, p.own_rid.p, row_of.p, rcount.p);
         LDS_HIP(hipGetLastError());
     }
@@ -431,7 +431,7 @@ void build_incidence_plan(Graph& g, const int32_t* pat, int64_t np, const int32_
         LDS_HIP(hipGetLastError());
         // the keys are made in pattern order and the sort is stable, so the
         // row bits alone order them
-        radix_sort_u64(ik.p, nullptr, H * np, tb, tb + rb, it.p, nullptr, s);
+        radix_sort_u64(ik, nullptr, H * np, tb, tb + rb, it, nullptr, s);
         if (H == 3) p.own_tos.alloc(H * np, s);
         if (p.packed)
             k_inc_pay<H, H == 4><<<grid_for(H * np, kT), kT, 0, s>>>(ik.p, H * np, tb, pat, p.own_rid.p, p.own_py.p,
