@@ -752,12 +752,13 @@ int64_t build_heavy(SweepPlan& p, int64_t n, hipStream_t s) {
 // and `pieces` hub pieces.  A sweep runs in rounds (every one of its kSweepWaves
 // waves takes one chunk or piece), so the size is the smallest that fills a
 // whole number of rounds.  A round costs a chain of dependent reads, then a
-// batch of 512 slots at a time: up to kOneBatch slots (one batch with the part
-// of the last row that a chunk takes beyond its target) is the best size while
-// there are few rounds, two batches once there are many, and tiny plans use
-// kChunkMin, to have more waves in flight.  Measured per sweep in us, by size:
-// 4.4M slots 1024 44, 768 35, 384 33, 256 40; 1.4M 1024 25, 320 19, 128 25;
-// 37M 1024 236, 960 221, 384 236; 24k 1024 14, 256 8.1, 128 7.7.
+// batch of 256 slots (512 from 2^22 slots on) at a time: up to kOneBatch slots
+// (with the part of the last row that a chunk takes beyond its target) is the
+// best size while there are few rounds, kTwoBatches once there are many, and
+// tiny plans use kChunkMin, to have more waves in flight.  Measured per sweep
+// in us, by size: 37M slots 1024 236, 960 221, 384 236; 4.4M 1024 44, 768 35,
+// 384 33, 256 40; 2.9M 512 18.9, 384 17.2, 256 20.2; 1.6M 512 17.0, 384 15.5,
+// 256 20.5; 24k 512 8.1, 256 6.8, 128 5.9, 64 6.4.
 // LDS_SWEEP_CHUNK (a multiple of 64 up to kChunk) overrides.
 constexpr int64_t kSweepWaves = 4096;
 constexpr int kChunkMin = 128;
