@@ -119,8 +119,9 @@ void exclusive_scan_u32_to_u64(const uint32_t* in, uint64_t* out, int64_t n, uin
 void radix_sort_u64(DBuf<uint64_t>& keys, DBuf<uint32_t>* vals, int64_t n, int begin_bit, int end_bit,
                     DBuf<uint64_t>& tmp_keys, DBuf<uint32_t>* tmp_vals, hipStream_t s);
 
-// Both orientations (a << vb | b) of every pair of distinct ids below n,
-// grouped by the top `bits` (at most 16) of their 2 vb bits: ka and kb hold
+// Both orientations (a' << vb | b) of every pair of distinct ids below n, a'
+// being a with its low `bits` (at most 16) moved to the top of its vb bits,
+// grouped by those: ka and kb hold
 // 2 np keys each, the result is one of them and *count_dev the keys in it.
 // *err gets bit 0 for an id out of range and, when strict, bit 1 for a loop.
 const uint64_t* bucket_pairs(const int32_t* src, const int32_t* dst, int64_t np, int64_t n, int vb, int bits,

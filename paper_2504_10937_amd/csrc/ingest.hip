@@ -56,14 +56,17 @@ __global__ void k_compact(const uint64_t* keys, const uint32_t* flag, const uint
 
 // ------------------------------------------------------------- buckets
 // The symmetric rows without a full sort.  The pairs' keys are grouped by the
-// top bits of their row (one or two radix passes), so that a bucket's keys
-// (those of 2^rowbits consecutive rows) fit a workgroup's LDS; the workgroup
-// drops duplicates with a hash set and groups the rest by row.  Rows come out
-// unsorted: they are sorted once, after the renumbering.  Compared with the
-// full sort of both ids (6 passes, then flags, a scan and a compaction over
-// all keys) the ingest of 2.1e8 keys went from 20 to 12.2 ms (the buckets
-// themselves 1.6) and of 4e7 keys from 4.8 to 2.3.  Bound: HBM (16 B per key
-// and pass, 12 for the buckets) and, in the buckets, LDS atomics.
+// low bits of their row (one or two radix passes), so that a bucket's keys
+// (those of 2^rowbits rows; neighbouring ids, among which the vertices of
+// large degree often crowd, fall into different buckets) fit a workgroup's
+// LDS; the workgroup drops duplicates with a hash set and groups the rest by
+// row.  Rows come out unsorted: they are sorted once, after the renumbering.
+// Compared with the full sort of both ids (6 passes, then flags, a scan and a
+// compaction over all keys) the ingest of 2.1e8 keys went from 20 to 12.2 ms
+// (the buckets themselves 1.6), of 4e7 keys from 4.8 to 2.3, and of 2e8 keys
+// with rows of 11,000, whose five fullest buckets go by groups, from 23.8 to
+// 12.9.  Bound: HBM (16 B per key and pass, 12 for the buckets) and, in the
+// buckets, LDS atomics.
 constexpr int kBucketSmall = 8192;   // keys of a bucket for a workgroup with half a CU's LDS
 constexpr int kBucketLarge = 24576;  // and for one with all of it
 constexpr int kBucketRowBits = 12;   // most rows of a bucket: 2^12 counters in LDS
@@ -137,7 +140,7 @@ __device__ inline void bucket_rows(const uint64_t* keys, int64_t q, int64_t s0, 
     if (t == NT - 1) bucket_n[q] = run + sum;
     for (int r = r0; r < r1; ++r) {
         const uint32_t c = cnt[r];
-        const int64_t o = (q << rowbits) + r;
+        const int64_t o = ((int64_t)r << (vb - rowbits)) + q;
         if (o < n) {
             deg[o] = (int32_t)c;
             rstart[o] = s0 + run;
@@ -151,8 +154,88 @@ __device__ inline void bucket_rows(const uint64_t* keys, int64_t q, int64_t s0, 
         if (rank[k] != kEmpty) out[s0 + cnt[key[k] >> vb] + rank[k]] = key[k];
 }
 
+// one bucket of any size, by groups of consecutive rows of at most
+// kBucketLarge keys each (a row past that, or too many groups, raises err bit
+// 3): the bucket's keys are read once to count the rows', then once a group,
+// whose keys go through the table and leave from it
+template <int NT, int TAB>
+__device__ inline void bucket_groups(const uint64_t* keys, int64_t q, int64_t s0, int64_t len, int vb, int rowbits,
+                                     int64_t n, int strict, uint32_t* out, uint32_t* bucket_n, int32_t* deg,
+                                     int64_t* rstart, unsigned* err, uint32_t* tab, uint32_t* cnt) {
+    constexpr int kGroups = 64;
+    constexpr uint32_t kEmpty = 0xffffffffu;
+    __shared__ int32_t from[kGroups + 1];
+    __shared__ int32_t groups;
+    __shared__ uint32_t total;
+    const int R = 1 << rowbits, t = threadIdx.x;
+    const uint64_t mask = (1ull << (vb + rowbits)) - 1;
+    for (int r = t; r < R; r += NT) cnt[r] = 0;
+    __syncthreads();
+    for (int64_t i = t; i < len; i += NT) atomicAdd(&cnt[(uint32_t)(keys[s0 + i] & mask) >> vb], 1u);
+    __syncthreads();
+    if (t == 0) {
+        int g = 0;
+        uint32_t sum = 0;
+        from[0] = 0;
+        for (int r = 0; r < R && g >= 0; ++r) {
+            if (sum + cnt[r] > (uint32_t)kBucketLarge) {
+                sum = 0;
+                if (++g == kGroups) g = -1;
+                else from[g] = r;
+            }
+            sum += cnt[r];
+            if (cnt[r] > (uint32_t)kBucketLarge) g = -1;
+        }
+        if (g < 0) atomicOr(err, 8u);
+        else from[g + 1] = R;
+        groups = g + 1;
+        total = 0;
+    }
+    __syncthreads();
+    bool dup = false;
+    for (int g = 0; g < groups; ++g) {
+        const int ra = from[g], rb = from[g + 1];
+        for (int i = t; i < TAB; i += NT) tab[i] = kEmpty;
+        for (int r = ra + t; r < rb; r += NT) cnt[r] = 0;
+        __syncthreads();
+        for (int64_t i = t; i < len; i += NT) {
+            const uint32_t key = (uint32_t)(keys[s0 + i] & mask);
+            const int r = (int)(key >> vb);
+            if (r < ra || r >= rb) continue;
+            uint32_t p = (key * 2654435769u) >> 8;
+            for (;; ++p) {  // ends: a quarter of the table stays empty
+                const uint32_t old = atomicCAS(&tab[p & (TAB - 1)], kEmpty, key);
+                if (old == kEmpty) atomicAdd(&cnt[r], 1u);
+                if (old == key) dup = true;
+                if (old == kEmpty || old == key) break;
+            }
+        }
+        __syncthreads();
+        if (t == 0) {
+            uint32_t run = total;
+            for (int r = ra; r < rb; ++r) {
+                const uint32_t c = cnt[r];
+                const int64_t o = ((int64_t)r << (vb - rowbits)) + q;
+                if (o < n) {
+                    deg[o] = (int32_t)c;
+                    rstart[o] = s0 + run;
+                }
+                cnt[r] = run;
+                run += c;
+            }
+            total = run;
+        }
+        __syncthreads();
+        for (int i = t; i < TAB; i += NT)
+            if (tab[i] != kEmpty) out[s0 + atomicAdd(&cnt[tab[i] >> vb], 1u)] = tab[i];
+        __syncthreads();
+    }
+    if (strict && dup) atomicOr(err, 4u);
+    if (t == 0) bucket_n[q] = groups > 0 ? total : 0;
+}
+
 // small buckets; the others go to the list of large ones (list[0]: their
-// number), those past kBucketLarge raise err bit 3
+// number)
 __global__ __launch_bounds__(1024) void k_buckets(const uint64_t* keys, const int64_t* start, int64_t buckets, int vb,
                                                  int rowbits, int64_t n, int strict, uint32_t* out,
                                                  uint32_t* bucket_n, int32_t* deg, int64_t* rstart, int32_t* list,
@@ -161,10 +244,7 @@ __global__ __launch_bounds__(1024) void k_buckets(const uint64_t* keys, const in
     __shared__ uint32_t part[16];
     const int64_t q = blockIdx.x, s0 = start[q], len = start[q + 1] - s0;
     if (len > kBucketSmall) {
-        if (threadIdx.x == 0) {
-            if (len > kBucketLarge) atomicOr(err, 8u);
-            else list[1 + atomicAdd(list, 1)] = (int32_t)q;
-        }
+        if (threadIdx.x == 0) list[1 + atomicAdd(list, 1)] = (int32_t)q;
         return;
     }
     bucket_rows<1024, kBucketSmall, 2 * kBucketSmall>(keys, q, s0, (int)len, vb, rowbits, n, strict, out, bucket_n,
@@ -178,9 +258,13 @@ __global__ __launch_bounds__(1024) void k_buckets_large(const uint64_t* keys, co
     extern __shared__ uint32_t bdyn[];  // 32768 table entries, the rows' counts
     __shared__ uint32_t part[16];
     for (int k = blockIdx.x; k < list[0]; k += gridDim.x) {
-        const int64_t q = list[1 + k], s0 = start[q];
-        bucket_rows<1024, kBucketLarge, 32768>(keys, q, s0, (int)(start[q + 1] - s0), vb, rowbits, n, strict, out,
-                                               bucket_n, deg, rstart, err, bdyn, bdyn + 32768, part);
+        const int64_t q = list[1 + k], s0 = start[q], len = start[q + 1] - s0;
+        if (len <= kBucketLarge)
+            bucket_rows<1024, kBucketLarge, 32768>(keys, q, s0, (int)len, vb, rowbits, n, strict, out, bucket_n, deg,
+                                                   rstart, err, bdyn, bdyn + 32768, part);
+        else
+            bucket_groups<1024, 32768>(keys, q, s0, len, vb, rowbits, n, strict, out, bucket_n, deg, rstart, err, bdyn,
+                                       bdyn + 32768);
         __syncthreads();
     }
 }
@@ -197,7 +281,7 @@ __global__ __launch_bounds__(kT) void k_bucket_permute(const uint32_t* in, const
     const int len = (int)bucket_n[q], R = 1 << rowbits;
     if (len == 0) return;
     for (int r = threadIdx.x; r < R; r += kT) {
-        const int64_t o = (q << rowbits) + r;
+        const int64_t o = ((int64_t)r << (vb - rowbits)) + q;
         if (o < n) shift_of[r] = rowptr[int_of[o]] - rstart[o];
     }
     __syncthreads();
@@ -986,11 +1070,11 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
     DBuf<int64_t> rstart;
     deg_orig.alloc(n, s);
     rstart.alloc(n, s);
-    // 1a. by buckets of rows: bits of the row that number the buckets, so that
+    // 1a. by buckets of rows: low bits of the row that number the buckets, so that
     //     a bucket holds 2048 to 4096 keys in the mean, at most 2^12 rows, and
-    //     a key's other bits fit 32; graphs past 2^16 such buckets, a bucket
-    //     past kBucketLarge keys (a vertex of that degree, ids that crowd) and
-    //     inputs that one workgroup sorts go by the full sort
+    //     a key's other bits fit 32; graphs past 2^16 such buckets, a row past
+    //     kBucketLarge keys and inputs that one workgroup sorts go by the full
+    //     sort
     const int64_t nk = 2 * npairs;
     int bits = std::max({bits_for((uint64_t)(nk >> 12)), vb - kBucketRowBits, 2 * vb - 32, 1});
     const int rowbits = vb - bits;
@@ -1029,7 +1113,7 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         LDS_HIP(hipGetLastError());
         degrees_found(deg_orig.p);
         read_found();
-        if (h.err & 8u) {  // a bucket too large
+        if (h.err & 8u) {  // a row too large
             bucketed = false;
             bkeys.release();
             bucket_n.release();

@@ -137,7 +137,7 @@ struct PairKeys {
     const int32_t* src;
     const int32_t* dst;
     int64_t np, n;
-    int vb;
+    int vb, low;  // bits of an id; low bits of a row that lead its key
     unsigned strict;
     unsigned* err;  // bit 0: an id out of range, bit 1: a loop (strict only)
     __device__ int64_t count() const { return 2 * np; }
@@ -154,7 +154,9 @@ struct PairKeys {
             if (e) atomicOr(err, e);
             return false;
         }
-        key = (i & 1) ? ((uint64_t)b << vb) | (uint64_t)a : ((uint64_t)a << vb) | (uint64_t)b;
+        const uint64_t row = (uint64_t)((i & 1) ? b : a), nb = (uint64_t)((i & 1) ? a : b);
+        const uint64_t lead = ((row & ((1ull << low) - 1)) << (vb - low)) | (row >> low);
+        key = (lead << vb) | nb;
         return true;
     }
 };
@@ -486,7 +488,7 @@ const uint64_t* bucket_pairs(const int32_t* src, const int32_t* dst, int64_t np,
     DBuf<uint64_t> hist;
     hist.alloc((size_t)256 * radix_blocks(2 * np), s);
     const int shift = 2 * vb - bits;
-    radix_pass(PairKeys{src, dst, np, n, vb, strict ? 1u : 0u, err}, nullptr, ka, nullptr, 2 * np, shift, hist.p, count_dev, s);
+    radix_pass(PairKeys{src, dst, np, n, vb, bits, strict ? 1u : 0u, err}, nullptr, ka, nullptr, 2 * np, shift, hist.p, count_dev, s);
     if (bits <= 8) return ka;
     radix_pass(ArrayKeys{ka, count_dev, 0}, nullptr, kb, nullptr, 2 * np, shift + 8, hist.p, nullptr, s);
     return kb;

@@ -24,6 +24,14 @@ def star(leaves, extra, seed):
         [np.arange(1, leaves + 1, dtype=np.int32), v])
 
 
+def hubs(count, leaves, step, extra, seed):
+    """`count` hubs whose ids agree in their low bits, with copies and loops"""
+    n, u, v = random_pairs(count * step * 64 + leaves, extra, seed)
+    h = np.repeat(np.arange(count, dtype=np.int32) * (step * 64), leaves)
+    w = np.tile(np.arange(leaves, dtype=np.int32), count)
+    return n, np.concatenate([h, u, h[:500]]), np.concatenate([w, v, w[:500]])
+
+
 CASES = {
     "buckets_2": lambda: random_pairs(700, 2_049, 1),
     "rows_below_buckets": lambda: random_pairs(40, 50_000, 2),     # mostly duplicates, tiny n
@@ -31,6 +39,8 @@ CASES = {
     "two_passes": lambda: random_pairs(60_000, 400_000, 4),
     "large_bucket": lambda: star(9_000, 30_000, 5),                # a row of 9000 keys
     "largest_bucket": lambda: star(24_000, 200, 6),
+    "grouped_buckets": lambda: hubs(9, 9_000, 64, 20_000, 10),     # hubs that share one bucket, three groups
+    "grouped_by_one": lambda: hubs(3, 24_000, 64, 3_000, 11),      # a row a group
     "overflowing_bucket": lambda: star(60_000, 20_000, 7),         # full sort
     "crowded": lambda: random_pairs(1_000_000, 150_000, 8, crowd=6.0),
     "sparse": lambda: random_pairs(3_000_000, 5_000, 9),
