@@ -45,6 +45,7 @@
 
 #include "graph.hpp"
 #include "gridsync.hpp"
+#include "kept.hpp"
 #include "push.hpp"
 #include "wave.hpp"
 
@@ -563,6 +564,7 @@ struct ScanArgs {
     // are one contiguous range of records, streamed instead of chased
     // through order -> row -> slot -> neighbour -> position
     const int64_t* P;      // n + 1 record offsets by position
+    bool narrow;           // whose values fit 32 bits
     const int32_t* own;    // position of the record's own vertex
     const int2* rec2;      // edges: (position of the other end, a_x)
     const int4* rec3;      // triangles: (position v, position w, a_x, a_v)
@@ -1220,9 +1222,8 @@ __device__ inline long long first_kept(int64_t lo, int64_t hi, int64_t from, con
 }
 
 // leader: the events of [lo, hi) (hi - lo <= 64 kEvWords) into the bitmaps
-// and the low words of the record offsets P after each position into pw,
-// then the first event; the loads of up to 4 kRT positions are in flight at
-// once
+// and the record offset P after each position into pw, then the first event;
+// the loads of up to 4 kRT positions are in flight at once
 __device__ inline long long search_kept(const ScanArgs& g, int64_t lo, int64_t hi, bool hasH, long long minH,
                                         uint64_t* evb, uint64_t* stb, uint32_t* pw) {
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -1250,7 +1251,7 @@ __device__ inline long long search_kept(const ScanArgs& g, int64_t lo, int64_t h
                     evb[wi] = be;
                     stb[wi] = bs;
                 }
-                pw[64 * wi + lane] = (uint32_t)(uint64_t)Pn[u];
+                keep_offset(pw, 64 * wi + lane, Pn[u]);
             }
         }
     }
@@ -1357,11 +1358,8 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
             // positions [fb, b) join the pending group S = [S0, b); the
             // frontier of the loads below and the end of S always coincide:
             // both start at the accepted boundary and move to every verified b
-            // P[b], from the kept window when it holds e (a walk has fewer than
-            // 2^32 records: the low words give its length)
-            const int64_t k1 = e >= kept_lo && e < kept_hi
-                                   ? kfb + (int64_t)(uint32_t)(pw[e - kept_lo] - (uint32_t)(uint64_t)kfb)
-                                   : g.P[b];
+            // P[b], from the kept window when it holds e
+            const int64_t k1 = e >= kept_lo && e < kept_hi ? kept_end(pw, g.narrow, kept_lo, e, g.P) : g.P[b];
             walked += k1 - kfb;
             // ahead only where the separate acceptance walk would be a grid
             // phase: a walk the leader runs alone costs less than the extra
@@ -1800,6 +1798,7 @@ void sg_stable_groups(Graph& g, int mode, hipStream_t s) {
     sa.part_work = std::max<int64_t>(1, env_i64("LDS_SCAN_PART_WORK", kPartWork));
     sa.lead_pos = env_i64("LDS_SCAN_LEAD_POS", kLeadPos);
     sa.P = rv.P;
+    sa.narrow = kept_in_32_bits(mode == 2 ? g.edge_plan.nslots : g.tri_plan.nslots);
     sa.own = rv.own;
     sa.rec2 = rv.rec2;
     sa.rec3 = rv.rec3;

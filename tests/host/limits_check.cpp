@@ -1,0 +1,42 @@
+// Host checks of the library's own arithmetic at the ends of its ranges, where
+// no test input of a usable size reaches: each line that fails is printed, and
+// "ok" when none does.
+#include <cstdint>
+#include <cstdio>
+#include <vector>
+
+#include "kept.hpp"
+
+using namespace lds;
+
+static int failures = 0;
+#define EXPECT(cond)                                          \
+    do {                                                      \
+        if (!(cond)) {                                        \
+            std::printf("line %d: %s\n", __LINE__, #cond);    \
+            ++failures;                                       \
+        }                                                     \
+    } while (0)
+
+// a window of 2056 positions with the records of a complete graph's triangles
+// (2,110,485 a position, 4,339,157,160 in all), and windows that end at 2^32
+static void kept_offsets() {
+    const int64_t per = 2055LL * 2054 / 2, n = 2056, lo = 7, top = (int64_t)1 << 32;
+    for (int64_t last : {n * per, top - 1, top, top + 1, (int64_t)3 * INT32_MAX}) {
+        std::vector<int64_t> P(lo + n + 1, 0);
+        std::vector<uint32_t> kept(n);
+        for (int64_t i = 0; i < n; ++i) {
+            P[lo + i + 1] = last - (n - 1 - i) * (last >= n * per ? per : 1);
+            keep_offset(kept.data(), i, P[lo + i + 1]);
+        }
+        for (int64_t i = 0; i < n; ++i)
+            EXPECT(kept_end(kept.data(), kept_in_32_bits(last), lo, lo + i, P.data()) == P[lo + i + 1]);
+    }
+    EXPECT(kept_in_32_bits(top - 1) && !kept_in_32_bits(top));
+}
+
+int main() {
+    kept_offsets();
+    if (failures == 0) std::printf("ok\n");
+    return failures != 0;
+}
