@@ -55,6 +55,13 @@ inline void check_split_width(int mode, int64_t iters) {
         throw Error(ST_OVERFLOW, "split numerators of this many iterations exceed 32 bits (D_N > 2^32 - 1)");
 }
 
+// At most 2^31 - 1 unique edges: the patterns of a prefix and its length then
+// lie below 2^31 each, so that two prefix densities are compared by 64-bit
+// products (the patterns of the other modes are checked at their listing).
+inline void check_edge_count(int64_t m) {
+    if (m > (int64_t)INT32_MAX) throw Error(ST_OVERFLOW, "more than 2^31 - 1 unique edges");
+}
+
 // index of a mode's Frank-Wolfe / stable-group state: edges 0, triangles 1, 4-cliques 2
 inline int mode_slot(int mode) { return mode - 2; }
 

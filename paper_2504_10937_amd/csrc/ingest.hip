@@ -1166,6 +1166,7 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
     dsrc.release();
     ddst.release();
     g.m = ns / 2;
+    check_edge_count(g.m);
 
     // 2. renumbering by degree desc, original id asc
     g.max_deg = h.dmax;

@@ -298,8 +298,9 @@ __global__ void k_inclusive(const uint64_t* excl, const int64_t* c, int64_t n, i
 }
 
 // ---------------------------------------------- strict suffix maxima of E/j
-// fraction (num, den), den = 0 means "minus infinity"; pattern counts and
-// positions are below 2^31 each, so the cross products fit 64 bits
+// fraction (num, den), den = 0 means "minus infinity"; pattern counts
+// (check_edge_count, build_incidence_plan) and positions are below 2^31 each,
+// so the cross products fit 64 bits
 struct Frac {
     int64_t n, d;
 };

@@ -5,7 +5,14 @@
 #include <cstdio>
 #include <vector>
 
+#include "graph.hpp"
 #include "kept.hpp"
+
+namespace lds {
+void* dev_alloc(size_t, hipStream_t) { return nullptr; }
+void dev_free(void*) {}
+Graph::~Graph() {}
+}  // namespace lds
 
 using namespace lds;
 
@@ -35,7 +42,22 @@ static void kept_offsets() {
     EXPECT(kept_in_32_bits(top - 1) && !kept_in_32_bits(top));
 }
 
+// as include/lds.h promises for lds_create_graph
+static void edge_count() {
+    auto status = [](int64_t m) {
+        try {
+            check_edge_count(m);
+        } catch (const Error& e) {
+            return e.code;
+        }
+        return (int)ST_OK;
+    };
+    EXPECT(status(0) == ST_OK && status(INT32_MAX) == ST_OK);
+    EXPECT(status((int64_t)INT32_MAX + 1) == ST_OVERFLOW && status((int64_t)1 << 33) == ST_OVERFLOW);
+}
+
 int main() {
+    edge_count();
     kept_offsets();
     if (failures == 0) std::printf("ok\n");
     return failures != 0;
