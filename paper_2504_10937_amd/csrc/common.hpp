@@ -100,6 +100,16 @@ inline unsigned grid_for(int64_t work, int per_block) {
     return static_cast<unsigned>(g);
 }
 
+// Workgroups for `items` items, `per` of them a workgroup of at most 512
+// threads, where the kernel strides over the items by the grid: a launch may
+// not have 2^32 threads, so more items than that take turns (2^22 workgroups
+// keep the dynamic order of the workgroups in all but such sizes).
+constexpr int64_t kStrideWG = (int64_t)1 << 22;
+inline unsigned stride_grid(int64_t items, int per) {
+    const int64_t g = (items + per - 1) / per;
+    return static_cast<unsigned>(g < 1 ? 1 : g > kStrideWG ? kStrideWG : g);
+}
+
 // workgroups of a grid-stride reduction into a few global counters (one
 // atomic per wave): enough to fill the chip, few enough that the atomics on
 // one address stay cheap

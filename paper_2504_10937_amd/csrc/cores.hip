@@ -66,14 +66,18 @@ __global__ void k_init_whole(const int64_t* rowptr, int64_t n, int32_t* cnt, int
 constexpr int kInitG = 16;
 __global__ __launch_bounds__(kT) void k_init_edges(const int64_t* rowptr, const int32_t* col, int64_t n,
                                                    const uint8_t* alive, int32_t* cnt) {
-    const int64_t v = ((int64_t)blockIdx.x * kT + threadIdx.x) / kInitG;
     const int e = threadIdx.x % kInitG;
-    int32_t c = 0;
-    if (v < n && alive[v])
-        for (int64_t s = rowptr[v] + e; s < rowptr[v + 1]; s += kInitG) c += alive[col[s]] ? 1 : 0;
+    const int64_t step = (int64_t)gridDim.x * (kT / kInitG);
+    // (the same trips for every lane of a wave, for the shuffles)
+    for (int64_t v0 = (int64_t)blockIdx.x * (kT / kInitG); v0 < n; v0 += step) {
+        const int64_t v = v0 + threadIdx.x / kInitG;
+        int32_t c = 0;
+        if (v < n && alive[v])
+            for (int64_t s = rowptr[v] + e; s < rowptr[v + 1]; s += kInitG) c += alive[col[s]] ? 1 : 0;
 #pragma unroll
-    for (int m = kInitG / 2; m > 0; m >>= 1) c += __shfl_xor(c, m, 64);
-    if (v < n && e == 0) cnt[v] = c;
+        for (int m = kInitG / 2; m > 0; m >>= 1) c += __shfl_xor(c, m, 64);
+        if (v < n && e == 0) cnt[v] = c;
+    }
 }
 
 // the alive vertices, with counts still to be made when zero is set
@@ -586,7 +590,7 @@ void core_numbers_gpu(Graph& g, int mode, const uint8_t* alive, int32_t* core, h
         k_init_vertices<<<grid_for(n, kT), kT, 0, s>>>(n, alive, mode != 2, cnt.p, core, act.p, ctr.p);
     if (mode == 2) {
         if (alive)
-            k_init_edges<<<grid_for(n, kT / kInitG), kT, 0, s>>>(g.rowptr.p, g.col.p, n, alive, cnt.p);
+            k_init_edges<<<stride_grid(n, kT / kInitG), kT, 0, s>>>(g.rowptr.p, g.col.p, n, alive, cnt.p);
     } else {
         if (g.T > 0) {
             talive.alloc(g.T, s);

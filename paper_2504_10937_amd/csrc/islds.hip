@@ -133,23 +133,24 @@ template <bool WRITE>
 __global__ void k_pairs(const int32_t* U, int32_t nu, const int64_t* rowptr, const int32_t* col, const int32_t* loc,
                         uint32_t* cnt, const uint64_t* off, int32_t* pairs) {
     const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
-    if (i >= nu) return;
-    const int32_t v = U[i];
-    const int64_t e = rowptr[v + 1];
-    uint64_t o = WRITE ? off[i] : 0;
-    for (int64_t s0 = rowptr[v]; s0 < e; s0 += 64) {
-        const int64_t s = s0 + lane;
-        const int32_t j = s < e ? loc[col[s]] : -1;
-        const uint64_t in = __ballot(j > (int32_t)i);
-        if (WRITE && j > (int32_t)i) {
-            const uint64_t at = o + __popcll(in & ((1ull << lane) - 1));
-            pairs[2 * at] = (int32_t)i;
-            pairs[2 * at + 1] = j;
+    for (int64_t i = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6); i < nu;
+         i += (int64_t)gridDim.x * (kT / 64)) {
+        const int32_t v = U[i];
+        const int64_t e = rowptr[v + 1];
+        uint64_t o = WRITE ? off[i] : 0;
+        for (int64_t s0 = rowptr[v]; s0 < e; s0 += 64) {
+            const int64_t s = s0 + lane;
+            const int32_t j = s < e ? loc[col[s]] : -1;
+            const uint64_t in = __ballot(j > (int32_t)i);
+            if (WRITE && j > (int32_t)i) {
+                const uint64_t at = o + __popcll(in & ((1ull << lane) - 1));
+                pairs[2 * at] = (int32_t)i;
+                pairs[2 * at + 1] = j;
+            }
+            o += __popcll(in);
         }
-        o += __popcll(in);
+        if (!WRITE && lane == 0) cnt[i] = (uint32_t)o;
     }
-    if (!WRITE && lane == 0) cnt[i] = (uint32_t)o;
 }
 
 // triangle patterns by local index, -1 for members above the band
@@ -347,8 +348,8 @@ bool scope_band(Graph& g, BandScope& b, const std::vector<int32_t>& S, int64_t r
             off.alloc(nu, s);
             tot.alloc(1, s);
             lp.alloc(nu, s);
-            k_pairs<false><<<grid_for(nu, kT / 64), kT, 0, s>>>(b.U.p, nu, g.rowptr.p, g.col.p, b.loc.p, cnt.p, nullptr,
-                                                          nullptr);
+            const unsigned grid = stride_grid(nu, kT / 64);
+            k_pairs<false><<<grid, kT, 0, s>>>(b.U.p, nu, g.rowptr.p, g.col.p, b.loc.p, cnt.p, nullptr, nullptr);
             LDS_HIP(hipGetLastError());
             exclusive_scan_u32_to_u64(cnt.p, off.p, nu, tot.p, s);
             uint64_t m = 0;
@@ -357,8 +358,7 @@ bool scope_band(Graph& g, BandScope& b, const std::vector<int32_t>& S, int64_t r
             DBuf<int32_t> pairs;
             pairs.alloc(2 * m, s);
             if (m > 0) {
-                k_pairs<true><<<grid_for(nu, kT / 64), kT, 0, s>>>(b.U.p, nu, g.rowptr.p, g.col.p, b.loc.p, nullptr, off.p,
-                                                             pairs.p);
+                k_pairs<true><<<grid, kT, 0, s>>>(b.U.p, nu, g.rowptr.p, g.col.p, b.loc.p, nullptr, off.p, pairs.p);
                 LDS_HIP(hipGetLastError());
             }
             k_loops_of<<<grid_for(nu, kT), kT, 0, s>>>(b.U.p, nu, b.loops.p, lp.p);

@@ -100,93 +100,95 @@ __global__ __launch_bounds__(kT) void k_tri_units(const int64_t* rp, const int32
     __shared__ uint32_t pre[NW][kUnitEdges];    // inclusive candidate counts of the unit's edges
     __shared__ uint32_t ecnt[NW][kUnitEdges];   // WRITE: triangles of each edge
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t k = (int64_t)blockIdx.x * NW + w;
-    if (k >= units) return;  // whole waves; no workgroup barrier below
-    const int32_t u = unit_u[k];
-    const int i0 = unit_i0[k];
-    const int du = outdeg[u];
-    const int64_t ua = rp[u];
-    const int need = min(du, i0 + kUnitEdges);
-    const bool staged = need <= kUnitList;
-    const int i = i0 + lane;
-    int32_t v = 0;
-    int dv = 0;
-    int64_t va = 0;
-    if (i < du) {
-        v = col[ua + i];
-        dv = outdeg[v];
-        va = rp[v];
-    }
-    if (staged)
-        for (int q = lane; q < need; q += 64) list[w][q] = col[ua + q];
-    const bool walk = (int64_t)dv <= (int64_t)kProbeBias * i;
-    const uint32_t items = i < du && dv > 0 ? (uint32_t)(walk ? dv : i) : 0u;
-    const uint32_t inc = wave_incl_scan_u32(items);
-    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-    pre[w][lane] = inc;
-    if (WRITE) ecnt[w][lane] = 0;
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    uint32_t found = 0;
-    uint64_t o = WRITE ? off[k] : 0;
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (uint32_t base = 0; base < total; base += 64) {
-        const uint32_t c = base + (uint32_t)lane;
-        const bool in = c < total;
-        // the edge of candidate c: first e with pre[e] > c
-        int e = 0;
-#pragma unroll
-        for (int st = 32; st > 0; st >>= 1)
-            if (pre[w][e + st - 1] <= c) e += st;
-        if (!in) e = 63;
-        const int32_t ev = __shfl(v, e, 64);
-        const int edv = __shfl(dv, e, 64);
-        const int64_t eva = ((int64_t)__shfl((int)(va >> 32), e, 64) << 32) | (uint32_t)__shfl((int)(uint32_t)va, e, 64);
-        const int ei = i0 + e;
-        const uint32_t q = c - (e > 0 ? pre[w][e - 1] : 0u);
-        bool hit = false;
-        int32_t x = 0;
-        if (in) {
-            if ((int64_t)edv <= (int64_t)kProbeBias * ei) {  // walk N+(v), look up in N+(u)[0, ei)
-                x = col[eva + q];
-                if (staged) {
-                    int lo = 0, hi = ei;
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
-                        if (list[w][mid] < x) lo = mid + 1; else hi = mid;
+    // whole waves; no workgroup barrier within
+    for (int64_t k = (int64_t)blockIdx.x * NW + w; k < units; k += (int64_t)gridDim.x * NW) {
+        __builtin_amdgcn_wave_barrier();  // the wave's LDS is rewritten by its next unit
+        const int32_t u = unit_u[k];
+        const int i0 = unit_i0[k];
+        const int du = outdeg[u];
+        const int64_t ua = rp[u];
+        const int need = min(du, i0 + kUnitEdges);
+        const bool staged = need <= kUnitList;
+        const int i = i0 + lane;
+        int32_t v = 0;
+        int dv = 0;
+        int64_t va = 0;
+        if (i < du) {
+            v = col[ua + i];
+            dv = outdeg[v];
+            va = rp[v];
+        }
+        if (staged)
+            for (int q = lane; q < need; q += 64) list[w][q] = col[ua + q];
+        const bool walk = (int64_t)dv <= (int64_t)kProbeBias * i;
+        const uint32_t items = i < du && dv > 0 ? (uint32_t)(walk ? dv : i) : 0u;
+        const uint32_t inc = wave_incl_scan_u32(items);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        pre[w][lane] = inc;
+        if (WRITE) ecnt[w][lane] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        uint32_t found = 0;
+        uint64_t o = WRITE ? off[k] : 0;
+        const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+        for (uint32_t base = 0; base < total; base += 64) {
+            const uint32_t c = base + (uint32_t)lane;
+            const bool in = c < total;
+            // the edge of candidate c: first e with pre[e] > c
+            int e = 0;
+    #pragma unroll
+            for (int st = 32; st > 0; st >>= 1)
+                if (pre[w][e + st - 1] <= c) e += st;
+            if (!in) e = 63;
+            const int32_t ev = __shfl(v, e, 64);
+            const int edv = __shfl(dv, e, 64);
+            const int64_t eva = ((int64_t)__shfl((int)(va >> 32), e, 64) << 32) | (uint32_t)__shfl((int)(uint32_t)va, e, 64);
+            const int ei = i0 + e;
+            const uint32_t q = c - (e > 0 ? pre[w][e - 1] : 0u);
+            bool hit = false;
+            int32_t x = 0;
+            if (in) {
+                if ((int64_t)edv <= (int64_t)kProbeBias * ei) {  // walk N+(v), look up in N+(u)[0, ei)
+                    x = col[eva + q];
+                    if (staged) {
+                        int lo = 0, hi = ei;
+                        while (lo < hi) {
+                            const int mid = (lo + hi) >> 1;
+                            if (list[w][mid] < x) lo = mid + 1; else hi = mid;
+                        }
+                        hit = lo < ei && list[w][lo] == x;
+                    } else {
+                        const int64_t p = lower_bound_i32(col, ua, ua + ei, x);
+                        hit = p < ua + ei && col[p] == x;
                     }
-                    hit = lo < ei && list[w][lo] == x;
-                } else {
-                    const int64_t p = lower_bound_i32(col, ua, ua + ei, x);
-                    hit = p < ua + ei && col[p] == x;
+                } else {  // probe N+(u)[0, ei) in N+(v)
+                    x = staged ? list[w][q] : col[ua + q];
+                    const int64_t p = lower_bound_i32(col, eva, eva + edv, x);
+                    hit = p < eva + edv && col[p] == x;
                 }
-            } else {  // probe N+(u)[0, ei) in N+(v)
-                x = staged ? list[w][q] : col[ua + q];
-                const int64_t p = lower_bound_i32(col, eva, eva + edv, x);
-                hit = p < eva + edv && col[p] == x;
             }
-        }
-        const uint64_t H = __ballot(hit);
-        if (WRITE) {
-            if (hit) {
-                const uint64_t t = o + (uint64_t)__popcll(H & lt);
-                tri[3 * t + 0] = u;
-                tri[3 * t + 1] = ev;
-                tri[3 * t + 2] = x;
-                atomicAdd(&ecnt[w][e], 1u);
+            const uint64_t H = __ballot(hit);
+            if (WRITE) {
+                if (hit) {
+                    const uint64_t t = o + (uint64_t)__popcll(H & lt);
+                    tri[3 * t + 0] = u;
+                    tri[3 * t + 1] = ev;
+                    tri[3 * t + 2] = x;
+                    atomicAdd(&ecnt[w][e], 1u);
+                }
+                o += (uint64_t)__popcll(H);
             }
-            o += (uint64_t)__popcll(H);
+            found += (uint32_t)__popcll(H);
         }
-        found += (uint32_t)__popcll(H);
+        if (!WRITE) {
+            if (lane == 0) cnt[k] = found;
+            continue;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (ecnt[w][lane]) atomicAdd(&tc[v], (int32_t)ecnt[w][lane]);
+        if (lane == 0 && found) atomicAdd(&tc[u], (int32_t)found);
     }
-    if (!WRITE) {
-        if (lane == 0) cnt[k] = found;
-        return;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    if (ecnt[w][lane]) atomicAdd(&tc[v], (int32_t)ecnt[w][lane]);
-    if (lane == 0 && found) atomicAdd(&tc[u], (int32_t)found);
 }
 
 // Counts of a list of member ids (every stride-th entry of ids, from the
@@ -519,7 +521,7 @@ void list_triangles(Graph& g, hipStream_t s) {
             LDS_HIP(hipGetLastError());
             cnt.alloc(units, s);
             off.alloc(units, s);
-            const unsigned grid = grid_for(units, kT / 64);
+            const unsigned grid = stride_grid(units, kT / 64);
             k_tri_units<false><<<grid, kT, 0, s>>>(g.rowptr.p, g.col.p, outdeg.p, unit_u.p, unit_i0.p, units, cnt.p,
                                                    nullptr, nullptr, nullptr);
             LDS_HIP(hipGetLastError());

@@ -56,7 +56,19 @@ static void edge_count() {
     EXPECT(status((int64_t)INT32_MAX + 1) == ST_OVERFLOW && status((int64_t)1 << 33) == ST_OVERFLOW);
 }
 
+// 4 items a workgroup of 256 threads (a wave an item) and 16 (16 lanes an item)
+static void launches() {
+    for (int per : {4, 16})
+        for (int64_t items : {(int64_t)0, (int64_t)1, (int64_t)1 << 20, ((int64_t)1 << 26) - 1, (int64_t)1 << 26,
+                              (int64_t)1 << 28, (int64_t)INT32_MAX, (int64_t)1 << 33}) {
+            const int64_t g = stride_grid(items, per);
+            EXPECT(g >= 1 && g * 512 < (int64_t)1 << 32);
+            EXPECT(g * per >= items || g == kStrideWG);
+        }
+}
+
 int main() {
+    launches();
     edge_count();
     kept_offsets();
     if (failures == 0) std::printf("ok\n");
