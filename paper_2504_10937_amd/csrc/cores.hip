@@ -121,9 +121,10 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
 // leave waves without work), numbers their slots consecutively and deals them
 // to its lanes, U per lane in flight, so that short rows fill the wave and
 // the dependent reads of many slots overlap: with a wave per vertex and one
-// slot per lane, the peel of 1M vertices of 16 slots took 7.4 ms, now 2.3 ms.  range(v, q0, q1) gives
-// a vertex's slots, body(q, in) handles U slots per lane.  pre: 64 words of
-// LDS of the wave's own.
+// slot per lane, the peel of 1M vertices of 16 slots took 7.4 ms, now 2.3 ms.
+// The numbers are 32-bit: vertices with 2^31 slots together are taken one at a
+// time (one has fewer).  range(v, q0, q1) gives a vertex's slots, body(q, in)
+// handles U slots per lane.  pre: 64 words of LDS of the wave's own.
 template <int U, class RANGE, class BODY>
 __device__ inline void walk_slots(const int32_t* f, int32_t fc, int64_t gw, int64_t nwave, uint32_t* pre, RANGE range,
                                   BODY body) {
@@ -132,33 +133,38 @@ __device__ inline void walk_slots(const int32_t* f, int32_t fc, int64_t gw, int6
     for (int64_t base = gw * per; base < fc; base += nwave * per) {
         int64_t q0 = 0, q1 = 0;
         if (lane < per && base + lane < fc) range(f[base + lane], q0, q1);
-        const uint32_t inc =
-            (uint32_t)wave::scan(q1 - q0, (int64_t)0, [](int64_t a, int64_t b) { return a + b; });
-        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-        pre[lane] = inc;
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const int64_t from = q0 - (int64_t)(inc - (uint32_t)(q1 - q0));  // slot of number c: from + c
-        for (uint32_t c0 = 0; c0 < total; c0 += 64 * U) {
-            int64_t q[U];
-            bool in[U];
+        const int64_t len = q1 - q0;
+        const int64_t sum = wave::scan(len, (int64_t)0, [](int64_t a, int64_t b) { return a + b; });
+        const int rows = wave::rows_at_once(wave::lane63(sum));
+        for (int e0 = 0; e0 < 64; e0 += rows) {
+            // inclusive counts, of all the rows or of row e0 alone
+            const uint32_t inc = (uint32_t)(rows == 64 ? sum : lane >= e0 ? wave::lane_of(len, e0) : 0);
+            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+            pre[lane] = inc;
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int64_t from = q0 - (int64_t)(inc - (uint32_t)len);  // slot of number c: from + c
+            for (uint32_t c0 = 0; c0 < total; c0 += 64 * U) {
+                int64_t q[U];
+                bool in[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t c = c0 + 64 * u + (uint32_t)lane;
-                in[u] = c < total;
-                int e = 0;  // the vertex of slot c: first e with pre[e] > c
-                if (per > 1) {
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t c = c0 + 64 * u + (uint32_t)lane;
+                    in[u] = c < total;
+                    int e = 0;  // the vertex of slot c: first e with pre[e] > c
+                    if (per > 1) {
 #pragma unroll
-                    for (int st = 32; st > 0; st >>= 1)
-                        if (pre[e + st - 1] <= c) e += st;
+                        for (int st = 32; st > 0; st >>= 1)
+                            if (pre[e + st - 1] <= c) e += st;
+                    }
+                    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)from, e, 64);
+                    const int hi = __shfl((int)(from >> 32), e, 64);
+                    q[u] = (int64_t)(((uint64_t)(uint32_t)hi << 32) | lo) + (int64_t)c;
                 }
-                const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)from, e, 64);
-                const int hi = __shfl((int)(from >> 32), e, 64);
-                q[u] = (int64_t)(((uint64_t)(uint32_t)hi << 32) | lo) + (int64_t)c;
+                body(q, in);
             }
-            body(q, in);
+            __builtin_amdgcn_wave_barrier();  // pre is rewritten by the next vertices
         }
-        __builtin_amdgcn_wave_barrier();  // pre is rewritten by the next vertices
     }
 }
 

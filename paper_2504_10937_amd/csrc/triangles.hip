@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kT) void k_tri_units(const int64_t* rp, const int32
             const bool in = c < total;
             // the edge of candidate c: first e with pre[e] > c
             int e = 0;
-    #pragma unroll
+#pragma unroll
             for (int st = 32; st > 0; st >>= 1)
                 if (pre[w][e + st - 1] <= c) e += st;
             if (!in) e = 63;

@@ -7,6 +7,7 @@
 
 #include "graph.hpp"
 #include "kept.hpp"
+#include "wave.hpp"
 
 namespace lds {
 void* dev_alloc(size_t, hipStream_t) { return nullptr; }
@@ -67,7 +68,19 @@ static void launches() {
         }
 }
 
+// slots of 64 rows numbered in 32 bits by steps of 64 lanes and 4 a lane: the
+// last step's numbers do not wrap
+static void row_slots() {
+    for (int64_t slots : {(int64_t)1, (int64_t)INT32_MAX, (int64_t)1 << 31, ((int64_t)1 << 32) - 256,
+                          ((int64_t)1 << 32) + 41664}) {
+        const int64_t most = wave::rows_at_once(slots) == 64 ? slots : (int64_t)INT32_MAX;
+        EXPECT(most + 2 * 256 <= (int64_t)UINT32_MAX);
+    }
+    EXPECT(wave::rows_at_once(((int64_t)1 << 31) - 1) == 64);
+}
+
 int main() {
+    row_slots();
     launches();
     edge_count();
     kept_offsets();
