@@ -61,12 +61,15 @@ __global__ void k_compact(const uint64_t* keys, const uint32_t* flag, const uint
 // large degree often crowd, fall into different buckets) fit a workgroup's
 // LDS; the workgroup drops duplicates with a hash set and groups the rest by
 // row.  Rows come out unsorted: they are sorted once, after the renumbering.
-// Compared with the full sort of both ids (6 passes, then flags, a scan and a
-// compaction over all keys) the ingest of 2.1e8 keys went from 20 to 12.2 ms
-// (the buckets themselves 1.6), of 4e7 keys from 4.8 to 2.3, and of 2e8 keys
-// with rows of 11,000, whose five fullest buckets go by groups, from 23.8 to
-// 12.9.  Bound: HBM (16 B per key and pass, 12 for the buckets) and, in the
-// buckets, LDS atomics.
+// The keys of the buckets that overfill LDS (a vertex of large degree, a pair
+// given very often, ids that agree in their low bits) are sorted together, by
+// bucket and the 32 bits of a key, at what the keys of these buckets alone cost
+// (98M random pairs 8.6 ms, with a vertex of 1M neighbours besides 11.0; a full
+// sort of everything for its sake, after the buckets, took 23.4).  Compared with the full sort of both ids (6 passes, then flags, a
+// scan and a compaction over all keys) the ingest of 2.1e8 keys went from 20 to
+// 12.2 ms (the buckets themselves 1.6), of 4e7 keys from 4.8 to 2.3.  Bound:
+// HBM (16 B per key and pass, 12 for the buckets) and, in the buckets, LDS
+// atomics.
 constexpr int kBucketSmall = 8192;   // keys of a bucket for a workgroup with half a CU's LDS
 constexpr int kBucketLarge = 24576;  // and for one with all of it
 constexpr int kBucketRowBits = 12;   // most rows of a bucket: 2^12 counters in LDS
@@ -154,101 +157,36 @@ __device__ inline void bucket_rows(const uint64_t* keys, int64_t q, int64_t s0, 
         if (rank[k] != kEmpty) out[s0 + cnt[key[k] >> vb] + rank[k]] = key[k];
 }
 
-// one bucket of any size, by groups of consecutive rows of at most
-// kBucketLarge keys each (a row past that, or too many groups, raises err bit
-// 3): the bucket's keys are read once to count the rows', then once a group,
-// whose keys go through the table and leave from it
-template <int NT, int TAB>
-__device__ inline void bucket_groups(const uint64_t* keys, int64_t q, int64_t s0, int64_t len, int vb, int rowbits,
-                                     int64_t n, int strict, uint32_t* out, uint32_t* bucket_n, int32_t* deg,
-                                     int64_t* rstart, unsigned* err, uint32_t* tab, uint32_t* cnt) {
-    constexpr int kGroups = 64;
-    constexpr uint32_t kEmpty = 0xffffffffu;
-    __shared__ int32_t from[kGroups + 1];
-    __shared__ int32_t groups;
-    __shared__ uint32_t total;
-    const int R = 1 << rowbits, t = threadIdx.x;
-    const uint64_t mask = (1ull << (vb + rowbits)) - 1;
-    for (int r = t; r < R; r += NT) cnt[r] = 0;
-    __syncthreads();
-    for (int64_t i = t; i < len; i += NT) atomicAdd(&cnt[(uint32_t)(keys[s0 + i] & mask) >> vb], 1u);
-    __syncthreads();
-    if (t == 0) {
-        int g = 0;
-        uint32_t sum = 0;
-        from[0] = 0;
-        for (int r = 0; r < R && g >= 0; ++r) {
-            if (sum + cnt[r] > (uint32_t)kBucketLarge) {
-                sum = 0;
-                if (++g == kGroups) g = -1;
-                else from[g] = r;
-            }
-            sum += cnt[r];
-            if (cnt[r] > (uint32_t)kBucketLarge) g = -1;
-        }
-        if (g < 0) atomicOr(err, 8u);
-        else from[g + 1] = R;
-        groups = g + 1;
-        total = 0;
-    }
-    __syncthreads();
-    bool dup = false;
-    for (int g = 0; g < groups; ++g) {
-        const int ra = from[g], rb = from[g + 1];
-        for (int i = t; i < TAB; i += NT) tab[i] = kEmpty;
-        for (int r = ra + t; r < rb; r += NT) cnt[r] = 0;
-        __syncthreads();
-        for (int64_t i = t; i < len; i += NT) {
-            const uint32_t key = (uint32_t)(keys[s0 + i] & mask);
-            const int r = (int)(key >> vb);
-            if (r < ra || r >= rb) continue;
-            uint32_t p = (key * 2654435769u) >> 8;
-            for (;; ++p) {  // ends: a quarter of the table stays empty
-                const uint32_t old = atomicCAS(&tab[p & (TAB - 1)], kEmpty, key);
-                if (old == kEmpty) atomicAdd(&cnt[r], 1u);
-                if (old == key) dup = true;
-                if (old == kEmpty || old == key) break;
-            }
-        }
-        __syncthreads();
-        if (t == 0) {
-            uint32_t run = total;
-            for (int r = ra; r < rb; ++r) {
-                const uint32_t c = cnt[r];
-                const int64_t o = ((int64_t)r << (vb - rowbits)) + q;
-                if (o < n) {
-                    deg[o] = (int32_t)c;
-                    rstart[o] = s0 + run;
-                }
-                cnt[r] = run;
-                run += c;
-            }
-            total = run;
-        }
-        __syncthreads();
-        for (int i = t; i < TAB; i += NT)
-            if (tab[i] != kEmpty) out[s0 + atomicAdd(&cnt[tab[i] >> vb], 1u)] = tab[i];
-        __syncthreads();
-    }
-    if (strict && dup) atomicOr(err, 4u);
-    if (t == 0) bucket_n[q] = groups > 0 ? total : 0;
-}
+// what the host reads of the device's findings, in one copy
+struct Found {
+    unsigned long long nz, slots;  // vertices with slots, slots
+    int dmax;                      // largest degree
+    unsigned err;
+    unsigned long long over_keys;  // keys of the overfull buckets,
+    int over;                      // their number
+};
 
 // small buckets; the others go to the list of large ones (list[0]: their
-// number)
+// number) or to that of the overfull ones (over, found->over of them)
 __global__ __launch_bounds__(1024) void k_buckets(const uint64_t* keys, const int64_t* start, int64_t buckets, int vb,
                                                  int rowbits, int64_t n, int strict, uint32_t* out,
                                                  uint32_t* bucket_n, int32_t* deg, int64_t* rstart, int32_t* list,
-                                                 unsigned* err) {
+                                                 int32_t* over, Found* found) {
     extern __shared__ uint32_t bdyn[];  // 2 * kBucketSmall table entries, the rows' counts
     __shared__ uint32_t part[16];
     const int64_t q = blockIdx.x, s0 = start[q], len = start[q + 1] - s0;
     if (len > kBucketSmall) {
-        if (threadIdx.x == 0) list[1 + atomicAdd(list, 1)] = (int32_t)q;
+        if (threadIdx.x != 0) return;
+        if (len <= kBucketLarge) {
+            list[1 + atomicAdd(list, 1)] = (int32_t)q;
+        } else {
+            over[atomicAdd(&found->over, 1)] = (int32_t)q;
+            atomicAdd(&found->over_keys, (unsigned long long)len);
+        }
         return;
     }
     bucket_rows<1024, kBucketSmall, 2 * kBucketSmall>(keys, q, s0, (int)len, vb, rowbits, n, strict, out, bucket_n,
-                                                     deg, rstart, err, bdyn, bdyn + 2 * kBucketSmall, part);
+                                                     deg, rstart, &found->err, bdyn, bdyn + 2 * kBucketSmall, part);
 }
 
 __global__ __launch_bounds__(1024) void k_buckets_large(const uint64_t* keys, const int64_t* start, int vb,
@@ -259,25 +197,87 @@ __global__ __launch_bounds__(1024) void k_buckets_large(const uint64_t* keys, co
     __shared__ uint32_t part[16];
     for (int k = blockIdx.x; k < list[0]; k += gridDim.x) {
         const int64_t q = list[1 + k], s0 = start[q], len = start[q + 1] - s0;
-        if (len <= kBucketLarge)
-            bucket_rows<1024, kBucketLarge, 32768>(keys, q, s0, (int)len, vb, rowbits, n, strict, out, bucket_n, deg,
-                                                   rstart, err, bdyn, bdyn + 32768, part);
-        else
-            bucket_groups<1024, 32768>(keys, q, s0, len, vb, rowbits, n, strict, out, bucket_n, deg, rstart, err, bdyn,
-                                       bdyn + 32768);
+        bucket_rows<1024, kBucketLarge, 32768>(keys, q, s0, (int)len, vb, rowbits, n, strict, out, bucket_n, deg,
+                                               rstart, err, bdyn, bdyn + 32768, part);
         __syncthreads();
     }
 }
 
+// ---- overfull buckets: bucket i of the list holds the keys [off[i], off[i + 1])
+// of the concatenation
+__global__ void k_over_len(const int32_t* over, int nb, const int64_t* start, uint64_t* len) {
+    const int i = (int)(blockIdx.x * kT + threadIdx.x);
+    if (i < nb) len[i] = (uint64_t)(start[over[i] + 1] - start[over[i]]);
+}
+
+// the bucket of the concatenation's entry j: the last i with off[i] <= j
+__device__ inline int over_bucket(const uint64_t* off, int nb, uint64_t j) {
+    int lo = 0, hi = nb;
+    while (lo + 1 < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (off[mid] <= j) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// (bucket, row, neighbour) keys: the bucket from bit kb on
+__global__ void k_over_gather(const uint64_t* keys, const int32_t* over, int nb, const int64_t* start,
+                              const uint64_t* off, int64_t R, int kb, uint64_t* out) {
+    const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (j >= R) return;
+    const int i = over_bucket(off, nb, (uint64_t)j);
+    const uint64_t k = keys[start[over[i]] + (j - (int64_t)off[i])];
+    out[j] = ((uint64_t)i << kb) | (k & ((1ull << kb) - 1));
+}
+
+// first of the R sorted keys that is not below x
+__device__ inline int64_t over_lower(const uint64_t* k, int64_t R, uint64_t x) {
+    int64_t lo = 0, hi = R;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (k[mid] < x) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// a thread per row of the buckets: its degree and first slot, and the bucket's
+// slots, from the places `pos` (of *total) of the distinct keys
+__global__ void k_over_rows(const uint64_t* k, int64_t R, const uint64_t* pos, const uint64_t* total,
+                            const int32_t* over, int nb, const int64_t* start, const uint64_t* off, int vb, int rowbits,
+                            int64_t n, uint32_t* bucket_n, int32_t* deg, int64_t* rstart) {
+    const int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (t >= ((int64_t)nb << rowbits)) return;
+    const int64_t i = t >> rowbits, r = t & (((int64_t)1 << rowbits) - 1), q = over[i];
+    auto place = [&](int64_t x) { return (int64_t)(x < R ? pos[x] : *total); };
+    const uint64_t row = ((uint64_t)i << (vb + rowbits)) | ((uint64_t)r << vb);
+    const int64_t base = place((int64_t)off[i]);
+    const int64_t a = place(over_lower(k, R, row)), b = place(over_lower(k, R, row + (1ull << vb)));
+    const int64_t o = (r << (vb - rowbits)) + q;
+    if (o < n) {
+        deg[o] = (int32_t)(b - a);
+        rstart[o] = start[q] + (a - base);
+    }
+    if (r == 0) bucket_n[q] = (uint32_t)(place(i + 1 < nb ? (int64_t)off[i + 1] : R) - base);
+}
+
+__global__ void k_over_place(const uint64_t* k, const uint32_t* flag, const uint64_t* pos, int64_t R,
+                             const int32_t* over, const int64_t* start, const uint64_t* off, int kb, uint32_t* out) {
+    const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (j >= R || !flag[j]) return;
+    const int64_t i = (int64_t)(k[j] >> kb);
+    out[start[over[i]] + (int64_t)(pos[j] - pos[off[i]])] = (uint32_t)(k[j] & ((1ull << kb) - 1));
+}
+
 // the buckets' slots to their internal rows: row o's move from the bucket's
 // order to rowptr[int_of[o]], columns renumbered.  Bound: the random reads of
-// int_of (4 bytes a slot).
+// int_of (4 bytes a slot).  Overfull buckets take a thread a slot, below.
 __global__ __launch_bounds__(kT) void k_bucket_permute(const uint32_t* in, const int64_t* start,
                                                        const uint32_t* bucket_n, int vb, int rowbits, int64_t n,
                                                        const int64_t* rstart, const int32_t* int_of,
                                                        const int64_t* rowptr, int32_t* col) {
     extern __shared__ int64_t shift_of[];  // per row: first internal slot less the first bucket slot
     const int64_t q = blockIdx.x, s0 = start[q];
+    if (start[q + 1] - s0 > kBucketLarge) return;
     const int len = (int)bucket_n[q], R = 1 << rowbits;
     if (len == 0) return;
     for (int r = threadIdx.x; r < R; r += kT) {
@@ -298,6 +298,19 @@ __global__ __launch_bounds__(kT) void k_bucket_permute(const uint32_t* in, const
         for (int u = 0; u < U; ++u)
             if (j + u * kT < len) col[shift_of[k[u] >> vb] + s0 + j + u * kT] = c[u];
     }
+}
+
+__global__ void k_over_permute(const uint32_t* in, const int32_t* over, int nb, const int64_t* start,
+                               const uint64_t* off, int64_t R, const uint32_t* bucket_n, int vb, int rowbits,
+                               const int64_t* rstart, const int32_t* int_of, const int64_t* rowptr, int32_t* col) {
+    const int64_t x = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (x >= R) return;
+    const int i = over_bucket(off, nb, (uint64_t)x);
+    const int64_t q = over[i], j = x - (int64_t)off[i], s = start[q] + j;
+    if (j >= (int64_t)bucket_n[q]) return;
+    const uint32_t k = in[s];
+    const int64_t o = ((int64_t)(k >> vb) << (vb - rowbits)) + q;
+    col[rowptr[int_of[o]] + (s - rstart[o])] = int_of[k & (uint32_t)((1ull << vb) - 1)];
 }
 
 // run boundaries of the sorted symmetric keys: first slot and one-past-last
@@ -1044,12 +1057,6 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         ps = dsrc.p;
         pd = ddst.p;
     }
-    // what the host reads of the device's findings, in one copy
-    struct Found {
-        unsigned long long nz, slots;
-        int dmax;
-        unsigned err;
-    };
     DBuf<Found> found;
     found.alloc(1, s);
     Found h{};
@@ -1072,15 +1079,16 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
     rstart.alloc(n, s);
     // 1a. by buckets of rows: low bits of the row that number the buckets, so that
     //     a bucket holds 2048 to 4096 keys in the mean, at most 2^12 rows, and
-    //     a key's other bits fit 32; graphs past 2^16 such buckets, a row past
-    //     kBucketLarge keys and inputs that one workgroup sorts go by the full
-    //     sort
+    //     a key's other bits fit 32; graphs past 2^16 such buckets and inputs
+    //     that one workgroup sorts go by the full sort
     const int64_t nk = 2 * npairs;
     int bits = std::max({bits_for((uint64_t)(nk >> 12)), vb - kBucketRowBits, 2 * vb - 32, 1});
     const int rowbits = vb - bits;
-    bool bucketed = nk > 4096 && bits <= 16 && rowbits >= 0;
+    const bool bucketed = nk > 4096 && bits <= 16 && rowbits >= 0;
     DBuf<uint32_t> bkeys, bucket_n;
     DBuf<int64_t> bstart;
+    DBuf<int32_t> over;     // overfull buckets,
+    DBuf<uint64_t> over_off;  // their keys concatenated
     if (bucketed) {
         const int64_t buckets = (int64_t)1 << bits;
         DBuf<uint64_t> ka, kb, count;
@@ -1096,8 +1104,8 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         bkeys.alloc(nk, s);
         bucket_n.alloc(buckets, s);
         list.alloc(buckets + 1, s);
+        over.alloc(buckets, s);
         LDS_HIP(hipMemsetAsync(list.p, 0, sizeof(int32_t), s));
-        LDS_HIP(hipMemsetAsync(bucket_n.p, 0, bucket_n.bytes(), s));
         const size_t rows_lds = ((size_t)1 << rowbits) * sizeof(uint32_t);
         const size_t small_lds = 2 * kBucketSmall * sizeof(uint32_t) + rows_lds;
         const size_t large_lds = 32768 * sizeof(uint32_t) + rows_lds;
@@ -1106,19 +1114,45 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         LDS_HIP(hipFuncSetAttribute((const void*)k_buckets_large, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)(32768 * sizeof(uint32_t) + ((size_t)4 << kBucketRowBits))));
         k_buckets<<<(unsigned)buckets, 1024, small_lds, s>>>(keys, bstart.p, buckets, vb, rowbits, n, strict, bkeys.p,
-                                                           bucket_n.p, deg_orig.p, rstart.p, list.p, &found.p->err);
+                                                           bucket_n.p, deg_orig.p, rstart.p, list.p, over.p, found.p);
         LDS_HIP(hipGetLastError());
         k_buckets_large<<<(unsigned)std::min<int64_t>(buckets, kReduceWG), 1024, large_lds, s>>>(
             keys, bstart.p, vb, rowbits, n, strict, bkeys.p, bucket_n.p, deg_orig.p, rstart.p, list.p, &found.p->err);
         LDS_HIP(hipGetLastError());
         degrees_found(deg_orig.p);
         read_found();
-        if (h.err & 8u) {  // a row too large
-            bucketed = false;
-            bkeys.release();
-            bucket_n.release();
-            bstart.release();
-            LDS_HIP(hipMemsetAsync(found.p, 0, sizeof(Found), s));
+        if (h.over > 0) {
+            const int64_t R = (int64_t)h.over_keys;
+            const int nb = h.over, kb2 = vb + rowbits;
+            over_off.alloc(nb, s);
+            k_over_len<<<grid_for(nb, kT), kT, 0, s>>>(over.p, nb, bstart.p, over_off.p);
+            LDS_HIP(hipGetLastError());
+            exclusive_scan_u64(over_off.p, over_off.p, nb, nullptr, s);
+            // sorted in the key buffers: the other buckets are done with theirs
+            DBuf<uint64_t>& from = keys == ka.p ? ka : kb;
+            DBuf<uint64_t>& to = keys == ka.p ? kb : ka;
+            if ((int64_t)to.n < R) to.alloc(R, s);
+            k_over_gather<<<grid_for(R, kT), kT, 0, s>>>(from.p, over.p, nb, bstart.p, over_off.p, R, kb2, to.p);
+            LDS_HIP(hipGetLastError());
+            radix_sort_u64(to, nullptr, R, 0, kb2 + bits_for((uint64_t)(nb - 1)), from, nullptr, s);
+            DBuf<uint32_t> flag;
+            flag.alloc(R, s);
+            k_unique_flags<<<grid_for(R, kT), kT, 0, s>>>(to.p, R, ~0ull, strict, flag.p, &found.p->err);
+            LDS_HIP(hipGetLastError());
+            DBuf<uint64_t> total;
+            total.alloc(1, s);
+            exclusive_scan_u32_to_u64(flag.p, from.p, R, total.p, s);
+            k_over_rows<<<grid_for((int64_t)nb << rowbits, kT), kT, 0, s>>>(to.p, R, from.p, total.p, over.p, nb,
+                                                                          bstart.p, over_off.p, vb, rowbits, n,
+                                                                          bucket_n.p, deg_orig.p, rstart.p);
+            LDS_HIP(hipGetLastError());
+            k_over_place<<<grid_for(R, kT), kT, 0, s>>>(to.p, flag.p, from.p, R, over.p, bstart.p, over_off.p, kb2,
+                                                      bkeys.p);
+            LDS_HIP(hipGetLastError());
+            // the counts again, over every row
+            LDS_HIP(hipMemsetAsync(&found.p->nz, 0, 2 * sizeof(found.p->nz) + sizeof(found.p->dmax), s));
+            degrees_found(deg_orig.p);
+            read_found();
         }
     }
     // 1b. by a full sort of both orientations: duplicates are adjacent, rows
@@ -1202,11 +1236,18 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         LDS_HIP(hipGetLastError());
     }
     if (ns > 0) {
-        if (bucketed)
+        if (bucketed) {
             k_bucket_permute<<<(unsigned)((int64_t)1 << bits), kT, ((size_t)1 << rowbits) * sizeof(int64_t), s>>>(
                 bkeys.p, bstart.p, bucket_n.p, vb, rowbits, n, rstart.p, g.int_of.p, g.rowptr.p, g.col.p);
-        else
+            if (h.over > 0) {
+                LDS_HIP(hipGetLastError());
+                k_over_permute<<<grid_for((int64_t)h.over_keys, kT), kT, 0, s>>>(
+                    bkeys.p, over.p, h.over, bstart.p, over_off.p, (int64_t)h.over_keys, bucket_n.p, vb, rowbits,
+                    rstart.p, g.int_of.p, g.rowptr.p, g.col.p);
+            }
+        } else {
             k_permute<<<grid_for(ns, kT), kT, 0, s>>>(skeys.p, ns, vb, rstart.p, g.int_of.p, g.rowptr.p, g.col.p);
+        }
         LDS_HIP(hipGetLastError());
     }
     bkeys.release();
