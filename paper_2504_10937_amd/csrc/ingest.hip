@@ -65,11 +65,11 @@ __global__ void k_compact(const uint64_t* keys, const uint32_t* flag, const uint
 // given very often, ids that agree in their low bits) are sorted together, by
 // bucket and the 32 bits of a key, at what the keys of these buckets alone cost
 // (98M random pairs 8.6 ms, with a vertex of 1M neighbours besides 11.0; a full
-// sort of everything for its sake, after the buckets, took 23.4).  Compared with the full sort of both ids (6 passes, then flags, a
-// scan and a compaction over all keys) the ingest of 2.1e8 keys went from 20 to
-// 12.2 ms (the buckets themselves 1.6), of 4e7 keys from 4.8 to 2.3.  Bound:
-// HBM (16 B per key and pass, 12 for the buckets) and, in the buckets, LDS
-// atomics.
+// sort of everything for its sake, after the buckets, took 23.4).  Compared
+// with the full sort of both ids (6 passes, then flags, a scan and a compaction
+// over all keys) the ingest of 2.1e8 keys went from 20 to 12.2 ms (the buckets
+// themselves 1.6), of 4e7 keys from 4.8 to 2.3.  Bound: HBM (16 B per key and
+// pass, 12 for the buckets) and, in the buckets, LDS atomics.
 constexpr int kBucketSmall = 8192;   // keys of a bucket for a workgroup with half a CU's LDS
 constexpr int kBucketLarge = 24576;  // and for one with all of it
 constexpr int kBucketRowBits = 12;   // most rows of a bucket: 2^12 counters in LDS
@@ -1075,8 +1075,6 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
     LDS_HIP(hipMemsetAsync(found.p, 0, sizeof(Found), s));
     DBuf<int32_t> deg_orig;
     DBuf<int64_t> rstart;
-    deg_orig.alloc(n, s);
-    rstart.alloc(n, s);
     // 1a. by buckets of rows: low bits of the row that number the buckets, so that
     //     a bucket holds 2048 to 4096 keys in the mean, at most 2^12 rows, and
     //     a key's other bits fit 32; graphs past 2^16 such buckets and inputs
@@ -1098,6 +1096,10 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         count.alloc(1, s);
         const uint64_t* keys = bucket_pairs(ps, pd, npairs, n, vb, bits, strict, ka.p, kb.p, count.p,
                                             &found.p->err, s);
+        dsrc.release();
+        ddst.release();
+        deg_orig.alloc(n, s);
+        rstart.alloc(n, s);
         bstart.alloc(buckets + 1, s);
         k_bucket_starts<<<grid_for(buckets + 1, kT), kT, 0, s>>>(keys, count.p, 2 * vb - bits, buckets, bstart.p);
         LDS_HIP(hipGetLastError());
@@ -1166,6 +1168,8 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
             tmp.alloc(nk, s);
             k_canon<<<grid_for(npairs, kT), kT, 0, s>>>(ps, pd, npairs, n, vb, strict, keys.p, &found.p->err);
             LDS_HIP(hipGetLastError());
+            dsrc.release();
+            ddst.release();
             radix_sort_u64(keys, nullptr, nk, 0, 2 * vb, tmp, nullptr, s);
             DBuf<uint32_t> flag;
             flag.alloc(nk, s);
@@ -1181,6 +1185,8 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         }
         // degrees from the row runs (no atomics)
         DBuf<int64_t> rend;
+        deg_orig.alloc(n, s);
+        rstart.alloc(n, s);
         rend.alloc(n, s);
         if (n) {
             LDS_HIP(hipMemsetAsync(rstart.p, 0, n * sizeof(int64_t), s));
@@ -1197,8 +1203,6 @@ void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const 
         degrees_found(deg_orig.p);
         read_found();
     }
-    dsrc.release();
-    ddst.release();
     g.m = ns / 2;
     check_edge_count(g.m);
 
