@@ -28,6 +28,7 @@
 // integers per workgroup and reduced once after the last iteration.
 #include "batch.hpp"
 #include "graph.hpp"
+#include "loadcode.hpp"
 #include "push.hpp"
 #include "wave.hpp"
 
@@ -47,16 +48,6 @@ namespace lds {
 namespace {
 
 typedef unsigned __int128 u128;
-
-// the windows of an iteration's 16-bit load codes (see qcode), in one register:
-// bases of the loads read and written, mantissa bits
-struct Codes {
-    uint32_t x;
-    __host__ __device__ Codes(int in = 0, int out = 0, int mant = 11) : x((uint32_t)(in | (out << 8) | (mant << 16))) {}
-    __device__ inline int in() const { return (int)(x & 255u); }
-    __device__ inline int out() const { return (int)((x >> 8) & 255u); }
-    __device__ inline int mant() const { return (int)(x >> 16); }
-};
 
 struct SweepArgs {
     const int32_t* rid;
@@ -113,27 +104,6 @@ __device__ inline uint64_t readlane64(uint64_t v, int lane) {
     const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, lane);
     const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
     return ((uint64_t)hi << 32) | lo;
-}
-
-// 16-bit monotone code of a load numerator: a pseudo-float of `mant` mantissa
-// bits whose exponents count from `base`, the position of the leading one of
-// D_i / 2, so the code is one of the load r = A / D_i and the same window of
-// loads, 2^(16 - mant) octaves from 1/2, serves every iteration.  Numerators
-// below it have code 0, those past it 65535.  A < A' implies qcode(A) <=
-// qcode(A'), so different codes decide a comparison of packed keys exactly and
-// equal codes fall back to the 64-bit keys.  The code array is a quarter of
-// the key array, so the gathered working set stays in the L2 caches far more
-// often.  11 mantissa bits cover any load (2^31); 12 are taken where no vertex
-// has 2^16 patterns.  A tie costs its batch a wait for the keys, and each bit
-// halves them: 195M clique slots took 404 us with 10 bits and any exponent, 374
-// with this code and 361 when ties were not looked up; 206M edge slots 822,
-// 795 and 773.
-__device__ inline uint16_t qcode(uint64_t A, int base, int mant) {
-    A |= 1;  // zero: below any window
-    const int z = __clzll(A);
-    const uint32_t top = (uint32_t)((A << z) >> 32) >> (31 - mant);  // leading one and mantissa
-    const int c = ((62 - z - base) << mant) + (int)top;
-    return (uint16_t)min(max(c, 0), 65535);
 }
 
 // the h-1 other vertices of the pattern stored at a slot; the slot arrays
@@ -962,8 +932,7 @@ uint64_t denom(int mode, int64_t i) { return fw_denom(mode, i); }
 // the codes of iteration i's sweep (i = 0: of the initial loads)
 Codes codes_of(const Graph& g, int mode, int64_t i) {
     const int64_t most = mode == 2 ? g.max_deg : mode == 3 ? g.t_max : g.q_max;
-    auto base = [&](int64_t k) { return 62 - __builtin_clzll(denom(mode, k)); };
-    return Codes(base(i > 0 ? i - 1 : 0), base(i), most < (int64_t)1 << 16 ? 12 : 11);
+    return Codes(code_base(mode, denom(mode, i > 0 ? i - 1 : 0)), code_base(mode, denom(mode, i)), code_mant(most));
 }
 
 template <int H, bool HEAVY, bool PK, int W>

@@ -7,6 +7,7 @@
 
 #include "graph.hpp"
 #include "kept.hpp"
+#include "loadcode.hpp"
 #include "wave.hpp"
 
 namespace lds {
@@ -79,7 +80,39 @@ static void row_slots() {
     EXPECT(wave::rows_at_once(((int64_t)1 << 31) - 1) == 64);
 }
 
+// codes of loads: monotone, and for the loads about a lone pattern's even split
+// (1/h each) told apart to a part in 2^10, at any iteration
+static void load_codes() {
+    for (int mode : {2, 3, 4}) {
+        for (int64_t i : {0, 1, 2, 5, 10, 30, 31, 32, 99, 100, 199, 1000, 20000}) {
+            const uint64_t D = fw_denom(mode, i);
+            for (int64_t most : {(int64_t)1, (int64_t)65535, (int64_t)65536, (int64_t)INT32_MAX}) {
+                const int base = code_base(mode, D), mant = code_mant(most);
+                EXPECT(mant == 11 || mant == 12);
+                EXPECT(base >= 0 && base < 256 && Codes(base, base, mant).in() == base &&
+                       Codes(base, base, mant).mant() == mant);
+                int last = -1;
+                for (uint64_t A = 0; A <= 64 * D && A < 1000000; A += A < 4096 ? 1 : 1 + A / 5000) {
+                    const int c = qcode(A, base, mant);
+                    EXPECT(c >= last);
+                    last = c;
+                }
+                // from the even split on (triangles: a tenth below it): a step of 1/1000 apart
+                for (int k = mode == 3 ? 900 : 1000; k < 1200; ++k) {
+                    const uint64_t a = D * k / (1000 * mode), b = D * (k + 1) / (1000 * mode);
+                    if (a >= 64 && (b - a) * 1024 >= b) EXPECT(qcode(b, base, mant) > qcode(a, base, mant));
+                }
+                // a quarter of the initial load of the vertex of the most patterns is in the window
+                const uint64_t A0 = (uint64_t)most * (D / mode) / 4;
+                if ((unsigned __int128)most * (D / mode) < ((unsigned __int128)1 << 62))
+                    EXPECT(qcode(A0, base, mant) < 65535);
+            }
+        }
+    }
+}
+
 int main() {
+    load_codes();
     row_slots();
     launches();
     edge_count();
