@@ -62,7 +62,7 @@ __device__ inline uint64_t fw_inc(int h, int i) {  // D_i - D_{i-1}
 // words are there or not: the graphs that run alone in k_fw_one have few words
 // a wave (446 slots 2.03 us an iteration with 8, 1.54 with 4; 2.6k 2.78 and
 // 2.49; 10k 4.65 and 4.46; 16k 6.42 and 6.51), the largest of a batch, which
-// bound its time, many (768 graphs 9.6 and 9.9 ms).
+// bound its time, many.
 constexpr int kBatchWords = 8, kOneWords = 4;
 constexpr int kRows = 4;   // rows per thread whose bounds stay in registers over the iterations
 
@@ -362,8 +362,11 @@ BItem make_item(Graph& g, int mode, int iters, int lds_vertices) {
 
 // Whether fw_run gives the graph to one workgroup for all iterations: its
 // keys fit LDS and a sweep launch would take longer than the workgroup's pass
-// over the slots.  An iteration takes one workgroup 2.0 us at 446 slots, 2.8 at 2.6k,
-// 4.7 at 10k and 9 at 24k; a sweep launch takes 6.7, 7.2, 7.4 and 7.5 us.
+// over the slots and rows.  Microseconds an iteration of a call, by one
+// workgroup and by sweeps: 1500 vertices with 4.0k slots 3.6 and 6.0, 10.0k 4.9
+// and 6.1, 12.0k 5.8 and 6.1, 14.0k 6.7 and 6.0; 6000 vertices with 10.0k slots
+// 6.1 and 6.4, 12.0k 7.2 and 6.3; triangles of 300 vertices with 11.8k 6.2 and
+// 6.0; a clique of 120 (14.3k) 5.4 and 5.7.
 namespace {
 constexpr size_t kMaxLds = 160 * 1024 - 2048;  // dynamic LDS of a workgroup, beside the reductions
 size_t one_lds(const Graph& g, const SweepPlan& p) {
@@ -374,7 +377,7 @@ size_t one_lds(const Graph& g, const SweepPlan& p) {
 bool fw_fits_one(const Graph& g, int mode) {
     if (mode != 2 && mode != 3) return false;
     const SweepPlan& p = plan_of(g, mode);
-    return g.n > 0 && g.n <= kOneVertices && p.nrows > 0 && p.nslots <= kOneSlots && p.wdesc.p &&
+    return g.n > 0 && g.n <= kOneVertices && p.nrows > 0 && p.nslots + g.n / 4 <= kOneSlots && p.wdesc.p &&
            one_lds(g, p) <= kMaxLds;
 }
 

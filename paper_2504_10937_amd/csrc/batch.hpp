@@ -47,7 +47,9 @@ int64_t batch_cost(const Graph& g, int mode, int iters);
 // (device, 4 * iters words, or nullptr) receives the exact gap sums, and the
 // result is in K[iters & 1]
 constexpr int32_t kOneVertices = 8192;   // two key buffers of 64 KB in LDS
-constexpr int64_t kOneSlots = 16384;
+// what a workgroup sweeps in the time of a sweep launch: slots, and a quarter
+// for each vertex
+constexpr int64_t kOneSlots = 12288;
 bool fw_fits_one(const Graph& g, int mode);
 void fw_run_one(Graph& g, int mode, int iters, uint64_t* sums, hipStream_t s);
 void batch_build(Batch& b, hipStream_t s);  // sizes buffers, builds the item table, captures the hipGraph

@@ -999,8 +999,6 @@ void collect_groups(Graph& gg, int mode, int iters, hipStream_t s, Map map, std:
     }
 }
 
-constexpr int64_t kRefineSlots = 16384;  // slots a workgroup sweeps in the time of a sweep launch
-
 // FW + ExtractSG on G[vs]: the stable groups of the induced subgraph
 // Alg. 5 re-runs FW + ExtractSG on G[S] for a popped candidate S that is not
 // self-densest.  The candidates of one round go through the batched FW
@@ -1041,9 +1039,9 @@ void refine_batch(Ctx& c, const std::vector<const std::vector<int32_t>*>& cands,
         // the graphs of the batched kernel run side by side, one workgroup
         // each; the others one after another on the whole chip, at the price
         // of their launches: a graph goes there when its slots would keep a
-        // workgroup longer than all those launches
+        // workgroup longer than all those launches (see fw_fits_one)
         bt.tune.max_kernel_cost =
-            std::min<int64_t>(bt.tune.max_kernel_cost, (int64_t)nb * kRefineSlots * std::max(c.iters, 1));
+            std::min<int64_t>(bt.tune.max_kernel_cost, (int64_t)nb * kOneSlots * std::max(c.iters, 1));
         batch_build(bt, c.s);
         batch_run(bt, c.s);
         LDS_HIP(hipStreamSynchronize(c.s));
