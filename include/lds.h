@@ -202,8 +202,10 @@ lds_status lds_sg_scan_info(lds_graph g, lds_mode mode, int64_t* out);
 /* GPU time of the sweep launches of the last lds_frank_wolfe call for this
  * graph and mode, from HIP events recorded on that call's stream right before
  * the first and after the last sweep launch (waits for the end event).
- * *launches = number of sweep launches (= iters when the graph has
- * patterns).  Any output may be NULL. */
+ * *launches = number of sweeps between them (= iters when the graph has
+ * patterns): one launch each, except that a graph small enough for one
+ * workgroup runs all of them in a single launch, and that the hub push and the
+ * heavy rows add a finishing launch to a sweep.  Any output may be NULL. */
 lds_status lds_fw_elapsed(lds_graph g, lds_mode mode, float* ms, int32_t* launches);
 
 /* Shape of the sweep over incidence slots (Alg. 1 / Alg. 6 pull form):

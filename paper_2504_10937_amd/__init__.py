@@ -316,7 +316,8 @@ def lds_sg_scan_info(g, mode):
 
 
 def lds_fw_elapsed(g, mode):
-    """(GPU ms of the sweep launches of the last FW run, number of launches)."""
+    """(GPU ms of the sweeps of the last FW run, number of sweeps: one per
+    iteration, also where a small graph runs all of them in one launch)."""
     ms = ctypes.c_float()
     k = ctypes.c_int32()
     _check(load().lds_fw_elapsed(g.handle, mode, ctypes.byref(ms), ctypes.byref(k)))

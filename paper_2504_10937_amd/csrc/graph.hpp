@@ -190,7 +190,7 @@ struct FwState {
     DBuf<uint32_t> push_part;    // hub push: per sweep workgroup, the hub rows' win counts (two 16-bit halves a word)
     std::vector<double> gap, lb, fval;  // per iteration, filled on request: gap, lower bound, sum r^2 at r^(i-1)
     hipEvent_t ev[2] = {nullptr, nullptr};  // around the sweep launches of the last run
-    int launches = 0;
+    int launches = 0;                        // sweeps of the last run (lds_fw_elapsed)
     bool ran = false;            // keys hold the result of a completed run of `iters` iterations
     bool timed = false;          // ev[] bracket the last run (plain runs only)
     size_t device_bytes() const {
