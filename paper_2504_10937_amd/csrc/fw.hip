@@ -971,6 +971,12 @@ unsigned sweep_grid() {
     return (unsigned)(cus * kWgPerCU);
 }
 
+}  // namespace
+
+int64_t sweep_waves() { return (int64_t)sweep_grid() * kWaves; }
+
+namespace {
+
 // workgroups that have a chunk, piece or part to sweep (at least one)
 unsigned sweep_blocks(const SweepPlan& p) {
     const int64_t work = p.n_chunks + (p.n_push > 0 ? p.n_ppieces : p.n_pieces) + p.heavy.n_parts;

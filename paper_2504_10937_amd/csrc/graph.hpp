@@ -275,6 +275,7 @@ struct Graph {
 // ingest.hip
 void build_graph(Graph& g, int64_t n, int64_t npairs, const int32_t* src, const int32_t* dst, bool on_device,
                  bool strict, hipStream_t s);
+int64_t sweep_waves();  // waves of the device's sweep launch
 void build_sweep_plan(SweepPlan& p, hipStream_t s, int64_t n_vertices = 0);  // needs h, nrows, nslots, rowptr, pay, rowid;
                                                                              // n_vertices > 0 allows the 2D heavy part (edges)
 void sort_rows(Graph& g, hipStream_t s);             // CSR rows ascending (triangle listing)

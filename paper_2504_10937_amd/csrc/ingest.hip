@@ -3,6 +3,7 @@
 // plan (hub rows, row-aligned chunks, word offsets and row-start flags) that
 // the Frank-Wolfe kernels stream over.
 
+#include "chunks.hpp"
 #include "graph.hpp"
 
 #include <algorithm>
@@ -845,30 +846,6 @@ int64_t build_heavy(SweepPlan& p, int64_t n, hipStream_t s) {
 
 }  // namespace
 
-// Target slots of a chunk for a plan with `slots` slots outside the hub rows
-// and `pieces` hub pieces.  A sweep runs in rounds (every one of its kSweepWaves
-// waves takes one chunk or piece), so the size is the smallest that fills a
-// whole number of rounds.  A round costs a chain of dependent reads, then a
-// batch of 256 slots (512 from 2^22 slots on) at a time: up to kOneBatch slots
-// (with the part of the last row that a chunk takes beyond its target) is the
-// best size while there are few rounds, kTwoBatches once there are many, and
-// tiny plans use kChunkMin, to have more waves in flight.  Measured per sweep
-// in us, by size: 37M slots 1024 236, 960 221, 384 236; 4.4M 1024 44, 768 35,
-// 384 33, 256 40; 2.9M 512 18.9, 384 17.2, 256 20.2; 1.6M 512 17.0, 384 15.5,
-// 256 20.5; 24k 512 8.1, 256 6.8, 128 5.9, 64 6.4.
-// LDS_SWEEP_CHUNK (a multiple of 64 up to kChunk) overrides.
-constexpr int64_t kSweepWaves = 4096;
-constexpr int kChunkMin = 128;
-constexpr int kOneBatch = 448;
-constexpr int kTwoBatches = 960;
-int64_t chunk_slots(int64_t slots, int64_t pieces) {
-    if (slots <= kSweepWaves * kChunkMin) return kChunkMin;
-    const int64_t per = slots <= 3 * kSweepWaves * kOneBatch ? kOneBatch : kTwoBatches;
-    const int64_t rounds = (slots / per + pieces + kSweepWaves - 1) / kSweepWaves;
-    const int64_t chunks = std::max<int64_t>(1, rounds * kSweepWaves - pieces);
-    return std::max<int64_t>(kChunkMin, (slots + chunks - 1) / chunks + 63);
-}
-
 // plans with fewer slots cut their hub rows into shorter pieces
 constexpr int64_t kPieceSlots = (int64_t)1 << 22;
 constexpr int kPieceSmall = 512;
@@ -981,7 +958,9 @@ void build_sweep_plan(SweepPlan& p, hipStream_t s, int64_t n_vertices) {
     LDS_HIP(hipMemcpyAsync(&base, p.rp + p.n_hub, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     LDS_HIP(hipStreamSynchronize(s));
     const int64_t nonhub = p.nslots - base;
-    p.chunk = (int)env_int("LDS_SWEEP_CHUNK", chunk_slots(nonhub, p.n_push > 0 ? p.n_ppieces : p.n_pieces));
+    // (LDS_SWEEP_CHUNK overrides: a multiple of 64 up to kChunk)
+    p.chunk = (int)env_int("LDS_SWEEP_CHUNK",
+                           chunk_slots(nonhub, p.n_push > 0 ? p.n_ppieces : p.n_pieces, sweep_waves()));
     p.chunk = std::min(std::max(64, p.chunk / 64 * 64), kChunk);
     p.n_chunks = (nonhub + p.chunk - 1) / p.chunk;
     p.chunk_row.alloc(p.n_chunks + 1, s);

@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <vector>
 
+#include "chunks.hpp"
 #include "graph.hpp"
 #include "kept.hpp"
 #include "loadcode.hpp"
@@ -111,7 +112,22 @@ static void load_codes() {
     }
 }
 
+// chunks (a multiple of 64 slots, at most kChunk) and pieces fill whole rounds
+// of whatever number of waves sweeps them: no more rounds than the largest
+// chunks of the size's class need
+static void chunk_rounds() {
+    for (int64_t waves : {512, 2048, 3072, 4096})
+        for (int64_t pieces : {(int64_t)0, waves / 3})
+            for (int64_t k : {1, 2, 3, 5}) {
+                const int64_t slots = (k * waves - pieces) * kOneBatch - 1;
+                const int64_t c = std::min<int64_t>(chunk_slots(slots, pieces, waves) / 64 * 64, kChunk);
+                const int64_t rounds = ((slots + c - 1) / c + pieces + waves - 1) / waves;
+                EXPECT(c >= kChunkMin && rounds <= k);
+            }
+}
+
 int main() {
+    chunk_rounds();
     load_codes();
     row_slots();
     launches();
