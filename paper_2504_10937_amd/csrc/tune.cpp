@@ -57,7 +57,8 @@ std::string tune_signature(const std::vector<Graph*>& gs, const std::vector<int>
         ne += modes[i] == 2 ? 1 : 0;
     }
     std::ostringstream o;
-    o << "v2/count=" << log2i((double)gs.size()) << "/cost=" << log2i(cost) << "/maxn=" << log2i((double)maxn)
+    // the version changes with the batched kernel, whose timings the entries are
+    o << "v3/count=" << log2i((double)gs.size()) << "/cost=" << log2i(cost) << "/maxn=" << log2i((double)maxn)
       << "/edgefrac=" << (gs.empty() ? 0 : (int)(4 * ne / (int64_t)gs.size())) << "/cus=" << cus();
     return o.str();
 }
