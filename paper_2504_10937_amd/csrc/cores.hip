@@ -122,49 +122,44 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
 // to its lanes, U per lane in flight, so that short rows fill the wave and
 // the dependent reads of many slots overlap: with a wave per vertex and one
 // slot per lane, the peel of 1M vertices of 16 slots took 7.4 ms, now 2.3 ms.
-// The numbers are 32-bit: vertices with 2^31 slots together are taken one at a
-// time (one has fewer).  range(v, q0, q1) gives a vertex's slots, body(q, in)
+// The numbers are 32-bit: most (rows_at_once) is the vertices whose slots they
+// hold in any case.  range(v, q0, q1) gives a vertex's slots, body(q, in)
 // handles U slots per lane.  pre: 64 words of LDS of the wave's own.
 template <int U, class RANGE, class BODY>
-__device__ inline void walk_slots(const int32_t* f, int32_t fc, int64_t gw, int64_t nwave, uint32_t* pre, RANGE range,
-                                  BODY body) {
+__device__ inline void walk_slots(const int32_t* f, int32_t fc, int64_t gw, int64_t nwave, int most, uint32_t* pre,
+                                  RANGE range, BODY body) {
     const int lane = threadIdx.x & 63;
-    const int64_t per = max<int64_t>(1, min<int64_t>(64, (fc + nwave - 1) / nwave));
+    const int per = max(1, (int)min<int64_t>(most, (fc + nwave - 1) / nwave));
     for (int64_t base = gw * per; base < fc; base += nwave * per) {
         int64_t q0 = 0, q1 = 0;
         if (lane < per && base + lane < fc) range(f[base + lane], q0, q1);
-        const int64_t len = q1 - q0;
-        const int64_t sum = wave::scan(len, (int64_t)0, [](int64_t a, int64_t b) { return a + b; });
-        const int rows = wave::rows_at_once(wave::lane63(sum));
-        for (int e0 = 0; e0 < 64; e0 += rows) {
-            // inclusive counts, of all the rows or of row e0 alone
-            const uint32_t inc = (uint32_t)(rows == 64 ? sum : lane >= e0 ? wave::lane_of(len, e0) : 0);
-            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-            pre[lane] = inc;
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const int64_t from = q0 - (int64_t)(inc - (uint32_t)len);  // slot of number c: from + c
-            for (uint32_t c0 = 0; c0 < total; c0 += 64 * U) {
-                int64_t q[U];
-                bool in[U];
+        const uint32_t inc =
+            (uint32_t)wave::scan(q1 - q0, (int64_t)0, [](int64_t a, int64_t b) { return a + b; });
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        pre[lane] = inc;
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int64_t from = q0 - (int64_t)(inc - (uint32_t)(q1 - q0));  // slot of number c: from + c
+        for (uint32_t c0 = 0; c0 < total; c0 += 64 * U) {
+            int64_t q[U];
+            bool in[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const uint32_t c = c0 + 64 * u + (uint32_t)lane;
-                    in[u] = c < total;
-                    int e = 0;  // the vertex of slot c: first e with pre[e] > c
-                    if (per > 1) {
+            for (int u = 0; u < U; ++u) {
+                const uint32_t c = c0 + 64 * u + (uint32_t)lane;
+                in[u] = c < total;
+                int e = 0;  // the vertex of slot c: first e with pre[e] > c
+                if (per > 1) {
 #pragma unroll
-                        for (int st = 32; st > 0; st >>= 1)
-                            if (pre[e + st - 1] <= c) e += st;
-                    }
-                    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)from, e, 64);
-                    const int hi = __shfl((int)(from >> 32), e, 64);
-                    q[u] = (int64_t)(((uint64_t)(uint32_t)hi << 32) | lo) + (int64_t)c;
+                    for (int st = 32; st > 0; st >>= 1)
+                        if (pre[e + st - 1] <= c) e += st;
                 }
-                body(q, in);
+                const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)from, e, 64);
+                const int hi = __shfl((int)(from >> 32), e, 64);
+                q[u] = (int64_t)(((uint64_t)(uint32_t)hi << 32) | lo) + (int64_t)c;
             }
-            __builtin_amdgcn_wave_barrier();  // pre is rewritten by the next vertices
+            body(q, in);
         }
+        __builtin_amdgcn_wave_barrier();  // pre is rewritten by the next vertices
     }
 }
 
@@ -183,7 +178,7 @@ constexpr int32_t kTailMax = 1 << 13;
 constexpr int kTailU = 4;  // slots per lane in flight in the adjacency walks
 
 template <bool TRI>
-__global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_t na, int32_t k, int32_t* loc,
+__global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_t na, int32_t k, int most, int32_t* loc,
                                                       const int64_t* rowptr, const int32_t* col,
                                                       const int32_t* row_of, const int64_t* rp, const int32_t* py,
                                                       const int32_t* tos, uint32_t* talive, const int32_t* cnt,
@@ -262,7 +257,7 @@ __global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_
             for (int32_t i = tid; i < fc; i += kTailT) fvert[i] = act[lfr[f][i]];
             __syncthreads();
             walk_slots<kTailU>(
-                fvert, fc, wv, kTailT / 64, pre[wv],
+                fvert, fc, wv, kTailT / 64, most, pre[wv],
                 [&](int32_t v, int64_t& q0, int64_t& q1) {
                     const int32_t r = TRI ? row_of[v] : v;
                     if (r < 0) return;
@@ -356,6 +351,7 @@ struct PeelArgs {
     unsigned* bar;  // grid barrier counter
     int64_t n;
     int32_t na, k, tail_max;
+    int32_t most;  // of rows_at_once
 };
 
 // Pushes of a workgroup collected in LDS (those past its kPushBuf entries go
@@ -458,7 +454,7 @@ __global__ __launch_bounds__(kPT) void k_peel_grid(PeelArgs a) {
                     push(nx, slot, w);
             };
             walk_slots<kWalkU>(
-                f, fc, gw, nwave, pre[threadIdx.x >> 6],
+                f, fc, gw, nwave, a.most, pre[threadIdx.x >> 6],
                 [&](int32_t v, int64_t& q0, int64_t& q1) {
                     const int32_t r = TRI ? a.row_of[v] : v;
                     if (r < 0) return;
@@ -609,6 +605,7 @@ void core_numbers_gpu(Graph& g, int mode, const uint8_t* alive, int32_t* core, h
     LDS_HIP(hipMemcpyAsync(h, ctr.p, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     LDS_HIP(hipStreamSynchronize(s));
     int32_t na = h[C_NA], k = 0;
+    const int most = wave::rows_at_once(mode == 2 ? g.max_deg : g.t_max);
     if (na > kTailMax) {  // the levels with many vertices: one cooperative launch
         static int cus = 0, per[2] = {0, 0};
         if (!cus) {
@@ -655,6 +652,7 @@ void core_numbers_gpu(Graph& g, int mode, const uint8_t* alive, int32_t* core, h
         pa.na = na;
         pa.k = 0;
         pa.tail_max = kTailMax;
+        pa.most = most;
         void* kargs[] = {&pa};
         LDS_HIP(hipLaunchCooperativeKernel(mode == 2 ? (const void*)k_peel_grid<false> : (const void*)k_peel_grid<true>,
                                            dim3((unsigned)grid), dim3(kPT), kargs, 0, s));
@@ -673,10 +671,10 @@ void core_numbers_gpu(Graph& g, int mode, const uint8_t* alive, int32_t* core, h
         k_fill_i32<<<grid_for(n, kT), kT, 0, s>>>(loc.p, n, -1);
         k_set<<<1, 1, 0, s>>>(ctr.p + 7, 0);
         if (mode == 2)
-            k_peel_tail<false><<<1, kTailT, 0, s>>>(act.p, na, k, loc.p, g.rowptr.p, g.col.p, nullptr, nullptr,
+            k_peel_tail<false><<<1, kTailT, 0, s>>>(act.p, na, k, most, loc.p, g.rowptr.p, g.col.p, nullptr, nullptr,
                                                     nullptr, nullptr, nullptr, cnt.p, core, ctr.p + 7);
         else
-            k_peel_tail<true><<<1, kTailT, 0, s>>>(act.p, na, k, loc.p, nullptr, nullptr, tp.own_row_of.p, tp.rp,
+            k_peel_tail<true><<<1, kTailT, 0, s>>>(act.p, na, k, most, loc.p, nullptr, nullptr, tp.own_row_of.p, tp.rp,
                                                    tp.py, tp.own_tos.p, talive.p, cnt.p, core, ctr.p + 7);
         LDS_HIP(hipGetLastError());
         LDS_CHECK(d2h_i32(ctr.p + 7, s) == 0, ST_DEVICE, "core peeling: no progress");

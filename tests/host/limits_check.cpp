@@ -70,15 +70,15 @@ static void launches() {
         }
 }
 
-// slots of 64 rows numbered in 32 bits by steps of 64 lanes and 4 a lane: the
-// last step's numbers do not wrap
+// slots of up to 64 rows numbered in 32 bits by steps of 64 lanes and 4 a lane:
+// the last step's numbers do not wrap
 static void row_slots() {
-    for (int64_t slots : {(int64_t)1, (int64_t)INT32_MAX, (int64_t)1 << 31, ((int64_t)1 << 32) - 256,
-                          ((int64_t)1 << 32) + 41664}) {
-        const int64_t most = wave::rows_at_once(slots) == 64 ? slots : (int64_t)INT32_MAX;
-        EXPECT(most + 2 * 256 <= (int64_t)UINT32_MAX);
+    for (int64_t longest : {(int64_t)0, (int64_t)1, (int64_t)1 << 24, ((int64_t)1 << 25) - 1, (int64_t)1 << 25,
+                            (int64_t)1 << 30, (int64_t)INT32_MAX}) {
+        const int64_t rows = wave::rows_at_once(longest);
+        EXPECT(rows >= 1 && rows <= 64 && rows * longest + 2 * 256 <= (int64_t)UINT32_MAX);
+        EXPECT(rows == 64 || longest >= (int64_t)1 << 25);
     }
-    EXPECT(wave::rows_at_once(((int64_t)1 << 31) - 1) == 64);
 }
 
 // codes of loads: monotone, and for the loads about a lone pattern's even split
