@@ -168,7 +168,7 @@ __device__ inline void walk_slots(const int32_t* f, int32_t fc, int64_t gw, int6
 // Pruning rule 2): the same levels, frontiers and cascades, separated by
 // workgroup barriers.  The remaining vertices get local ids (their index in
 // the remaining list; loc maps a vertex to it, -1 for every other vertex), and
-// their counts, peeled flags, remaining lists and frontiers live in LDS (144 KB), so a
+// their counts, peeled flags, remaining lists and frontiers live in LDS (140 KB), so a
 // level touches global memory only to walk the frontier's adjacency (and, for
 // triangles, to kill each triangle once).  Every level assigns a vertex or
 // jumps to a larger count, so the loops are bounded by the number of

@@ -13,14 +13,15 @@
 // other two vertices.  Rows are "compact": only vertices with at least one
 // slot, ordered by slot count (descending), mapped to internal ids by rowid.
 //
-// Sweep plan.  Rows with more than kChunk slots are hubs, one workgroup
-// each.  The remaining rows are cut into chunks of a target size C <= kChunk
-// (SweepPlan::chunk): chunk c holds the rows whose first slot lies in
-// [c*C, (c+1)*C) (relative to the first non-hub slot), so a chunk spans
-// fewer than 2*kChunk slots and always starts at a row start.  Each chunk is
-// one wave64.  The decision bits of one
-// iteration are stored per chunk from a 64-bit-word-aligned offset (cwo),
-// followed by the hub rows (hwo); a per-chunk "head" bitmap marks row starts.
+// Sweep plan.  Rows with more than kChunk slots are hubs, cut into
+// word-aligned pieces of at most SweepPlan::piece slots.  The remaining rows
+// are cut into chunks of a target size C <= kChunk (SweepPlan::chunk, see
+// chunks.hpp): chunk c holds the rows whose first slot lies in [c*C, (c+1)*C)
+// (relative to the first non-hub slot), so a chunk spans fewer than 2*kChunk
+// slots and always starts at a row start.  Each piece and each chunk is one
+// wave64's.  The decision bits of one iteration are stored per chunk from a
+// 64-bit-word-aligned offset (cwo), followed by the hub rows (hwo); a
+// per-chunk "head" bitmap marks row starts.
 #pragma once
 #include <memory>
 
