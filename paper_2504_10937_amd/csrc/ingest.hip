@@ -3,6 +3,7 @@
 // plan (hub rows, row-aligned chunks, word offsets and row-start flags) that
 // the Frank-Wolfe kernels stream over.
 
+#include "bucketset.hpp"
 #include "chunks.hpp"
 #include "graph.hpp"
 
@@ -97,8 +98,9 @@ __device__ inline void bucket_rows(const uint64_t* keys, int64_t q, int64_t s0, 
     constexpr int PER = CAP / NT;
     constexpr uint32_t kEmpty = 0xffffffffu;  // no key: both ids would be all ones, which n never is
     const int R = 1 << rowbits, t = threadIdx.x, lane = t & 63, w = t >> 6;
-    int size = 1024;  // of the table: at least twice the keys, or all of it
-    while (size < 2 * len && size < TAB) size <<= 1;
+    int bits = 10;  // of the table: at least twice the keys, or all of it
+    while ((1 << bits) < 2 * len && (1 << bits) < TAB) ++bits;
+    const int size = 1 << bits;
     const uint32_t slot = (uint32_t)size - 1;
     for (int i = t; i < size; i += NT) tab[i] = kEmpty;
     for (int i = t; i < R; i += NT) cnt[i] = 0;
@@ -112,7 +114,7 @@ __device__ inline void bucket_rows(const uint64_t* keys, int64_t q, int64_t s0, 
     for (int k = 0; k < PER; ++k) {
         rank[k] = kEmpty;  // not a row's entry (no key, or a duplicate)
         if (key[k] == kEmpty) continue;
-        uint32_t p = (key[k] * 2654435769u) >> 8;
+        uint32_t p = bucket_place(key[k], bits);
         for (;; ++p) {  // ends: more than a quarter of the table stays empty
             const uint32_t old = atomicCAS(&tab[p & slot], kEmpty, key[k]);
             if (old == kEmpty) {

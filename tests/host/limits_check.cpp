@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <vector>
 
+#include "bucketset.hpp"
 #include "chunks.hpp"
 #include "graph.hpp"
 #include "kept.hpp"
@@ -126,7 +127,32 @@ static void chunk_rounds() {
             }
 }
 
+// the rows of a bucket that share a neighbour, and the neighbours of one row,
+// start from places of their own: at least a third as many as the keys
+static void bucket_places() {
+    for (int vb : {12, 17, 19, 22, 24, 28}) {
+        const int rows = 1 << std::min(11, 32 - vb);
+        for (uint32_t nb : {0u, 1u, 5u, 1000u, (1u << (vb - 1)) + 3u})
+            for (int by_row : {1, 0}) {
+                const int n = by_row ? rows : 2048;
+                int log2 = 10;
+                while ((1 << log2) < 2 * n) ++log2;
+                std::vector<char> hit((size_t)1 << log2, 0);
+                int places = 0;
+                for (int x = 0; x < n; ++x) {
+                    const uint32_t key = by_row ? ((uint32_t)x << vb) | (nb & ((1u << vb) - 1)) : ((uint32_t)(rows - 1) << vb) | ((nb + x) & ((1u << vb) - 1));
+                    const uint32_t p = bucket_place(key, log2);
+                    EXPECT(p < (uint32_t)1 << log2);
+                    if (!hit[p]) ++places;
+                    hit[p] = 1;
+                }
+                EXPECT(3 * places >= n);
+            }
+    }
+}
+
 int main() {
+    bucket_places();
     chunk_rounds();
     load_codes();
     row_slots();
