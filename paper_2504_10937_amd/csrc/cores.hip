@@ -116,30 +116,62 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
     if (i < n) p[i] = v;
 }
 
-// Walk over the slots of the fc listed vertices by the waves of a phase.  A
-// wave takes up to 64 vertices at a time (fewer when the list would otherwise
-// leave waves without work), numbers their slots consecutively and deals them
-// to its lanes, U per lane in flight, so that short rows fill the wave and
-// the dependent reads of many slots overlap: with a wave per vertex and one
-// slot per lane, the peel of 1M vertices of 16 slots took 7.4 ms, now 2.3 ms.
-// The numbers are 32-bit: most (rows_at_once) is the vertices whose slots they
-// hold in any case.  range(v, q0, q1) gives a vertex's slots, body(q, in)
-// handles U slots per lane.  pre: 64 words of LDS of the wave's own.
-template <int U, class RANGE, class BODY>
-__device__ inline void walk_slots(const int32_t* f, int32_t fc, int64_t gw, int64_t nwave, int most, uint32_t* pre,
-                                  RANGE range, BODY body) {
+// Walk over the slots of fc vertices (vert(i): the i-th) by the waves of a
+// phase.  A wave takes up to 64 vertices at a time (fewer when the list would
+// otherwise leave waves without work).  Rows of kLongRow slots or more, which
+// fill its lanes by themselves, and single vertices are walked one by one; the
+// slots of the short rows together are numbered consecutively and dealt to the
+// lanes.  U slots per lane are in flight either way, so that short rows fill
+// the wave and the dependent reads of many slots overlap: with a wave per
+// vertex and one slot per lane, the peel of 1M vertices of 16 slots took 7.4
+// ms, now 2.3 ms.  (Dealing every row, each slot's row found by a search, took
+// 1.9 ms on a clique of 1500 vertices, now 1.06, and 0.70 on a path of 1000, two
+// of them a round, now 0.55.)  range(v, q0, q1) gives a vertex's slots,
+// body(q, in) handles U slots per lane.  pre: 64 words of LDS of the wave's own.
+constexpr int kLongRow = 128;
+template <int U, class VERT, class RANGE, class BODY>
+__device__ inline void walk_slots(VERT vert, int32_t fc, int64_t gw, int64_t nwave, uint32_t* pre, RANGE range,
+                                  BODY body) {
     const int lane = threadIdx.x & 63;
-    const int per = max(1, (int)min<int64_t>(most, (fc + nwave - 1) / nwave));
+    auto row = [&](int64_t ra, int64_t rb) {
+        for (int64_t c0 = ra + lane; c0 < rb; c0 += 64 * U) {
+            int64_t q[U];
+            bool in[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                q[u] = c0 + 64 * u;
+                in[u] = q[u] < rb;
+            }
+            body(q, in);
+        }
+    };
+    if (fc <= nwave) {  // a vertex a wave at most
+        if (gw < fc) {
+            int64_t q0 = 0, q1 = 0;
+            range(vert(gw), q0, q1);
+            row(q0, q1);
+        }
+        return;
+    }
+    // a wave's vertices, in as many equal turns as 64 lanes need
+    const unsigned all = ((unsigned)fc + (unsigned)nwave - 1) / (unsigned)nwave, turns = (all + 63) / 64;
+    const int per = (int)(turns == 1 ? all : (all + turns - 1) / turns);
     for (int64_t base = gw * per; base < fc; base += nwave * per) {
         int64_t q0 = 0, q1 = 0;
-        if (lane < per && base + lane < fc) range(f[base + lane], q0, q1);
-        const uint32_t inc =
-            (uint32_t)wave::scan(q1 - q0, (int64_t)0, [](int64_t a, int64_t b) { return a + b; });
-        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        if (lane < per && base + lane < fc) range(vert(base + lane), q0, q1);
+        const bool alone = q1 - q0 >= kLongRow;
+        for (uint64_t m = __ballot(alone); m; m &= m - 1) {
+            const int e = __ffsll((long long)m) - 1;
+            row(wave::lane_of(q0, e), wave::lane_of(q1, e));
+        }
+        const uint32_t len = alone ? 0u : (uint32_t)(q1 - q0);
+        if (__ballot(len != 0) == 0) continue;
+        const uint32_t inc = (uint32_t)wave::scan((int64_t)len, (int64_t)0, [](int64_t a, int64_t b) { return a + b; });
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);  // below 64 kLongRow
         pre[lane] = inc;
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        const int64_t from = q0 - (int64_t)(inc - (uint32_t)(q1 - q0));  // slot of number c: from + c
+        const int64_t from = q0 - (int64_t)(inc - len);  // slot of number c: from + c
         for (uint32_t c0 = 0; c0 < total; c0 += 64 * U) {
             int64_t q[U];
             bool in[U];
@@ -148,11 +180,9 @@ __device__ inline void walk_slots(const int32_t* f, int32_t fc, int64_t gw, int6
                 const uint32_t c = c0 + 64 * u + (uint32_t)lane;
                 in[u] = c < total;
                 int e = 0;  // the vertex of slot c: first e with pre[e] > c
-                if (per > 1) {
 #pragma unroll
-                    for (int st = 32; st > 0; st >>= 1)
-                        if (pre[e + st - 1] <= c) e += st;
-                }
+                for (int st = 32; st > 0; st >>= 1)
+                    if (pre[e + st - 1] <= c) e += st;
                 const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)from, e, 64);
                 const int hi = __shfl((int)(from >> 32), e, 64);
                 q[u] = (int64_t)(((uint64_t)(uint32_t)hi << 32) | lo) + (int64_t)c;
@@ -168,7 +198,7 @@ __device__ inline void walk_slots(const int32_t* f, int32_t fc, int64_t gw, int6
 // Pruning rule 2): the same levels, frontiers and cascades, separated by
 // workgroup barriers.  The remaining vertices get local ids (their index in
 // the remaining list; loc maps a vertex to it, -1 for every other vertex), and
-// their counts, peeled flags, remaining lists and frontiers live in LDS (140 KB), so a
+// their counts, peeled flags, remaining lists and frontiers live in LDS (108 KB), so a
 // level touches global memory only to walk the frontier's adjacency (and, for
 // triangles, to kill each triangle once).  Every level assigns a vertex or
 // jumps to a larger count, so the loops are bounded by the number of
@@ -178,7 +208,7 @@ constexpr int32_t kTailMax = 1 << 13;
 constexpr int kTailU = 4;  // slots per lane in flight in the adjacency walks
 
 template <bool TRI>
-__global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_t na, int32_t k, int most, int32_t* loc,
+__global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_t na, int32_t k, int32_t* loc,
                                                       const int64_t* rowptr, const int32_t* col,
                                                       const int32_t* row_of, const int64_t* rp, const int32_t* py,
                                                       const int32_t* tos, uint32_t* talive, const int32_t* cnt,
@@ -187,10 +217,9 @@ __global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_
     __shared__ uint8_t gone[kTailMax];
     __shared__ uint16_t lrem[2][kTailMax];  // remaining local ids, double-buffered
     __shared__ uint16_t lfr[2][kTailMax];   // frontier of a cascade round / the next one
-    __shared__ int32_t fvert[kTailMax];     // vertices of the frontier
     __shared__ uint32_t pre[kTailT / 64][64];
     __shared__ int32_t sc[4];               // [0] frontier, [1] next, [2] minimum, [3] remaining
-    const int tid = threadIdx.x, wv = tid >> 6;
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int32_t i = tid; i < na; i += kTailT) {
         const int32_t v = act[i];
         loc[v] = i;
@@ -254,13 +283,11 @@ __global__ __launch_bounds__(kTailT) void k_peel_tail(const int32_t* act, int32_
             if (tid == 0) sc[1] = 0;
             __syncthreads();
             uint16_t* nx = lfr[f ^ 1];
-            for (int32_t i = tid; i < fc; i += kTailT) fvert[i] = act[lfr[f][i]];
-            __syncthreads();
             walk_slots<kTailU>(
-                fvert, fc, wv, kTailT / 64, most, pre[wv],
+                [&](int64_t i) { return act[lfr[f][i]]; }, fc, wv, kTailT / 64, pre[wv],
                 [&](int32_t v, int64_t& q0, int64_t& q1) {
                     const int32_t r = TRI ? row_of[v] : v;
-                    if (r < 0) return;
+                    if (TRI && r < 0) return;
                     q0 = TRI ? rp[r] : rowptr[r];
                     q1 = TRI ? rp[r + 1] : rowptr[r + 1];
                 },
@@ -351,7 +378,6 @@ struct PeelArgs {
     unsigned* bar;  // grid barrier counter
     int64_t n;
     int32_t na, k, tail_max;
-    int32_t most;  // of rows_at_once
 };
 
 // Pushes of a workgroup collected in LDS (those past its kPushBuf entries go
@@ -454,10 +480,10 @@ __global__ __launch_bounds__(kPT) void k_peel_grid(PeelArgs a) {
                     push(nx, slot, w);
             };
             walk_slots<kWalkU>(
-                f, fc, gw, nwave, a.most, pre[threadIdx.x >> 6],
+                [&](int64_t i) { return f[i]; }, fc, gw, nwave, pre[threadIdx.x >> 6],
                 [&](int32_t v, int64_t& q0, int64_t& q1) {
                     const int32_t r = TRI ? a.row_of[v] : v;
-                    if (r < 0) return;
+                    if (TRI && r < 0) return;
                     q0 = TRI ? a.rp[r] : a.rowptr[r];
                     q1 = TRI ? a.rp[r + 1] : a.rowptr[r + 1];
                 },
@@ -605,7 +631,6 @@ void core_numbers_gpu(Graph& g, int mode, const uint8_t* alive, int32_t* core, h
     LDS_HIP(hipMemcpyAsync(h, ctr.p, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     LDS_HIP(hipStreamSynchronize(s));
     int32_t na = h[C_NA], k = 0;
-    const int most = wave::rows_at_once(mode == 2 ? g.max_deg : g.t_max);
     if (na > kTailMax) {  // the levels with many vertices: one cooperative launch
         static int cus = 0, per[2] = {0, 0};
         if (!cus) {
@@ -652,7 +677,6 @@ void core_numbers_gpu(Graph& g, int mode, const uint8_t* alive, int32_t* core, h
         pa.na = na;
         pa.k = 0;
         pa.tail_max = kTailMax;
-        pa.most = most;
         void* kargs[] = {&pa};
         LDS_HIP(hipLaunchCooperativeKernel(mode == 2 ? (const void*)k_peel_grid<false> : (const void*)k_peel_grid<true>,
                                            dim3((unsigned)grid), dim3(kPT), kargs, 0, s));
@@ -671,10 +695,10 @@ void core_numbers_gpu(Graph& g, int mode, const uint8_t* alive, int32_t* core, h
         k_fill_i32<<<grid_for(n, kT), kT, 0, s>>>(loc.p, n, -1);
         k_set<<<1, 1, 0, s>>>(ctr.p + 7, 0);
         if (mode == 2)
-            k_peel_tail<false><<<1, kTailT, 0, s>>>(act.p, na, k, most, loc.p, g.rowptr.p, g.col.p, nullptr, nullptr,
+            k_peel_tail<false><<<1, kTailT, 0, s>>>(act.p, na, k, loc.p, g.rowptr.p, g.col.p, nullptr, nullptr,
                                                     nullptr, nullptr, nullptr, cnt.p, core, ctr.p + 7);
         else
-            k_peel_tail<true><<<1, kTailT, 0, s>>>(act.p, na, k, most, loc.p, nullptr, nullptr, tp.own_row_of.p, tp.rp,
+            k_peel_tail<true><<<1, kTailT, 0, s>>>(act.p, na, k, loc.p, nullptr, nullptr, tp.own_row_of.p, tp.rp,
                                                    tp.py, tp.own_tos.p, talive.p, cnt.p, core, ctr.p + 7);
         LDS_HIP(hipGetLastError());
         LDS_CHECK(d2h_i32(ctr.p + 7, s) == 0, ST_DEVICE, "core peeling: no progress");

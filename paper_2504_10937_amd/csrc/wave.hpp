@@ -47,13 +47,6 @@ __device__ inline int64_t lane_of(int64_t v, int lane) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Rows (at most 64, at least one) whose slots a wave may number in 32 bits, with
-// room for a step past the last, when the longest row has `longest` slots.
-inline int rows_at_once(int64_t longest) {
-    const int64_t r = longest > 0 ? (((int64_t)1 << 31) - 1) / longest : 64;
-    return r < 1 ? 1 : r > 64 ? 64 : (int)r;
-}
-
 // inclusive scan: lane i ends with op over lanes 0..i (id: op's identity)
 template <class Op>
 __device__ inline int64_t scan(int64_t v, int64_t id, Op op) {

@@ -10,7 +10,6 @@
 #include "graph.hpp"
 #include "kept.hpp"
 #include "loadcode.hpp"
-#include "wave.hpp"
 
 namespace lds {
 void* dev_alloc(size_t, hipStream_t) { return nullptr; }
@@ -69,17 +68,6 @@ static void launches() {
             EXPECT(g >= 1 && g * 512 < (int64_t)1 << 32);
             EXPECT(g * per >= items || g == kStrideWG);
         }
-}
-
-// slots of up to 64 rows numbered in 32 bits by steps of 64 lanes and 4 a lane:
-// the last step's numbers do not wrap
-static void row_slots() {
-    for (int64_t longest : {(int64_t)0, (int64_t)1, (int64_t)1 << 24, ((int64_t)1 << 25) - 1, (int64_t)1 << 25,
-                            (int64_t)1 << 30, (int64_t)INT32_MAX}) {
-        const int64_t rows = wave::rows_at_once(longest);
-        EXPECT(rows >= 1 && rows <= 64 && rows * longest + 2 * 256 <= (int64_t)UINT32_MAX);
-        EXPECT(rows == 64 || longest >= (int64_t)1 << 25);
-    }
 }
 
 // codes of loads: monotone, and for the loads about a lone pattern's even split
@@ -155,7 +143,6 @@ int main() {
     bucket_places();
     chunk_rounds();
     load_codes();
-    row_slots();
     launches();
     edge_count();
     kept_offsets();
