@@ -11,7 +11,8 @@
 
 namespace lds {
 
-__host__ __device__ inline bool kept_in_32_bits(int64_t records) { return records <= (int64_t)UINT32_MAX; }
+// Edge plans always qualify: 2 (2^31 - 1) records (check_edge_count).
+inline bool kept_in_32_bits(int64_t records) { return records <= (int64_t)UINT32_MAX; }
 
 __host__ __device__ inline void keep_offset(uint32_t* kept, int64_t i, int64_t end) { kept[i] = (uint32_t)end; }
 

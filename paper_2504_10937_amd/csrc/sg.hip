@@ -1256,7 +1256,7 @@ __device__ inline long long search_kept(const ScanArgs& g, int64_t lo, int64_t h
     return first_kept(lo, hi, lo, evb, stb);
 }
 
-template <int H>
+template <int H, bool WIDE>
 __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* sh, int64_t* s_err) {
     __shared__ long long lred[2][kRW][3];
     LeadRed red{lred, 0};
@@ -1355,8 +1355,12 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
             // positions [fb, b) join the pending group S = [S0, b); the
             // frontier of the loads below and the end of S always coincide:
             // both start at the accepted boundary and move to every verified b
-            // P[b], from the kept window when it holds e
-            const int64_t k1 = e >= kept_lo && e < kept_hi ? kept_end(pw, g.narrow, kept_lo, e, g.P) : g.P[b];
+            // P[b], from the kept window when it holds e.  (Whether offsets fit
+            // 32 bits is known when compiling; for edges it is read at run time
+            // all the same: the leader spills 246 scalar registers so and 290
+            // otherwise, a 120k-vertex scan 5.5 ms and 5.9.)
+            const bool narrow = H == 2 ? g.narrow : !WIDE;
+            const int64_t k1 = e >= kept_lo && e < kept_hi ? kept_end(pw, narrow, kept_lo, e, g.P) : g.P[b];
             walked += k1 - kfb;
             // ahead only where the separate acceptance walk would be a grid
             // phase: a walk the leader runs alone costs less than the extra
@@ -1461,7 +1465,8 @@ __device__ void scan_leader(const ScanArgs& g, long long (*sred)[4], long long* 
     }
 }
 
-template <int H>
+// WIDE: a plan of 2^32 records or more (triangles: 3T)
+template <int H, bool WIDE>
 __global__ __launch_bounds__(kRT) void k_sg_scan(ScanArgs g) {
     __shared__ long long sred[kRW][4];
     __shared__ long long sh[4];
@@ -1469,7 +1474,7 @@ __global__ __launch_bounds__(kRT) void k_sg_scan(ScanArgs g) {
     if (threadIdx.x == 0) s_err = 0;
     __syncthreads();
     if (blockIdx.x == 0)
-        scan_leader<H>(g, sred, sh, &s_err);
+        scan_leader<H, WIDE>(g, sred, sh, &s_err);
     else
         scan_helper<H>(g, sred, &s_err);
     __syncthreads();
@@ -1746,8 +1751,8 @@ void sg_stable_groups(Graph& g, int mode, hipStream_t s) {
         int dev = 0;
         LDS_HIP(hipGetDevice(&dev));
         LDS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        LDS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per[0], k_sg_scan<2>, kRT, 0));
-        LDS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per[1], k_sg_scan<3>, kRT, 0));
+        LDS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per[0], k_sg_scan<2, false>, kRT, 0));
+        LDS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per[1], k_sg_scan<3, true>, kRT, 0));
     }
     const int64_t resident = (int64_t)cus * std::max(1, per[mode == 2 ? 0 : 1]);
     // the helpers only join the large phases, and each phase only as many of
@@ -1800,16 +1805,14 @@ void sg_stable_groups(Graph& g, int mode, hipStream_t s) {
     sa.rec2 = rv.rec2;
     sa.rec3 = rv.rec3;
     sa.rec3w = rv.rec3w;
+    const auto scan = mode == 2 ? k_sg_scan<2, false>
+                                : sa.narrow ? k_sg_scan<3, false> : k_sg_scan<3, true>;
     if (grid == 1) {  // one workgroup needs no co-residency guarantee
-        if (mode == 2)
-            k_sg_scan<2><<<1, kRT, 0, s>>>(sa);
-        else
-            k_sg_scan<3><<<1, kRT, 0, s>>>(sa);
+        scan<<<1, kRT, 0, s>>>(sa);
         LDS_HIP(hipGetLastError());
     } else {
         void* kargs[] = {&sa};
-        LDS_HIP(hipLaunchCooperativeKernel(mode == 2 ? (const void*)k_sg_scan<2> : (const void*)k_sg_scan<3>,
-                                           dim3((unsigned)grid), dim3(kRT), kargs, 0, s));
+        LDS_HIP(hipLaunchCooperativeKernel((const void*)scan, dim3((unsigned)grid), dim3(kRT), kargs, 0, s));
     }
     int64_t hinfo[16];
     LDS_HIP(hipMemcpyAsync(hinfo, info.p, sizeof(hinfo), hipMemcpyDeviceToHost, s));

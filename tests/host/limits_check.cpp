@@ -39,10 +39,12 @@ static void kept_offsets() {
             P[lo + i + 1] = last - (n - 1 - i) * (last >= n * per ? per : 1);
             keep_offset(kept.data(), i, P[lo + i + 1]);
         }
-        for (int64_t i = 0; i < n; ++i)
-            EXPECT(kept_end(kept.data(), kept_in_32_bits(last), lo, lo + i, P.data()) == P[lo + i + 1]);
+        for (int64_t i = 0; i < n; ++i) {
+            const int64_t e = lo + i;
+            EXPECT(kept_end(kept.data(), kept_in_32_bits(last), lo, e, P.data()) == P[e + 1]);
+        }
     }
-    EXPECT(kept_in_32_bits(top - 1) && !kept_in_32_bits(top));
+    EXPECT(kept_in_32_bits(top - 1) && !kept_in_32_bits(top) && kept_in_32_bits(2 * (int64_t)INT32_MAX));
 }
 
 // as include/lds.h promises for lds_create_graph
