@@ -862,9 +862,6 @@ int64_t build_heavy(SweepPlan& p, int64_t n, hipStream_t s) {
 
 }  // namespace
 
-// plans with fewer slots cut their hub rows into shorter pieces
-constexpr int64_t kPieceSlots = (int64_t)1 << 22;
-constexpr int kPieceSmall = 512;
 constexpr int64_t kPushSlots = (int64_t)1 << 21;
 
 void build_sweep_plan(SweepPlan& p, hipStream_t s, int64_t n_vertices) {
@@ -910,7 +907,7 @@ void build_sweep_plan(SweepPlan& p, hipStream_t s, int64_t n_vertices) {
     }
     // hub pieces and their per-row counters; a piece is one wave's, so small
     // plans cut shorter ones
-    p.piece = p.nslots >= kPieceSlots ? kPiece : kPieceSmall;
+    p.piece = piece_slots(p.nslots, 64 * p.hub_words, sweep_waves());
     p.n_pieces = 0;
     if (p.n_hub > 0 && n_heavy == 0) {
         DBuf<uint32_t> npc;

@@ -141,7 +141,21 @@ static void bucket_places() {
     }
 }
 
+// pieces are whole words, at most kPiece slots, longer in larger plans
+static void pieces() {
+    for (int64_t waves : {512, 4096}) {
+        int last = 0;
+        for (int64_t slots : {(int64_t)1100, waves * 128, waves * 128 + 64, kPieceSlots - 1, kPieceSlots, (int64_t)1 << 33}) {
+            const int p = piece_slots(slots, slots, waves);
+            EXPECT(p % 64 == 0 && p <= kPiece && p >= last);
+            EXPECT(piece_slots(slots, 1100, waves) <= p);
+            last = p;
+        }
+    }
+}
+
 int main() {
+    pieces();
     bucket_places();
     chunk_rounds();
     load_codes();
