@@ -1800,7 +1800,8 @@ void sg_stable_groups(Graph& g, int mode, hipStream_t s) {
     sa.part_work = std::max<int64_t>(1, env_i64("LDS_SCAN_PART_WORK", kPartWork));
     sa.lead_pos = env_i64("LDS_SCAN_LEAD_POS", kLeadPos);
     sa.P = rv.P;
-    sa.narrow = kept_in_32_bits(mode == 2 ? g.edge_plan.nslots : g.tri_plan.nslots);
+    // (LDS_SCAN_WIDE=1: as for a plan of 2^32 records)
+    sa.narrow = !env_i64("LDS_SCAN_WIDE", 0) && kept_in_32_bits(mode == 2 ? g.edge_plan.nslots : g.tri_plan.nslots);
     sa.own = rv.own;
     sa.rec2 = rv.rec2;
     sa.rec3 = rv.rec3;
